@@ -227,6 +227,7 @@ struct sg_ctx {
     std::vector<sg::QueueItem> h_qitems;
     uint8_t* dev = nullptr;
     hipStream_t stream = nullptr;
+    int32_t cus = 256;                 // compute units of the device bound to
     bool bound = false;
     std::vector<uint8_t> started;
     // Start energies left out by sg_init_spins: e_deferred marks the instances
@@ -1358,6 +1359,30 @@ void build_fmb_rows(const HostInst& q, std::vector<uint32_t>& out)
         }
 }
 
+// Widths of an instance's rows in the LDS row table of sg_fm_rows.hip: those
+// of its lane kernel rows, or the widest row of the sliced layout.
+void fm_row_widths(const HostInst& q, int32_t& dc, int32_t& tt)
+{
+    dc = tt = 0;
+    if (q.fml_off != UINT64_MAX) {
+        dc = q.fml_dc;
+        tt = q.fml_tt;
+        return;
+    }
+    for (const sg::Slice& S : q.slices) {
+        dc = std::max<int32_t>(dc, S.ew);
+        tt = std::max<int32_t>(tt, S.tw);
+    }
+    for (const sg::WSlice& S : q.w_slices) {
+        dc = std::max<int32_t>(dc, (int32_t)S.ew);
+        tt = std::max<int32_t>(tt, (int32_t)S.tw);
+    }
+}
+
+// Most LDS of a row-table workgroup (the kernel's static totals take the rest
+// of a compute unit's 160 KB).
+constexpr size_t kFmRowsLds = 160 * 1024 - 256;
+
 bool fml_candidate(const HostInst& q)
 {
     if (q.dense || q.wide || q.n > kFmlMaxN || q.max_w > kFmlMaxW) return false;
@@ -2352,6 +2377,30 @@ sg_status run_dense(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
     return SG_OK;
 }
 
+// Wavefronts per workgroup of the row-table pass kernel.  A workgroup's
+// wavefronts share one copy of the rows, so more of them hold more replicas
+// per compute unit, but the replicas of a small launch run fastest spread over
+// the compute units: the fewest wavefronts that keep every replica resident,
+// else the count with the most resident.  lds(w): a workgroup's LDS; items(w):
+// workgroups of the launch.
+template <class F, class G>
+int fm_rows_waves(int most, int cus, F&& lds, G&& items)
+{
+    int best = 0;
+    int64_t best_res = -1;
+    for (int w = 1; w <= most; ++w) {
+        const size_t b = lds(w);
+        if (b > kFmRowsLds) break;
+        const int64_t per_cu = std::min<int64_t>((int64_t)(160 * 1024 / (b + 256)), 32 / w);
+        if (per_cu * cus >= items(w)) return w;
+        if (per_cu * w > best_res) {
+            best_res = per_cu * w;
+            best = w;
+        }
+    }
+    return best;
+}
+
 // The pass-based search (SG_RULE_FM): every replica of every instance is one
 // wavefront item, largest instances first.
 sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
@@ -2359,9 +2408,20 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
     if (p->schedule != SG_SCHED_AUTO && p->schedule != SG_SCHED_FM)
         return fail(SG_EINVAL, "rule SG_RULE_FM runs under SG_SCHED_AUTO or SG_SCHED_FM only");
     int nmax = 1, lnmax = 1;
-    bool tri = false, key32 = true;
-    int64_t lane_reps = 0, wave_reps = 0;
+    bool tri = false, key32 = true, rtri = false;
+    int64_t lane_reps = 0, wave_reps = 0, row_reps = 0;
     auto on_lanes = [&](const HostInst& q) { return H->fm_lanes && q.fml_off != UINT64_MAX; };
+    // one replica per wavefront with the rows in LDS (sg_fm_rows.hip) where a
+    // workgroup of one wavefront holds them; the kernels of sg_fm.hip read
+    // what is larger from the sliced layout (dense graphs), and order moves
+    // on 64-bit keys when fm_key32 = 0 asks for them
+    auto on_rows = [&](const HostInst& q) {
+        if (on_lanes(q) || q.dense || q.n > kFmMaxN || !H->fm_key32) return false;
+        int32_t dc, tt;
+        fm_row_widths(q, dc, tt);
+        return sg::fm_rows_lds_bytes(q.n, dc, tt, q.wide != 0, 1) <= kFmRowsLds;
+    };
+    const int most_waves = H->fm_waves ? std::min(H->fm_waves, 16) : 16;
     int64_t big_reps = 0;
     for (const HostInst& q : H->insts) {
         if (q.n > kFmMaxN) {
@@ -2379,22 +2439,57 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
             lane_reps += q.R;
             continue;
         }
+        if (on_rows(q)) {
+            row_reps += q.R;
+            rtri = rtri || q.t > 0;
+            continue;
+        }
         wave_reps += q.R;
         nmax = std::max(nmax, q.n);
         tri = tri || q.t > 0;
         // 32-bit move keys: every gain |2 s f| < 2^19 and external indices below 4096
         key32 = key32 && 2 * q.max_w < (int64_t)1 << 19 && q.n <= 4096 && H->fm_key32;
     }
-    H->last_key32 = wave_reps && key32 ? 1 : 0;
+    H->last_key32 = (wave_reps && key32) || (!wave_reps && row_reps) ? 1 : 0;
     H->last_fm_lanes = (int32_t)std::min<int64_t>(lane_reps, INT32_MAX);
     hipStream_t st = H->stream;
     H->h_qitems.clear();
     for (size_t k = 0; k < H->insts.size(); ++k)
-        if (!on_lanes(H->insts[k]) && !H->insts[k].wide && H->insts[k].n <= kFmMaxN)
+        if (!on_lanes(H->insts[k]) && !H->insts[k].wide && H->insts[k].n <= kFmMaxN && !on_rows(H->insts[k]))
             for (int32_t r = 0; r < H->insts[k].R; ++r) H->h_qitems.push_back(sg::QueueItem{(int32_t)k, r});
     std::stable_sort(H->h_qitems.begin(), H->h_qitems.end(), [&](const sg::QueueItem& a, const sg::QueueItem& b) {
         return H->insts[a.inst].n > H->insts[b.inst].n;
     });
+    const size_t wave_items = H->h_qitems.size();
+    // the row-table items, after those of the other wavefront kernel: up to
+    // rw restarts of one instance each (their first restart, and their number
+    // above 16 bits), the largest instances first
+    int rw = 0;
+    size_t row_lds = 0;
+    if (row_reps) {
+        std::vector<size_t> on;
+        for (size_t k = 0; k < H->insts.size(); ++k)
+            if (!H->insts[k].wide && on_rows(H->insts[k])) on.push_back(k);
+        std::stable_sort(on.begin(), on.end(), [&](size_t a, size_t b) { return H->insts[a].n > H->insts[b].n; });
+        auto lds = [&](int w) {
+            size_t b = 0;
+            for (size_t k : on) {
+                int32_t dc, tt;
+                fm_row_widths(H->insts[k], dc, tt);
+                b = std::max(b, sg::fm_rows_lds_bytes(H->insts[k].n, dc, tt, false, w));
+            }
+            return b;
+        };
+        rw = fm_rows_waves(most_waves, H->cus, lds, [&](int w) {
+            int64_t c = 0;
+            for (size_t k : on) c += (H->insts[k].R + w - 1) / w;
+            return c;
+        });
+        row_lds = lds(rw);
+        for (size_t k : on)
+            for (int32_t r0 = 0; r0 < H->insts[k].R; r0 += rw)
+                H->h_qitems.push_back(sg::QueueItem{(int32_t)k, r0 | std::min(rw, H->insts[k].R - r0) << 16});
+    }
     // lane kernel items: restarts [r0, r0 + nr) of one instance per wavefront,
     // nr the largest multiple of 64 that still gives every resident wavefront
     // an item (a wavefront refills its lanes from its own item as replicas
@@ -2447,7 +2542,7 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
     // stage one instance's structure
     size_t stage = 0;
     for (const HostInst& q : H->insts)
-        if (!on_lanes(q) && !q.wide && q.n <= kFmMaxN)
+        if (!on_lanes(q) && !q.wide && q.n <= kFmMaxN && !on_rows(q))
             stage = std::max(stage, q.slices.size() * sizeof(sg::Slice) + q.nbr.size() * 4 + (tri ? q.ta.size() * 8 : 0));
     stage = (stage + 15) / 16 * 16;
     // wavefronts per workgroup: the most resident wavefronts per compute unit
@@ -2481,7 +2576,7 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
         }
     }
     if (waves == 0) return fail(SG_EINVAL, "rule SG_RULE_FM: no workgroup size fits LDS (fm_waves %d)", H->fm_waves);
-    H->last_fm_waves = wave_reps ? waves : 0;
+    H->last_fm_waves = wave_reps ? waves : rw;
     sg::QueueItem* dit = H->at<sg::QueueItem>(H->off_qitems);
     uint32_t* err = H->at<uint32_t>(H->off_err);
     SG_HIP(sg::launch_fill_u32(H->at<uint32_t>(H->off_stats), sizeof(sg::CallStats) / 4, 0u, st), "fill kernel");
@@ -2512,9 +2607,14 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
             ++lane_launches;
             a = b;
         }
-    if (p->max_sweeps > 0 && !H->h_qitems.empty())
+    if (p->max_sweeps > 0 && H->h_qitems.size() > wave_items)
+        SG_HIP(sg::launch_fm_rows(H->at<sg::InstTab>(H->off_tab), dit + wave_items,
+                                  (int)(H->h_qitems.size() - wave_items), rw, row_lds, rtri, H->reps(),
+                                  H->at<sg::CallStats>(H->off_stats), err, p->max_sweeps, p->until_converged, st),
+               "row-table pass kernel");
+    if (p->max_sweeps > 0 && wave_items)
         SG_HIP(sg::launch_fm(H->at<sg::InstTab>(H->off_tab), H->at<int32_t>(H->off_ctab), dit,
-                             (int)H->h_qitems.size(), nmax, waves, (int)stage, tri, key32, H->reps(),
+                             (int)wave_items, nmax, waves, (int)stage, tri, key32, H->reps(),
                              H->at<sg::CallStats>(H->off_stats),
                              err, p->max_sweeps, p->until_converged, st),
                "pass kernel");
@@ -2522,11 +2622,24 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
     int wide_launches = 0;
     for (const HostInst& q : H->insts)
         if (q.wide && q.n <= kFmMaxN && p->max_sweeps > 0) {
+            ++wide_launches;
+            if (on_rows(q)) {
+                int32_t dc, tt;
+                fm_row_widths(q, dc, tt);
+                const int w = fm_rows_waves(
+                    most_waves, H->cus, [&](int k) { return sg::fm_rows_lds_bytes(q.n, dc, tt, true, k); },
+                    [&](int k) { return ((int64_t)q.R + k - 1) / k; });
+                SG_HIP(sg::launch_fm_rows_wide(H->wview(q), H->at<int8_t>(q.off_spins), (int64_t)q.spin_stride,
+                                               H->reps() + q.rep_base, q.R, dc, tt, w,
+                                               H->at<sg::CallStats>(H->off_stats), err, p->max_sweeps,
+                                               p->until_converged, st),
+                       "wide row-table pass kernel");
+                continue;
+            }
             SG_HIP(sg::launch_fm_wide(H->wview(q), H->at<int8_t>(q.off_spins), (int64_t)q.spin_stride,
                                       H->reps() + q.rep_base, q.R, H->at<sg::CallStats>(H->off_stats), err,
                                       p->max_sweeps, p->until_converged, st),
                    "wide pass kernel");
-            ++wide_launches;
         }
     // instances beyond a wavefront's LDS: one launch, a wavefront per slot
     int big_launches = 0;
@@ -2548,7 +2661,8 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
     SG_HIP(hipEventRecord(H->evh1, st), "event record");
     SG_HIP(hipEventRecord(H->ev1, st), "event record");
     H->hot_launches =
-        p->max_sweeps > 0 ? lane_launches + (int)!H->h_qitems.empty() + wide_launches + big_launches : 0;
+        p->max_sweeps > 0 ? lane_launches + (int)(wave_items > 0) + (int)(row_reps > 0) + wide_launches + big_launches
+                          : 0;
     sg::CallStats cs;
     uint32_t herr = 0;
     CopiesOut out(H);
@@ -2871,8 +2985,7 @@ sg_status bind_impl(sg_handle H, void* dev_ptr, uint64_t bytes, void* hip_stream
             T.n_et = q.n_et;
             T.eterm_pad = 0;
             T.fml = q.fml_off == UINT64_MAX ? nullptr : H->at<uint32_t>(H->off_fml) + q.fml_off;
-            T.fml_dc = q.fml_dc;
-            T.fml_tt = q.fml_tt;
+            fm_row_widths(q, T.fml_dc, T.fml_tt);
             for (int32_t c = 0; c <= q.C; ++c) ctab.push_back(q.colour_slice[c]);
         }
         SG_HIP(hipMemcpyAsync(H->dev + H->off_tab, tab.data(), tab.size() * sizeof(sg::InstTab), hipMemcpyHostToDevice,
@@ -2935,6 +3048,10 @@ sg_status bind_impl(sg_handle H, void* dev_ptr, uint64_t bytes, void* hip_stream
     if (!H->evh0) SG_HIP(hipEventCreate(&H->evh0), "event create");
     if (!H->evh1) SG_HIP(hipEventCreate(&H->evh1), "event create");
     if (!H->ev1) SG_HIP(hipEventCreate(&H->ev1), "event create");
+    int dev_id = 0, cus = 0;
+    if (hipGetDevice(&dev_id) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id) == hipSuccess && cus > 0)
+        H->cus = cus;
     if (!H->pin && may_alloc) SG_HIP(hipHostMalloc((void**)&H->pin, kPinBytes, hipHostMallocDefault), "pinned buffer");
     H->bound = true;
     return SG_OK;

@@ -72,6 +72,17 @@ int fm_max_blocks_per_cu(int waves, size_t lds, bool tri, bool key32);
 hipError_t launch_fm(const InstTab* tab, const int32_t* ctab, const QueueItem* items, int nitems, int nmax, int waves,
                      int stage_cap, bool tri, bool key32, RepState* rs, CallStats* cs, uint32_t* err, int max_passes,
                      int until_conv, hipStream_t st);
+// The pass-based search on instances of at most 4096 spins whose term rows
+// fit LDS (sg_fm_rows.hip), a wavefront per replica: workgroup k of `waves`
+// wavefronts runs item k, restarts [r & 0xFFFF, + r >> 16) of one packed
+// instance with rows of the widths InstTab::fml_dc and fml_tt.
+// fm_rows_lds_bytes: the LDS of such a workgroup; a launch's lds is the
+// largest of its items'.  The wide form takes one instance a launch.
+size_t fm_rows_lds_bytes(int n, int dc, int tt, bool wide, int waves);
+hipError_t launch_fm_rows(const InstTab* tab, const QueueItem* items, int nitems, int waves, size_t lds, bool tri,
+                          RepState* rs, CallStats* cs, uint32_t* err, int max_passes, int until_conv, hipStream_t st);
+hipError_t launch_fm_rows_wide(const WideDev& I, int8_t* spins, int64_t stride, RepState* rs, int R, int dc, int tt,
+                               int waves, CallStats* cs, uint32_t* err, int max_passes, int until_conv, hipStream_t st);
 // The pass-based search on instances of more than 4096 spins (packed form,
 // term rows FmbRows per instance): one wavefront per slot takes the items
 // (replicas) from *counter, zero at launch; per slot slot_spins half-gains,

@@ -134,7 +134,8 @@ struct InstTab {
     // Per-spin term rows in external order for the lane-per-replica pass
     // kernel (null when the instance does not qualify; layout in
     // sg_fm_lanes.hip): fml_dc coupling words and fml_tt hyper-couplings per
-    // spin.
+    // spin.  Without such rows fml_dc and fml_tt are the widths of the sliced
+    // layout's widest row (the LDS rows of sg_fm_rows.hip).
     const uint32_t* fml;
     int32_t fml_dc, fml_tt;
 };
