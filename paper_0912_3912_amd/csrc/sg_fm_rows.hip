@@ -7,15 +7,18 @@
 // Everything is in external order.  The workgroup rebuilds the instance's
 // rows from the sliced layout once: per spin dc coupling words (partner << 8 |
 // J & 255; in the wide form pairs partner, J) and tt hyper-couplings (a << 8 |
-// K & 255 and b; in the wide form a, b, K), unused entries zero.  A wavefront
-// keeps its replica's half-gains v_e = -s_e f_e (int32), spins, move list and
-// the 64 leaf maxima (leaves of 64 spins); fmcore::run_pass moves the spins.
+// K & 255 and b; in the wide form a, b, K), unused entries with coefficient
+// zero, couplings among them naming the spin itself.  A wavefront
+// keeps its replica's half-gains v_e = -s_e f_e (int32), spins and move list
+// there, and the 64 leaf maxima (leaves of 64 spins) in registers; fmcore::run_pass moves the spins.
 //
 // The kernel is bound by the latency of its serial chain of moves (see
 // fmcore::run_pass): a 50 x 50 +-J lattice with 62 restarts to convergence
-// takes 15.0 ms here, 0.55 us a move, against 107 ms on k_fm, whose lanes each
-// rescan n / 64 spins one after another and look their rows up through the
-// sliced layout; with Gaussian int32 couplings 17.4 ms against 130 ms.
+// takes 10.2 ms here, 0.37 us or 970 cycles a move (about 115 instructions and
+// four LDS round trips), against 107 ms on k_fm, whose lanes each rescan n / 64
+// spins one after another and look their rows up through the sliced layout;
+// with Gaussian int32 couplings 10.2 ms against 130 ms.  With the device full
+// (8192 restarts, two passes) 13.7 ms against 166 ms.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -37,21 +40,44 @@ __host__ __device__ inline size_t rows_stage_bytes(int n, int dc, int tt, bool w
     const size_t w = (size_t)n * ((size_t)dc * (wide ? 8 : 4) + (size_t)tt * (wide ? 12 : 8));
     return (w + 15) & ~(size_t)15;
 }
-__host__ __device__ inline size_t rows_wave_bytes(int n) { return 7 * rows_n64(n) + 64 * 8; }
+__host__ __device__ inline size_t rows_wave_bytes(int n) { return 7 * rows_n64(n); }
 
 // The replica's LDS state and the rows, as fmcore::run_pass wants them.
 template <bool WIDE, bool TRI>
 struct RowsPolicy {
     static constexpr int kRL = 1;
     static constexpr bool kTri = TRI;
+    static constexpr int32_t kNone = INT32_MIN, kBias = 0;
     const uint32_t* cw;  // couplings
     const uint32_t* tw;  // hyper-couplings
     int32_t* half;
-    int2* lf;
     uint16_t* moves;
     int8_t* sp;
-    int dc_, tt_, lane;
+    int dc_, tt_, lane, qc;  // qc: this lane's coupling of a row, or any
 
+    static constexpr int32_t kLocked = INT32_MIN + 4095;
+    __device__ __forceinline__ void tag(int e, int step)
+    {
+        if (lane == 0) half[e] = INT32_MIN + step;
+    }
+    __device__ __forceinline__ int32_t fetch(int g) const { return half[g * 64 + lane]; }
+    __device__ __forceinline__ void part(int32_t w, int32_t& x, int32_t& at) const
+    {
+        x = w;
+        at = 0;
+    }
+    __device__ __forceinline__ void row(int e, int& j, int32_t& J) const
+    {
+        if constexpr (WIDE) {
+            const uint2 w = reinterpret_cast<const uint2*>(cw)[e * dc_ + qc];
+            j = (int)w.x;
+            J = (int32_t)w.y;
+        } else {
+            const uint32_t w = cw[e * dc_ + qc];
+            j = (int)(w >> 8);
+            J = (int8_t)(w & 0xffu);
+        }
+    }
     __device__ __forceinline__ int dc() const { return dc_; }
     __device__ __forceinline__ int tt() const { return tt_; }
     __device__ __forceinline__ int spin(int e) const { return sp[e]; }
@@ -60,13 +86,13 @@ struct RowsPolicy {
     __device__ __forceinline__ void add(int e, int32_t d) { atomicAdd(half + e, d); }
     __device__ __forceinline__ void lock(int e, int s, int step)
     {
-        half[e] = fmcore::kNone;
+        half[e] = kNone;
         sp[e] = (int8_t)-s;
         moves[step] = (uint16_t)e;
     }
     __device__ __forceinline__ int leaf(int e) const { return e >> 6; }
-    __device__ __forceinline__ int2 leaf_max(int g) const { return lf[g]; }
-    __device__ __forceinline__ void set_leaf(int g, int32_t m, int32_t a) { lf[g] = make_int2(m, a); }
+    __device__ __forceinline__ int2 leaf_max(int) const { return make_int2(0, 0); }  // one leaf per lane: registers
+    __device__ __forceinline__ void set_leaf(int, int32_t, int32_t) {}
     __device__ __forceinline__ void coupling(int e, int q, int& j, int32_t& J) const
     {
         if constexpr (WIDE) {
@@ -98,13 +124,8 @@ struct RowsPolicy {
             K = (int8_t)(wa & 0xffu);
         }
     }
-    __device__ __forceinline__ void scan(const int (&g)[2], int32_t (&m)[2], int32_t (&a)[2]) const
-    {
-        const int32_t x[2] = {half[g[0] * 64 + lane], half[g[1] * 64 + lane]};
-        fmcore::wave_max<2>(x, m);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) a[u] = g[u] * 64 + fmcore::first_lane(x[u] == m[u]);
-    }
+    __device__ __forceinline__ void load(int g, int32_t& x, int32_t& at) const { part(fetch(g), x, at); }
+    __device__ __forceinline__ int index(int g, int o, int32_t) const { return g * 64 + o; }
 };
 
 // What a workgroup runs: restarts [r0, r0 + nr) of one instance.
@@ -132,7 +153,16 @@ __device__ __forceinline__ void rows_body(const RowsInst I, const int dc, const 
     // the first wavefront's half-gains go
     uint32_t* ext = reinterpret_cast<uint32_t*>(state);
     for (int i = threadIdx.x; i < n; i += blockDim.x) ext[i] = I.ext[i];
-    for (int i = threadIdx.x; i < (int)(rows_stage_bytes(n, dc, tt, WIDE) / 4); i += blockDim.x) cw[i] = 0u;
+    for (int i = threadIdx.x; i < n * dc; i += blockDim.x) {
+        const uint32_t e = (uint32_t)(i / dc);
+        if (WIDE) {
+            cw[2 * i] = e;
+            cw[2 * i + 1] = 0u;
+        } else {
+            cw[i] = e << 8;
+        }
+    }
+    for (int i = threadIdx.x; i < n * tt * (WIDE ? 3 : 2); i += blockDim.x) tw[i] = 0u;
     __syncthreads();
     fill_rows(cw, tw, ext, wave, lane);
     __syncthreads();
@@ -147,12 +177,16 @@ __device__ __forceinline__ void rows_body(const RowsInst I, const int dc, const 
         p.cw = cw;
         p.tw = tw;
         p.half = reinterpret_cast<int32_t*>(base);
-        p.lf = reinterpret_cast<int2*>(base + 4 * n64);
-        p.moves = reinterpret_cast<uint16_t*>(base + 4 * n64 + 512);
-        p.sp = reinterpret_cast<int8_t*>(base + 6 * n64 + 512);
+        p.moves = reinterpret_cast<uint16_t*>(base + 4 * n64);
+        p.sp = reinterpret_cast<int8_t*>(base + 6 * n64);
         p.dc_ = dc;
         p.tt_ = tt;
         p.lane = lane;
+        p.qc = lane < dc ? lane : 0;
+        // rows of at most 64 couplings and no hyper-couplings: the shorter
+        // move loop, in which a locked spin's value is the step it moved at
+        // (every half-gain lies above: the host checks)
+        const bool pairs = !TRI && dc > 0 && dc <= 64;
         int8_t* gs = I.spins + I.stride * r;
         for (int i = lane; i < n; i += 64) p.sp[I.ext[i]] = gs[i];
         const long long E0 = st->E;  // the same in every lane: kept in scalar registers
@@ -167,10 +201,10 @@ __device__ __forceinline__ void rows_body(const RowsInst I, const int dc, const 
             // |coefficients|
             for (int i = lane; i < n; i += 64) p.half[I.ext[i]] = field(i);
             fmcore::order();
-            int32_t mx[1] = {fmcore::kNone}, ix[1] = {0};
+            fmcore::Leaves<1> mx = INT32_MIN, ix = 0;
             for (int g = 0; g * 64 < n; ++g) {
                 const int e = g * 64 + lane;
-                int32_t v = fmcore::kNone;
+                int32_t v = INT32_MIN;
                 if (e < n) {
                     int32_t f = p.half[e];
                     for (int q = 0; q < dc; ++q) {
@@ -198,19 +232,27 @@ __device__ __forceinline__ void rows_body(const RowsInst I, const int dc, const 
                     ix[0] = a;
                 }
             }
-            p.lf[lane] = make_int2(mx[0], ix[0]);
             fmcore::order();
             long long Elow = Estar;
-            const int len = fmcore::run_pass(p, n, lane, Elow, mx, ix);
+            int len;
+            if (pairs) {
+                if constexpr (!TRI) len = fmcore::run_pass_pairs(p, n, lane, Elow, mx, ix);
+            } else {
+                len = fmcore::run_pass(p, n, lane, Elow, mx, ix);
+            }
             if (len < 0) {
                 bad = true;
                 break;
             }
             fmcore::order();
-            // undo the moves after the best prefix
-            for (int t = len + lane; t < n; t += 64) {
-                const int e = p.moves[t];
-                p.sp[e] = (int8_t)-p.sp[e];
+            if (pairs) {  // make the moves of the best prefix
+                for (int e = lane; e < n; e += 64)
+                    if ((uint32_t)p.half[e] - 0x80000000u < (uint32_t)len) p.sp[e] = (int8_t)-p.sp[e];
+            } else {  // undo the moves after it
+                for (int t = len + lane; t < n; t += 64) {
+                    const int e = p.moves[t];
+                    p.sp[e] = (int8_t)-p.sp[e];
+                }
             }
             fmcore::order();
             ++passes;

@@ -182,6 +182,10 @@ struct sg_ctx {
     int32_t fm_slots = 0;
     int32_t fmb_nmax = 0;
     int64_t fmb_reps = 0, fmb_slot_spins = 0, fmb_slot_leaves = 0;
+    // their replicas by kernel (fm_big_class), the largest instance of each
+    // and whether one of them has hyper-couplings
+    int64_t fmb_class_reps[3] = {0, 0, 0};
+    int32_t fmb_class_nmax[3] = {0, 0, 0}, fmb_class_tri[3] = {0, 0, 0};
     uint64_t off_fmb_half = 0, off_fmb_moves = 0, off_fmb_leaf = 0, off_fmb_spin = 0, off_fmb_ptr = 0,
              off_fmb_items = 0, off_fmb_cnt = 0;
     int32_t last_fm_big = 0;           // replicas of the last FM call run on that kernel
@@ -1303,15 +1307,48 @@ bool fmb_candidate(const HostInst& q, int32_t* dc = nullptr, int32_t* tt = nullp
     return true;
 }
 
+// Kernel of such an instance: 0 and 1 keep its half-gains in LDS
+// (sg_fm_mid.hip), as bytes where every half-gain fits one and as int32, up to
+// the sizes 160 KB hold; 2 keeps them in device memory (sg_fm_big.hip).  In
+// LDS a move takes about 0.7 us but a compute unit holds only 160 KB's worth
+// of replicas; in device memory 4.1 us with up to four replicas a compute
+// unit, 5.3 with eight and 7.2 with sixteen (200 x 200 and 190 x 190
+// lattices), so beyond six replicas a compute unit for each that LDS holds the
+// latter moves more spins a second (190 x 190, int32, 2048 at once: 191 ms
+// against 209 ms in LDS; 200 x 200 in bytes, 4096 at once: 286 against 185).
+int fm_big_class(const HostInst& q, int64_t at_once, int cus)
+{
+    const int c = !q.wide && q.max_w <= 127 && q.n <= sg::fm_mid_max_n(true) ? 0
+                  : q.n <= sg::fm_mid_max_n(false)                           ? 1
+                                                                             : 2;
+    if (c < 2 && at_once > 6 * (int64_t)cus * (int64_t)(160 * 1024 / sg::fm_mid_lds_bytes(q.n, c == 0))) return 2;
+    return c;
+}
+
 int32_t fmb_stride(const HostInst& q) { return q.wide ? 1 + 2 * q.fmb_dc + 3 * q.fmb_tt : 1 + q.fmb_dc + 2 * q.fmb_tt; }
 
 // The large-instance pass kernel's rows (FmbRows): per spin in external order
 // its field, its nonzero couplings and hyper-couplings with partners in
-// external order, zero-padded to q.fmb_dc and q.fmb_tt.
+// external order, padded to q.fmb_dc and q.fmb_tt by entries that name the
+// spin itself with coefficient zero.
 void build_fmb_rows(const HostInst& q, std::vector<uint32_t>& out)
 {
     const int32_t dc = q.fmb_dc, stride = fmb_stride(q);
-    out.assign((size_t)q.n * stride, 0u);
+    out.resize((size_t)q.n * stride);
+    for (uint32_t e = 0; e < (uint32_t)q.n; ++e) {
+        uint32_t* row = out.data() + (size_t)e * stride;
+        const uint32_t self = q.wide ? e : e << 8;
+        uint32_t* end = row + 1 + (q.wide ? 2 : 1) * dc;
+        for (uint32_t* w = row + 1; w < end; w += q.wide ? 2 : 1) {
+            w[0] = self;
+            if (q.wide) w[1] = 0u;
+        }
+        for (uint32_t* w = end; w < row + stride; w += q.wide ? 3 : 2) {
+            w[0] = self;
+            w[1] = e;
+            if (q.wide) w[2] = 0u;
+        }
+    }
     if (!q.wide) {
         for (const sg::Slice& S : q.slices)
             for (int32_t l = 0; l < S.rows; ++l) {
@@ -2415,12 +2452,33 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
     // workgroup of one wavefront holds them; the kernels of sg_fm.hip read
     // what is larger from the sliced layout (dense graphs), and order moves
     // on 64-bit keys when fm_key32 = 0 asks for them
+    bool rows = true;
     auto on_rows = [&](const HostInst& q) {
+        if (!q.wide && !rows) return false;
         if (on_lanes(q) || q.dense || q.n > kFmMaxN || !H->fm_key32) return false;
+        if (q.max_w >= INT32_MAX - kFmMaxN) return false;  // locked spins take the values below -2^31 + 4096
         int32_t dc, tt;
         fm_row_widths(q, dc, tt);
         return sg::fm_rows_lds_bytes(q.n, dc, tt, q.wide != 0, 1) <= kFmRowsLds;
     };
+    // The two packed kernels run one after the other.  A row-table move takes
+    // about an eighth of the other kernel's time, and few replicas cost the
+    // chain of their largest instance: with instances left to the other
+    // kernel, a row-table launch beside it pays if its largest instance is
+    // the larger, or if its replicas fill the device (30 instances of
+    // 200..1070 spins, the densest too large: 48 ms in two launches, 38 ms in
+    // one)
+    {
+        int32_t nr = 0, no = 0;
+        int64_t reps = 0;
+        for (const HostInst& q : H->insts)
+            if (!q.wide && q.n <= kFmMaxN && !on_lanes(q)) {
+                const bool r = on_rows(q);
+                (r ? nr : no) = std::max(r ? nr : no, q.n);
+                reps += r ? q.R : 0;
+            }
+        rows = no == 0 || (int64_t)nr * 8 > (int64_t)no * 9 || reps > 16 * H->cus;
+    }
     const int most_waves = H->fm_waves ? std::min(H->fm_waves, 16) : 16;
     int64_t big_reps = 0;
     for (const HostInst& q : H->insts) {
@@ -2641,22 +2699,37 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
                                       p->max_sweeps, p->until_converged, st),
                    "wide pass kernel");
         }
-    // instances beyond a wavefront's LDS: one launch, a wavefront per slot
+    // instances beyond 4096 spins: one launch per kernel, a wavefront per slot
     int big_launches = 0;
     H->last_fm_big = 0;
     if (big_reps && p->max_sweeps > 0) {
-        SG_HIP(sg::launch_fill_u32(H->at<uint32_t>(H->off_fmb_cnt), 1, 0u, st), "fill kernel");
+        SG_HIP(sg::launch_fill_u32(H->at<uint32_t>(H->off_fmb_cnt), 3, 0u, st), "fill kernel");
         const int slots = (int)std::min<int64_t>(H->fm_slots, H->fmb_reps);
-        SG_HIP(sg::launch_fm_big(H->at<sg::InstTab>(H->off_tab), H->at<sg::FmbRows>(H->off_fmb_ptr),
-                                 H->at<sg::QueueItem>(H->off_fmb_items), (int)H->fmb_reps,
-                                 H->at<uint32_t>(H->off_fmb_cnt), H->at<int32_t>(H->off_fmb_half),
-                                 H->at<int32_t>(H->off_fmb_moves), H->at<uint64_t>(H->off_fmb_leaf),
-                                 H->at<int8_t>(H->off_fmb_spin), H->fmb_slot_spins, H->fmb_slot_leaves, slots,
-                                 (int)((H->fmb_slot_leaves + 63) / 64), H->reps(), H->at<sg::CallStats>(H->off_stats),
-                                 err, p->max_sweeps, p->until_converged, st),
-               "large-instance pass kernel");
+        const sg::QueueItem* items = H->at<sg::QueueItem>(H->off_fmb_items);
+        for (int c = 0; c < 3; ++c) {
+            const int reps = (int)H->fmb_class_reps[c];
+            if (!reps) continue;
+            uint32_t* counter = H->at<uint32_t>(H->off_fmb_cnt) + c;
+            if (c < 2)
+                SG_HIP(sg::launch_fm_mid(H->at<sg::InstTab>(H->off_tab), H->at<sg::FmbRows>(H->off_fmb_ptr), items,
+                                         reps, H->fmb_class_nmax[c], c == 0, H->fmb_class_tri[c] != 0, counter,
+                                         H->at<int32_t>(H->off_fmb_moves), H->fmb_slot_spins, slots, H->reps(),
+                                         H->at<sg::CallStats>(H->off_stats), err, p->max_sweeps, p->until_converged,
+                                         st),
+                       "pass kernel with half-gains in LDS");
+            else
+                SG_HIP(sg::launch_fm_big(H->at<sg::InstTab>(H->off_tab), H->at<sg::FmbRows>(H->off_fmb_ptr), items,
+                                         reps, counter, H->at<int32_t>(H->off_fmb_half),
+                                         H->at<int32_t>(H->off_fmb_moves), H->at<uint64_t>(H->off_fmb_leaf),
+                                         H->at<int8_t>(H->off_fmb_spin), H->fmb_slot_spins, H->fmb_slot_leaves, slots,
+                                         (int)((H->fmb_slot_leaves + 63) / 64), H->reps(),
+                                         H->at<sg::CallStats>(H->off_stats), err, p->max_sweeps, p->until_converged,
+                                         st),
+                       "large-instance pass kernel");
+            items += reps;
+            ++big_launches;
+        }
         H->last_fm_big = (int32_t)std::min<int64_t>(big_reps, INT32_MAX);
-        big_launches = 1;
     }
     SG_HIP(hipEventRecord(H->evh1, st), "event record");
     SG_HIP(hipEventRecord(H->ev1, st), "event record");
@@ -2875,6 +2948,10 @@ sg_status bind_impl(sg_handle H, void* dev_ptr, uint64_t bytes, void* hip_stream
     std::fill(H->started.begin(), H->started.end(), 0);
     H->e_pending = false;
     H->e_deferred.assign(H->insts.size(), 0);
+    int dev_id = 0, cus = 0;
+    if (hipGetDevice(&dev_id) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id) == hipSuccess && cus > 0)
+        H->cus = cus;
     hipStream_t st = H->stream;
     for (const HostInst& q : H->insts) {
         SG_HIP(hipMemcpyAsync(H->dev + q.off_nbr, q.nbr.data(), q.nbr.size() * 4, hipMemcpyHostToDevice, st),
@@ -2999,6 +3076,19 @@ sg_status bind_impl(sg_handle H, void* dev_ptr, uint64_t bytes, void* hip_stream
             std::vector<sg::FmbRows> ptr(H->insts.size(), sg::FmbRows{nullptr, 0, 0, 0, 0});
             std::vector<sg::QueueItem> items;
             std::vector<uint32_t> rows;
+            const int64_t at_once = std::min<int64_t>(H->fm_slots, H->fmb_reps);
+            for (int c = 0; c < 3; ++c) {
+                H->fmb_class_reps[c] = 0;
+                H->fmb_class_nmax[c] = H->fmb_class_tri[c] = 0;
+                for (size_t k = 0; k < H->insts.size(); ++k) {
+                    const HostInst& q = H->insts[k];
+                    if (q.off_fmb_rows == UINT64_MAX || fm_big_class(q, at_once, H->cus) != c) continue;
+                    H->fmb_class_reps[c] += q.R;
+                    H->fmb_class_nmax[c] = std::max(H->fmb_class_nmax[c], q.n);
+                    H->fmb_class_tri[c] |= q.t > 0 ? 1 : 0;
+                    for (int32_t r = 0; r < q.R; ++r) items.push_back(sg::QueueItem{(int32_t)k, r});
+                }
+            }
             for (size_t k = 0; k < H->insts.size(); ++k) {
                 const HostInst& q = H->insts[k];
                 if (q.off_fmb_rows == UINT64_MAX) continue;
@@ -3006,7 +3096,6 @@ sg_status bind_impl(sg_handle H, void* dev_ptr, uint64_t bytes, void* hip_stream
                 SG_HIP(hipMemcpy(H->dev + q.off_fmb_rows, rows.data(), rows.size() * 4, hipMemcpyHostToDevice),
                        "upload pass rows");
                 ptr[k] = sg::FmbRows{H->at<uint32_t>(q.off_fmb_rows), fmb_stride(q), q.fmb_dc, q.fmb_tt, q.wide};
-                for (int32_t r = 0; r < q.R; ++r) items.push_back(sg::QueueItem{(int32_t)k, r});
             }
             SG_HIP(hipMemcpy(H->dev + H->off_fmb_ptr, ptr.data(), ptr.size() * sizeof(sg::FmbRows),
                              hipMemcpyHostToDevice),
@@ -3048,10 +3137,6 @@ sg_status bind_impl(sg_handle H, void* dev_ptr, uint64_t bytes, void* hip_stream
     if (!H->evh0) SG_HIP(hipEventCreate(&H->evh0), "event create");
     if (!H->evh1) SG_HIP(hipEventCreate(&H->evh1), "event create");
     if (!H->ev1) SG_HIP(hipEventCreate(&H->ev1), "event create");
-    int dev_id = 0, cus = 0;
-    if (hipGetDevice(&dev_id) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id) == hipSuccess && cus > 0)
-        H->cus = cus;
     if (!H->pin && may_alloc) SG_HIP(hipHostMalloc((void**)&H->pin, kPinBytes, hipHostMallocDefault), "pinned buffer");
     H->bound = true;
     return SG_OK;

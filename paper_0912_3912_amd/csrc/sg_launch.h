@@ -92,6 +92,15 @@ hipError_t launch_fm_big(const InstTab* tab, const FmbRows* rows, const QueueIte
                          uint32_t* counter, int32_t* half, int32_t* moves, uint64_t* leaf, int8_t* spins,
                          int64_t slot_spins, int64_t slot_leaves, int slots, int top_cap, RepState* rs, CallStats* cs,
                          uint32_t* err, int max_passes, int until_conv, hipStream_t st);
+// The same on instances whose half-gains one compute unit's LDS holds
+// (sg_fm_mid.hip): bytes where every spin's sum of |coefficients| is at most
+// 127 (packed form), else int32, up to fm_mid_max_n spins; of the slots only
+// the move lists are used.  nmax: the largest instance of the launch.
+int fm_mid_max_n(bool bytes);
+size_t fm_mid_lds_bytes(int n, bool bytes);  // a workgroup's LDS
+hipError_t launch_fm_mid(const InstTab* tab, const FmbRows* rows, const QueueItem* items, int nitems, int nmax,
+                         bool bytes, bool tri, uint32_t* counter, int32_t* moves, int64_t slot_spins, int slots,
+                         RepState* rs, CallStats* cs, uint32_t* err, int max_passes, int until_conv, hipStream_t st);
 // The pass-based search on one instance in the wide form (at most 4096
 // spins), one wavefront per replica of [0, R); rs and spins are the
 // instance's own.
