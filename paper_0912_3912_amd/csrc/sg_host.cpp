@@ -213,6 +213,10 @@ struct sg_ctx {
     uint64_t off_dtab = 0, off_ditems = 0;
     std::vector<sg::BlockItem> h_ditems;  // (instance, first restart, count <= 64)
     int32_t dense_nmax = 1;
+    // energy tables of the pass-based search: how many the workspace holds at
+    // once, the largest instance that uses one, where they stand
+    int32_t dense_tables = 0, dense_table_n = 0;
+    uint64_t off_dense_table = 0;
     hipStream_t cap_stream = nullptr;  // private stream used only to record graphs
     uint64_t off_tbase = 0;            // one sweep base per instance (graph replays)
     uint64_t off_tab = 0, off_ctab = 0, off_bitems = 0, off_qitems = 0, off_qcnt = 0;
@@ -1483,6 +1487,40 @@ void build_fml(const HostInst& q, std::vector<uint32_t>& out, int32_t dc, int32_
         }
 }
 
+// Energy tables (sg_dense.hip) for the pass-based search of a dense handle:
+// instances of at most kDenseTableMaxN spins share room for up to 32 MiB of
+// tables and run in rounds of as many instances as that holds.  A step takes
+// a round about 1.5 us and its table and launches about 20 us, on three passes
+// or so; without a table a step takes about 0.45 us per term of the picked
+// spin, for up to ~3000 wavefronts of 64 replicas at once (12 per compute
+// unit).  20 spins, 3135 terms: 15000 replicas 31 ms by terms, 0.2 ms by the
+// table; 64 replicas 19.7 against 0.17 ms; 21 = 3 x 7 (3 spins, 7 terms) stays
+// by terms.
+void dense_tables(sg_ctx* H, uint64_t off)
+{
+    H->dense_tables = H->dense_table_n = 0;
+    int64_t items = 0, insts = 0;
+    double per_spin = 0.0;
+    for (const HostInst& q : H->insts) {
+        if (!q.dense || q.n > sg::kDenseTableMaxN) continue;
+        ++insts;
+        items += (q.R + 63) / 64;
+        H->dense_table_n = std::max(H->dense_table_n, q.n);
+        per_spin = std::max(per_spin, (double)q.d_start[(size_t)q.n] / q.n);
+    }
+    if (!insts) return;
+    const int64_t each = (int64_t)8 << H->dense_table_n;
+    int64_t k = std::min<int64_t>(std::min<int64_t>(insts, 65535), ((int64_t)32 << 20) / each);
+    // the tables take no handle beyond sg_bind_noalloc's workspace
+    if (off <= SG_NOALLOC_MAX_BYTES) k = std::min<int64_t>(k, (int64_t)(SG_NOALLOC_MAX_BYTES - off) / each);
+    if (k < 1) return;
+    const double steps = 3.0 * H->dense_table_n;
+    const double by_table = (double)((insts + k - 1) / k) * (20.0 + 1.5 * steps);
+    const double by_terms = 0.45 * per_spin * steps * std::max(1.0, (double)items / (12.0 * 256.0));
+    if (by_table >= by_terms) return;
+    H->dense_tables = (int32_t)k;
+}
+
 void layout(sg_ctx* H)
 {
     // the lane path keeps one wavefront per 64 replicas busy with a whole
@@ -1654,6 +1692,8 @@ void layout(sg_ctx* H)
         H->off_fmb_items = take((uint64_t)H->fmb_reps * sizeof(sg::QueueItem));
         H->off_fmb_cnt = take(64);
     }
+    dense_tables(H, off);
+    if (H->dense_tables) H->off_dense_table = take((uint64_t)H->dense_tables * 8 << H->dense_table_n);
     H->bytes = off;
 }
 
@@ -2385,15 +2425,44 @@ sg_status run_dense(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
     SG_HIP(sg::launch_fill_u32(H->at<uint32_t>(H->off_stats), sizeof(sg::CallStats) / 4, 0u, st), "fill kernel");
     SG_HIP(hipEventRecord(H->ev0, st), "event record");
     SG_HIP(hipEventRecord(H->evh0, st), "event record");
-    if (p->max_sweeps > 0)
+    H->hot_launches = 0;
+    if (p->max_sweeps > 0 && p->rule == SG_RULE_FM && H->dense_tables) {
+        // instances in order: those with a table in rounds of as many as the
+        // workspace holds, runs of larger ones without
+        const int count = (int)H->insts.size();
+        size_t it = 0;
+        for (int a = 0, b; a < count; a = b) {
+            const bool tab = H->insts[(size_t)a].n <= sg::kDenseTableMaxN;
+            b = a;
+            size_t ie = it;
+            while (b < count && (H->insts[(size_t)b].n <= sg::kDenseTableMaxN) == tab &&
+                   (!tab || b - a < H->dense_tables))
+                ie += ((size_t)H->insts[(size_t)b++].R + 63) / 64;
+            const sg::BlockItem* items = H->at<sg::BlockItem>(H->off_ditems) + it;
+            if (tab)
+                SG_HIP(sg::launch_dense_fm_table(H->at<sg::DenseTab>(H->off_dtab), a, b - a, items, (int)(ie - it),
+                                                 H->at<int64_t>(H->off_dense_table), H->dense_table_n, H->reps(),
+                                                 H->at<sg::CallStats>(H->off_stats), p->max_sweeps, p->until_converged,
+                                                 st),
+                       "dense table kernels");
+            else
+                SG_HIP(sg::launch_dense_run(H->at<sg::DenseTab>(H->off_dtab), items, (int)(ie - it), H->dense_nmax,
+                                            H->reps(), H->at<sg::CallStats>(H->off_stats), p->rule, p->max_sweeps,
+                                            p->until_converged, p->seed, st),
+                       "dense kernel");
+            ++H->hot_launches;
+            it = ie;
+        }
+    } else if (p->max_sweeps > 0) {
+        H->hot_launches = 1;
         SG_HIP(sg::launch_dense_run(H->at<sg::DenseTab>(H->off_dtab), H->at<sg::BlockItem>(H->off_ditems),
                                     (int)H->h_ditems.size(), H->dense_nmax, H->reps(),
                                     H->at<sg::CallStats>(H->off_stats), p->rule, p->max_sweeps, p->until_converged,
                                     p->seed, st),
                "dense kernel");
+    }
     SG_HIP(hipEventRecord(H->evh1, st), "event record");
     SG_HIP(hipEventRecord(H->ev1, st), "event record");
-    H->hot_launches = p->max_sweeps > 0 ? 1 : 0;
     sg::CallStats cs;
     SG_HIP(hipMemcpyAsync(&cs, H->at<sg::CallStats>(H->off_stats), sizeof cs, hipMemcpyDeviceToHost, st), "stats copy");
     SG_HIP(hipStreamSynchronize(st), "stream sync");

@@ -128,6 +128,13 @@ hipError_t launch_dense_init(const DenseTab* tabs, const BlockItem* items, int n
 hipError_t launch_dense_energy(const DenseTab* tabs, const BlockItem* items, int nitems, int64_t* out, hipStream_t st);
 hipError_t launch_dense_run(const DenseTab* tabs, const BlockItem* items, int nitems, int nmax, RepState* rs,
                             CallStats* cs, int rule, int max_sweeps, int until_conv, uint64_t seed, hipStream_t st);
+// The pass-based search by a table of all 2^n energies: builds the tables of
+// instances [inst0, inst0 + ninst), each of 2^nmax entries (nmax: the largest
+// instance, at most kDenseTableMaxN spins), then runs their items.
+constexpr int kDenseTableMaxN = 22;
+hipError_t launch_dense_fm_table(const DenseTab* tabs, int inst0, int ninst, const BlockItem* items, int nitems,
+                                 int64_t* table, int nmax, RepState* rs, CallStats* cs, int max_passes, int until_conv,
+                                 hipStream_t st);
 // One workgroup per replica of a small lattice.  With a WgSolve the launch is
 // a whole solve: it draws each replica's start (seed also keys the start),
 // runs the sweeps from sweep 0, and leaves the replica state (exact final
