@@ -396,8 +396,8 @@ sg_status sg_solve(sg_handle h, const sg_run_params* p, sg_run_stats* stats, int
  *                        units of block_rg: its slots take the next restart
  *                        as replicas stop (0 = up to 4, fewer when the
  *                        workgroups would not fill the GPU; at most 64)
- *   "block_bits"         1: GREEDY on the block schedule uses the bit-sliced
- *                        kernel (32 restarts per word) for instances of at
+ *   "block_bits"         1: the block schedule uses the bit-sliced kernel (32
+ *                        restarts per word, GREEDY and GREEDY_TIE) for instances of at
  *                        most 2048 spins whose coefficients are at most 15
  *                        in magnitude and sum to at most 255 per spin; 0:
  *                        always the byte kernel (default 1)

@@ -2172,17 +2172,17 @@ int bits_ng_for(const sg_ctx* H, const HostInst& q)
 }
 
 // LDS of the bit-sliced block kernel for instance q (0 if it does not apply).
-size_t bits_lds_for(const sg_ctx* H, const HostInst& q)
+size_t bits_lds_for(const sg_ctx* H, const HostInst& q, bool tie)
 {
     if (!q.bits_ok) return 0;
     const size_t lds = sg::block_bits_lds_bytes(q.n, (int)q.nbr.size(), (int)q.ta.size(), (int)q.slices.size(), q.C,
-                                                bits_ng_for(H, q));
+                                                bits_ng_for(H, q), tie);
     return lds <= kLdsBudget ? lds : 0;
 }
 
 sg_status run_block_bits_ng(sg_handle H, const sg_run_params* p, const std::vector<int>& which, int NG);
 
-// GREEDY on the bit-sliced block kernel: one workgroup per range of restarts
+// GREEDY or GREEDY_TIE on the bit-sliced block kernel: one workgroup per range of restarts
 // (up to four workgroup-fulls of groups of 32, taken in turn as groups stop);
 // a finished group computes its restarts' energies from their final spins.
 sg_status run_block_bits(sg_handle H, const sg_run_params* p, const std::vector<int>& which_all)
@@ -2206,16 +2206,17 @@ sg_status run_block_bits(sg_handle H, const sg_run_params* p, const std::vector<
 sg_status run_block_bits_ng(sg_handle H, const sg_run_params* p, const std::vector<int>& which, int NG)
 {
     hipStream_t st = H->stream;
+    const bool tie = p->rule == SG_RULE_GREEDY_TIE;
     size_t lds = 0;
     int64_t groups = 0;
     for (int qi : which) {
         const HostInst& q = H->insts[qi];
-        lds = std::max(lds, bits_lds_for(H, q));
+        lds = std::max(lds, bits_lds_for(H, q, tie));
         groups += (q.R + 31) / 32;
     }
     int m = H->block_groups;
     if (m <= 0) {
-        const int cap = std::max(1, sg::block_bits_max_blocks(lds, NG));
+        const int cap = std::max(1, sg::block_bits_max_blocks(lds, NG, tie));
         m = (int)std::max<int64_t>(1, std::min<int64_t>(kBlockGroupsAuto, groups / ((int64_t)NG * cap)));
     }
     H->h_bitems.clear();
@@ -2233,7 +2234,7 @@ sg_status run_block_bits_ng(sg_handle H, const sg_run_params* p, const std::vect
     SG_HIP(hipEventRecord(H->evh0, st), "event record");
     SG_HIP(sg::launch_block_bits(H->at<sg::InstTab>(H->off_tab), H->at<int32_t>(H->off_ctab), dit,
                                  (int)H->h_bitems.size(), lds, H->reps(), H->at<sg::CallStats>(H->off_stats), NG,
-                                 p->max_sweeps, p->until_converged, st),
+                                 p->max_sweeps, p->seed, p->rule, p->until_converged, st),
            "bit-sliced block kernel");
     SG_HIP(hipEventRecord(H->evh1, st), "event record");
     H->hot_launches = 1;
@@ -2245,7 +2246,7 @@ sg_status run_block_bits_ng(sg_handle H, const sg_run_params* p, const std::vect
 // The block schedule runs this instance on the bit-sliced kernel.
 bool bits_path(const sg_ctx* H, const sg_run_params* p, const HostInst& q)
 {
-    return H->block_bits && p->rule == SG_RULE_GREEDY && p->max_sweeps > 0 && bits_lds_for(H, q) > 0;
+    return H->block_bits && p->max_sweeps > 0 && bits_lds_for(H, q, p->rule == SG_RULE_GREEDY_TIE) > 0;
 }
 
 sg_status run_block_schedule(sg_handle H, const sg_run_params* p, const std::vector<int>& which_all)
@@ -2858,7 +2859,7 @@ sg_status sg_internal_validate(const sg_instance_desc* d) { return validate(*d, 
 bool defer_lane_energy(const sg_ctx* H, const HostInst& q)
 {
     return H->defer_energy && H->block_bits && q.bits_ok && !q.lat_ok && q.R >= H->block_min_restarts &&
-           can_block(H, q) && bits_lds_for(H, q) > 0;
+           can_block(H, q) && bits_lds_for(H, q, false) > 0;
 }
 
 // The lattice schedule would run this instance on the bit-plane tile kernel

@@ -159,12 +159,14 @@ size_t block_lds_bytes(int n, int nbr_words, int tri_words, int nslices, int C, 
 hipError_t launch_block(const InstTab* tab, const int32_t* ctab, const BlockItem* items, int n_items, size_t lds,
                         RepState* rs, CallStats* cs, int RG, int T, uint64_t seed, int rule, int until_conv,
                         hipStream_t st);
-// The block schedule under GREEDY with 32 restarts per LDS word (NG groups of
-// 32 per workgroup); a finished group computes its restarts' energies.
-size_t block_bits_lds_bytes(int n, int nbr_words, int tri_words, int nslices, int C, int NG);
+// The block schedule under GREEDY or GREEDY_TIE (rule 0, 1) with 32 restarts
+// per LDS word (NG groups of 32 per workgroup); a finished group computes its
+// restarts' energies.
+size_t block_bits_lds_bytes(int n, int nbr_words, int tri_words, int nslices, int C, int NG, bool tie);
 hipError_t launch_block_bits(const InstTab* tab, const int32_t* ctab, const BlockItem* items, int n_items, size_t lds,
-                             RepState* rs, CallStats* cs, int NG, int T, int until_conv, hipStream_t st);
-int block_bits_max_blocks(size_t lds, int NG);
+                             RepState* rs, CallStats* cs, int NG, int T, uint64_t seed, int rule, int until_conv,
+                             hipStream_t st);
+int block_bits_max_blocks(size_t lds, int NG, bool tie);
 // Workgroups of the block kernel with this much LDS that fit the GPU at once.
 int block_max_blocks(size_t lds);
 int queue_max_blocks(size_t lds);
