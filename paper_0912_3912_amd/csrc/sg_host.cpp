@@ -85,6 +85,7 @@ constexpr int64_t kMaxWideField = INT32_MAX;    // per-spin |h| + sum|J| + sum|K
 constexpr int32_t kMaxLatticeTiles = 1024;
 constexpr int32_t kConvChunk = 16384;  // sweeps per bit-plane launch under the stopping rule (counter slots)
 constexpr size_t kLatLdsBudget = 160 * 1024 - 4 * 1024;  // dynamic LDS of the tile kernels
+constexpr int32_t kQueueMaxN = 150000;     // largest item of the queue schedule (spins in LDS)
 constexpr int32_t kFmMaxN = 4096;          // largest instance of the pass-based search (LDS per wavefront)
 constexpr int32_t kFmlMaxN = 1024;         // one replica per lane: instances up to this size ...
 constexpr int64_t kFmlMaxW = 127;          // ... whose per-spin sum of |coefficients| fits a byte gain
@@ -217,6 +218,10 @@ struct sg_ctx {
     // once, the largest instance that uses one, where they stand
     int32_t dense_tables = 0, dense_table_n = 0;
     uint64_t off_dense_table = 0;
+    // one replica's spins in external order on their way out (instances beyond
+    // the pinned buffer): the largest that fits, 0 for none
+    int32_t xspins_n = 0;
+    uint64_t off_xspins = 0;
     hipStream_t cap_stream = nullptr;  // private stream used only to record graphs
     uint64_t off_tbase = 0;            // one sweep base per instance (graph replays)
     uint64_t off_tab = 0, off_ctab = 0, off_bitems = 0, off_qitems = 0, off_qcnt = 0;
@@ -1694,6 +1699,12 @@ void layout(sg_ctx* H)
     }
     dense_tables(H, off);
     if (H->dense_tables) H->off_dense_table = take((uint64_t)H->dense_tables * 8 << H->dense_table_n);
+    H->xspins_n = 0;
+    for (const HostInst& q : H->insts)
+        if ((size_t)q.n > kPinBytes) H->xspins_n = std::max(H->xspins_n, q.n);
+    // (it takes no handle beyond sg_bind_noalloc's workspace)
+    if (off <= SG_NOALLOC_MAX_BYTES && off + align_up((uint64_t)H->xspins_n) > SG_NOALLOC_MAX_BYTES) H->xspins_n = 0;
+    if (H->xspins_n) H->off_xspins = take((uint64_t)H->xspins_n);
     H->bytes = off;
 }
 
@@ -2140,7 +2151,6 @@ sg_status run_lattice_schedule(sg_handle H, const sg_run_params* p, const std::v
 // batched schedules
 
 constexpr size_t kLdsBudget = 160 * 1024 - 6 * 1024;  // dynamic LDS left beside the kernels' static arrays
-constexpr int32_t kQueueMaxN = 150000;                  // largest item of the queue schedule (spins in LDS)
 constexpr int32_t kBlockGroupsAuto = 4;                 // most restart groups per block workgroup (auto)
 
 // Restarts per block workgroup for instance q (0 if the block schedule cannot
@@ -3450,6 +3460,15 @@ sg_status sg_energy(sg_handle H, int64_t* E, int32_t recompute)
         SG_HIP(hipStreamSynchronize(st), "stream sync");
         return SG_OK;
     }
+    if ((uint64_t)H->total_reps * sizeof(sg::RepState) > kPinBytes) {
+        // packed on the device, a quarter of the states' bytes, straight into
+        // the caller's array (262144 replicas: the states took 1 ms)
+        SG_HIP(sg::launch_energies(H->reps(), H->at<int64_t>(H->off_eout), H->total_reps, st), "energy readout kernel");
+        SG_HIP(hipMemcpyAsync(E, H->at<int64_t>(H->off_eout), (size_t)H->total_reps * 8, hipMemcpyDeviceToHost, st),
+               "energy copy");
+        SG_HIP(hipStreamSynchronize(st), "stream sync");
+        return SG_OK;
+    }
     std::vector<sg::RepState> rs((size_t)H->total_reps);
     CopiesOut out(H);
     SG_HIP(out.copy(rs.data(), H->reps(), rs.size() * sizeof(sg::RepState), st), "state copy");
@@ -3482,6 +3501,23 @@ sg_status sg_spins_out(sg_handle H, int32_t inst, int32_t r, int8_t* s)
     if ((e = check_inst(H, inst, r)) != SG_OK) return e;
     if (!s) return fail(SG_EINVAL, "sg_spins_out: null output");
     const HostInst& q = H->insts[inst];
+    const int8_t* sp = H->at<int8_t>(q.off_spins) + (uint64_t)r * q.spin_stride;
+    if (H->pin && (size_t)q.n <= kPinBytes) {
+        SG_HIP(hipMemcpyAsync(H->pin, sp, (size_t)q.n, hipMemcpyDeviceToHost, H->stream), "spin copy");
+        SG_HIP(hipStreamSynchronize(H->stream), "stream sync");
+        const int8_t* src = reinterpret_cast<const int8_t*>(H->pin);
+        for (int32_t i = 0; i < q.n; ++i) s[q.ext_of[i]] = src[i];
+        return SG_OK;
+    }
+    if (H->xspins_n >= q.n && (size_t)q.n > kPinBytes) {
+        // reordered on the device (500000 spins of a random graph: the byte
+        // scatter took the host about 0.15 ms)
+        int8_t* x = H->at<int8_t>(H->off_xspins);
+        SG_HIP(sg::launch_spins_ext(H->at<uint32_t>(q.off_ext), sp, x, q.n, H->stream), "spin readout kernel");
+        SG_HIP(hipMemcpyAsync(s, x, (size_t)q.n, hipMemcpyDeviceToHost, H->stream), "spin copy");
+        SG_HIP(hipStreamSynchronize(H->stream), "stream sync");
+        return SG_OK;
+    }
     std::vector<int8_t> tmp((size_t)q.n);
     SG_HIP(hipMemcpyAsync(tmp.data(), H->at<int8_t>(q.off_spins) + (uint64_t)r * q.spin_stride, (size_t)q.n,
                           hipMemcpyDeviceToHost, H->stream),
@@ -3519,7 +3555,9 @@ sg_status sg_best(sg_handle H, int64_t* E_best, int32_t* r_best)
     if ((e = ensure_energy(H)) != SG_OK) return e;
     const int ni = (int)H->insts.size();
     hipStream_t st = H->stream;
-    SG_HIP(sg::launch_best(H->reps(), H->at<int64_t>(H->off_rep_base), H->at<int32_t>(H->off_restarts), ni,
+    int32_t rmax = 0;
+    for (const HostInst& q : H->insts) rmax = std::max(rmax, q.R);
+    SG_HIP(sg::launch_best(H->reps(), H->at<int64_t>(H->off_rep_base), H->at<int32_t>(H->off_restarts), ni, rmax,
                            H->at<int64_t>(H->off_best_E), H->at<int32_t>(H->off_best_r), st),
            "best kernel");
     std::vector<int64_t> eb((size_t)ni);

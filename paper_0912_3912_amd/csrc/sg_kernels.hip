@@ -393,6 +393,59 @@ __global__ void k_best(const RepState* __restrict__ rs, const int64_t* __restric
     }
 }
 
+// The same with a workgroup per instance, for long restart lists (15000
+// restarts: 63 us on one wavefront, whose lanes each read 235 states in turn).
+__global__ __launch_bounds__(1024) void k_best_wide(const RepState* __restrict__ rs,
+                                                    const int64_t* __restrict__ rep_base,
+                                                    const int32_t* __restrict__ restarts, int64_t* __restrict__ Eb,
+                                                    int32_t* __restrict__ rb)
+{
+    __shared__ long long we[16];
+    __shared__ int wb[16];
+    const int q = blockIdx.x, tid = threadIdx.x;
+    const RepState* p = rs + rep_base[q];
+    const int R = restarts[q];
+    long long e = 0x7FFFFFFFFFFFFFFFll;
+    int best = 0x7FFFFFFF;
+    auto take = [&](long long e2, int b2) {
+        if (e2 < e || (e2 == e && b2 < best)) {
+            e = e2;
+            best = b2;
+        }
+    };
+    for (int r = tid; r < R; r += 1024) take(p[r].E, r);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) take(__shfl_xor(e, o, 64), __shfl_xor(best, o, 64));
+    if ((tid & 63) == 0) {
+        we[tid >> 6] = e;
+        wb[tid >> 6] = best;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < 16; ++w) take(we[w], wb[w]);
+        Eb[q] = e;
+        rb[q] = best;
+    }
+}
+
+// A replica's spins in external order, four internal spins a thread (the
+// spin rows are padded to 256 bytes).
+__global__ void k_spins_ext(const uint32_t* __restrict__ ext, const int8_t* __restrict__ sp, int8_t* __restrict__ out,
+                            int n)
+{
+    const int i = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
+    if (i >= n) return;
+    const uint32_t w = *reinterpret_cast<const uint32_t*>(sp + i);
+    for (int u = 0; u < 4 && i + u < n; ++u) out[ext[i + u]] = (int8_t)(w >> (8 * u) & 0xFFu);
+}
+
+// The replicas' energies, packed.
+__global__ void k_energies(const RepState* __restrict__ rs, int64_t* __restrict__ out, int64_t count)
+{
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g < count) out[g] = rs[g].E;
+}
+
 // ---------------------------------------------------------------------------
 // launchers
 
@@ -504,11 +557,27 @@ hipError_t launch_philox_word0(const uint32_t* ctr, uint32_t* out, int64_t count
     return hipGetLastError();
 }
 
-hipError_t launch_best(const RepState* rs, const int64_t* rep_base, const int32_t* restarts, int ninst,
+hipError_t launch_best(const RepState* rs, const int64_t* rep_base, const int32_t* restarts, int ninst, int rmax,
                        int64_t* Eb, int32_t* rb, hipStream_t st)
 {
+    if (rmax > 1024) {
+        hipLaunchKernelGGL(k_best_wide, dim3((unsigned)ninst), dim3(1024), 0, st, rs, rep_base, restarts, Eb, rb);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_best, dim3(grid1((uint64_t)ninst * 64, 256, 1u << 30)), dim3(256), 0, st, rs, rep_base,
                        restarts, ninst, Eb, rb);
+    return hipGetLastError();
+}
+
+hipError_t launch_spins_ext(const uint32_t* ext, const int8_t* sp, int8_t* out, int n, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_spins_ext, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st, ext, sp, out, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_energies(const RepState* rs, int64_t* out, int64_t count, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_energies, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, rs, out, count);
     return hipGetLastError();
 }
 

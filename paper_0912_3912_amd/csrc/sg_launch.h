@@ -31,8 +31,12 @@ hipError_t launch_end(RepState* rs, int R, const int64_t* acc, int nslots, int T
 hipError_t launch_any_active(const RepState* rs, int R, int T, uint32_t* flag, hipStream_t st);
 // Word 0 of Philox4x32-10 of count counters (4 uint32 each) under key seed.
 hipError_t launch_philox_word0(const uint32_t* ctr, uint32_t* out, int64_t count, uint64_t seed, hipStream_t st);
-hipError_t launch_best(const RepState* rs, const int64_t* rep_base, const int32_t* restarts, int ninst,
-                       int64_t* Eb, int32_t* rb, hipStream_t st);
+hipError_t launch_best(const RepState* rs, const int64_t* rep_base, const int32_t* restarts, int ninst, int rmax,
+                       int64_t* Eb, int32_t* rb, hipStream_t st);  // rmax: the most restarts of one instance
+// One replica's spins (internal order, row padded to 256 bytes) into external
+// order; the replicas' energies, packed.
+hipError_t launch_spins_ext(const uint32_t* ext, const int8_t* sp, int8_t* out, int n, hipStream_t st);
+hipError_t launch_energies(const RepState* rs, int64_t* out, int64_t count, hipStream_t st);
 
 // wide-form instances (sg_wide.hip): one colour phase, and the energy of
 // every replica (into rs[r].E, or out[r] when out is not null)
