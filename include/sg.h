@@ -448,6 +448,12 @@ sg_status sg_solve(sg_handle h, const sg_run_params* p, sg_run_stats* stats, int
  *                        that fit co-resident)
  *   "queue_min_items"    SG_SCHED_AUTO uses the queue schedule when the
  *                        handle has at least this many queue items (32)
+ *   "team_wgs"           workgroups per replica where SG_SCHED_AUTO runs the
+ *                        phases of an instance it gives to SG_SCHED_PHASE in
+ *                        one launch (at most 64 restarts, 1.2 million spins,
+ *                        64 colours, packed form): 0 chosen by size, 1..256,
+ *                        -1 per-phase launches as under SG_SCHED_PHASE itself
+ *                        (default 0; stats report SG_SCHED_PHASE either way)
  *   "graph_sweeps"       sweeps per captured HIP graph of SG_SCHED_GRAPH
  *                        (1..1024, default 32)
  *   "auto_graph"         1: SG_SCHED_AUTO records the per-phase launches of the
@@ -484,7 +490,8 @@ sg_status sg_tune(sg_handle h, const char* key, int64_t value);
  * replicas run one per lane), "last_fm_lane_nr" (its restarts per lane-kernel
  * wavefront), "last_fm_big" (its replicas on the kernel for instances beyond
  * 4096 spins), "energy_pending" (1 while start energies
- * left out by sg_init_spins are not yet computed), "last_queue_grid",
+ * left out by sg_init_spins are not yet computed), "last_queue_grid", "last_team" (workgroups per replica of the last such
+ * launch of the last call, 0 for none),
  * "total_replicas", "queue_ok" (1 when every instance can join sg_run_group),
  * "wide_instances" (instances stored in the wide form: a
  * coefficient beyond int8, a spin with |h|+sum|J|+sum|K| >= 2^23 or more than

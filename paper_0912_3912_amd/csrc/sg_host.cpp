@@ -137,6 +137,7 @@ struct HostInst {
     // workspace offsets (bytes)
     uint64_t off_nbr = 0, off_ta = 0, off_tb = 0, off_h = 0, off_ext = 0, off_slices = 0, off_eterm = 0;
     uint64_t off_spins = 0, spin_stride = 0, off_acc = 0;
+    uint64_t off_team = UINT64_MAX;             // exchange words of the team kernel, or none
     uint64_t off_fields = 0, field_stride = 0;  // maintained local fields (ints per replica), when enabled
     // wide form (values or sizes beyond the packed words, sg_layout.h)
     int32_t wide = 0;
@@ -203,6 +204,8 @@ struct sg_ctx {
     int32_t queue_grid = 0;            // persistent queue grid (0 = co-resident capacity)
     int32_t queue_min_items = 32;      // AUTO uses the queue schedule from this many items
     int32_t graph_sweeps = 32;         // sweeps per captured graph (SG_SCHED_GRAPH)
+    int32_t team_wgs = 0;              // workgroups per replica of the team kernel (0 = chosen, -1 = not used)
+    int32_t last_team = 0;             // what the last call's last team launch used (0: none)
     int32_t auto_graph = 0;            // SG_SCHED_AUTO records per-phase launches in graphs (SG_SCHED_GRAPH)
     int32_t conv_chunk = kConvChunk;   // sweeps per bit-plane launch under the stopping rule
     int32_t lattice_msc = 1;           // use the bit-plane tile kernel where it applies
@@ -1492,6 +1495,26 @@ void build_fml(const HostInst& q, std::vector<uint32_t>& out, int32_t dc, int32_
         }
 }
 
+// Slices of the largest colour.
+int team_slices(const HostInst& q)
+{
+    int m = 0;
+    for (int32_t c = 0; c < q.C; ++c) m = std::max(m, q.colour_slice[(size_t)c + 1] - q.colour_slice[(size_t)c]);
+    return m;
+}
+
+// Team kernel (sg_team.hip): instances whose spins fit LDS as bits, and with
+// exchange words those large enough to split, unless a batch (which the queue
+// schedule takes).
+constexpr int32_t kTeamMaxR = 64;
+constexpr int32_t kTeamSplit = 64;  // slices of a colour from which a replica is split over workgroups
+bool can_team(const HostInst& q) { return !q.wide && !q.dense && sg::team_fits(q.n, q.C); }
+bool team_words(const sg_ctx* H, const HostInst& q)
+{
+    return can_team(q) && q.R <= kTeamMaxR && team_slices(q) > kTeamSplit &&
+           (q.n > kQueueMaxN || q.lat_ok || H->total_reps < 64);
+}
+
 // Energy tables (sg_dense.hip) for the pass-based search of a dense handle:
 // instances of at most kDenseTableMaxN spins share room for up to 32 MiB of
 // tables and run in rounds of as many instances as that holds.  A step takes
@@ -1697,6 +1720,19 @@ void layout(sg_ctx* H)
         H->off_fmb_items = take((uint64_t)H->fmb_reps * sizeof(sg::QueueItem));
         H->off_fmb_cnt = take(64);
     }
+    // exchange words of the team kernel for the instances SG_SCHED_AUTO may
+    // give it with more than one workgroup per replica (they take no handle
+    // beyond sg_bind_noalloc's workspace)
+    {
+        uint64_t need = 0;
+        for (HostInst& q : H->insts) {
+            q.off_team = UINT64_MAX;
+            if (team_words(H, q)) need += align_up((uint64_t)q.R * q.slices.size() * 32);
+        }
+        if (off > SG_NOALLOC_MAX_BYTES || off + need <= SG_NOALLOC_MAX_BYTES)
+            for (HostInst& q : H->insts)
+                if (team_words(H, q)) q.off_team = take((uint64_t)q.R * q.slices.size() * 32);
+    }
     dense_tables(H, off);
     if (H->dense_tables) H->off_dense_table = take((uint64_t)H->dense_tables * 8 << H->dense_table_n);
     H->xspins_n = 0;
@@ -1790,6 +1826,62 @@ sg_status run_phase_schedule(sg_handle H, const sg_run_params* p, const std::vec
         if (qi == which.back()) SG_HIP(hipEventRecord(H->evh1, st), "event record");
         SG_HIP(sg::launch_end(rs, q.R, acc, q.acc_slots, T, p->until_converged, q.n, cs, st), "end kernel");
     }
+    return SG_OK;
+}
+
+// Workgroups per replica of the team kernel for a run of instance q that
+// SG_SCHED_AUTO would otherwise give to per-phase launches; 0: not used.  A
+// workgroup's sixteen wavefronts take a phase's slices in turn, a microsecond
+// or so each, an exchange costs about three, and one workgroup needs no
+// cooperative launch.  Whole calls on 3-regular graphs, one replica, in
+// microseconds (per-phase launches / one workgroup / best team): 1000 spins
+// 157 / 67 / -, 10000 spins 156 / 104 / -, 20000 spins 165 / 153 / 115 (16),
+// 100000 spins 174 / 506 / 136 (64), 500000 spins 330 / - / 206; teams of a
+// twelfth of the largest colour's slices are within 10% of the best.
+int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
+{
+    if (H->team_wgs < 0 || p->schedule != SG_SCHED_AUTO || p->max_sweeps <= 0 || q.R > kTeamMaxR || !can_team(q)) return 0;
+    const int ns = team_slices(q);
+    int g = H->team_wgs > 0 ? std::min(H->team_wgs, ns) : ns > kTeamSplit ? (ns + 11) / 12 : 1;
+    if (g > 1) {
+        const int most = sg::team_max_blocks(q.n, p->rule == SG_RULE_GREEDY_TIE, q.t > 0);
+        g = q.off_team == UINT64_MAX ? 1 : std::min(g, most / q.R);
+    }
+    if (g >= 2 || ns <= 2 * kTeamSplit || H->team_wgs > 0) return std::max(g, 1);
+    return 0;  // large and not split: the per-phase launches use the whole device
+}
+
+sg_status run_team(sg_handle H, const sg_run_params* p, const std::vector<int>& which)
+{
+    hipStream_t st = H->stream;
+    sg::CallStats* cs = H->at<sg::CallStats>(H->off_stats);
+    uint32_t* err = H->at<uint32_t>(H->off_err);
+    if (!H->lat_err_check) SG_HIP(sg::launch_fill_u32(err, 1, 0u, st), "fill kernel");
+    H->lat_err_check = true;
+    SG_HIP(hipEventRecord(H->evh0, st), "event record");
+    H->hot_launches = 0;
+    for (int qi : which) {
+        const HostInst& q = H->insts[(size_t)qi];
+        sg::RepState* rs = H->reps() + q.rep_base;
+        int64_t* acc = H->at<int64_t>(q.off_acc);
+        const int G = team_groups(H, q, p);
+        int64_t ct = 0;  // its colour offsets in the handle's table
+        for (int k = 0; k < qi; ++k) ct += H->insts[(size_t)k].C + 1;
+        uint64_t* words = nullptr;
+        if (G > 1) {
+            words = H->at<uint64_t>(q.off_team);
+            SG_HIP(sg::launch_fill_u32(words, (uint64_t)q.R * q.slices.size() * 8, 0u, st), "fill kernel");
+        }
+        SG_HIP(sg::launch_begin(rs, q.R, acc, (int64_t)q.R * q.acc_slots * 2, st), "begin kernel");
+        SG_HIP(sg::launch_team(H->view(q), H->at<int32_t>(H->off_ctab) + ct, q.C, H->at<int8_t>(q.off_spins),
+                               (int64_t)q.spin_stride, rs, q.R, G, acc, q.acc_slots, words, err, p->max_sweeps,
+                               p->seed, p->rule, p->until_converged, st),
+               "team kernel");
+        ++H->hot_launches;
+        H->last_team = G;
+        SG_HIP(sg::launch_end(rs, q.R, acc, q.acc_slots, p->max_sweeps, p->until_converged, q.n, cs, st), "end kernel");
+    }
+    SG_HIP(hipEventRecord(H->evh1, st), "event record");
     return SG_OK;
 }
 
@@ -3358,6 +3450,7 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
     SG_HIP(hipEventRecord(H->ev0, st), "event record");
     H->hot_launches = 0;
     H->lat_err_check = false;
+    H->last_team = 0;
     H->e_written.assign(H->insts.size(), 0);
     for (int kind : {SG_SCHED_LATTICE, SG_SCHED_BLOCK, SG_SCHED_QUEUE, SG_SCHED_GRAPH, SG_SCHED_FIELDS, SG_SCHED_PHASE}) {
         std::vector<int> which;
@@ -3370,7 +3463,14 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
         case SG_SCHED_QUEUE: e = run_queue_schedule(H, p, which); break;
         case SG_SCHED_GRAPH: e = run_graph_schedule(H, p, which); break;
         case SG_SCHED_FIELDS: e = run_phase_schedule(H, p, which, true); break;
-        default: e = run_phase_schedule(H, p, which); break;
+        default: {
+            // SG_SCHED_AUTO: all phases in one launch where the team kernel takes the instance
+            std::vector<int> team, rest;
+            for (int qi : which) (team_groups(H, H->insts[(size_t)qi], p) > 0 ? team : rest).push_back(qi);
+            e = rest.empty() ? SG_OK : run_phase_schedule(H, p, rest);
+            if (e == SG_OK && !team.empty()) e = run_team(H, p, team);
+            break;
+        }
         }
         if (e != SG_OK) return e;
     }
@@ -3383,7 +3483,7 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
     SG_HIP(hipStreamSynchronize(st), "stream sync");
     out.finish();
     if (herr)
-        return fail(SG_EDEVICE, "lattice tile kernel: a neighbour wait timed out (replica state is undefined; "
+        return fail(SG_EDEVICE, "lattice tile or team kernel: a neighbour wait timed out (replica state is undefined; "
                                 "start again with sg_init_spins)");
     if (H->e_pending) {
         // the queue kernel wrote the energies of the replicas that converged,
@@ -3746,6 +3846,9 @@ sg_status sg_tune(sg_handle H, const char* key, int64_t value)
     } else if (k == "auto_graph") {
         if (value != 0 && value != 1) return fail(SG_EINVAL, "auto_graph must be 0 or 1");
         H->auto_graph = (int32_t)value;
+    } else if (k == "team_wgs") {
+        if (value < -1 || value > 256) return fail(SG_EINVAL, "team_wgs must be -1..256");
+        H->team_wgs = (int32_t)value;
     } else if (k == "queue_min_items") {
         if (value < 1) return fail(SG_EINVAL, "queue_min_items must be >= 1");
         H->queue_min_items = (int32_t)std::min<int64_t>(value, INT32_MAX);
@@ -3782,6 +3885,8 @@ sg_status sg_query(sg_handle H, const char* key, int64_t* value)
     else if (k == "block_min_restarts") *value = H->block_min_restarts;
     else if (k == "queue_wave_max_n") *value = H->queue_wave_max_n;
     else if (k == "queue_grid") *value = H->queue_grid;
+    else if (k == "team_wgs") *value = H->team_wgs;
+    else if (k == "last_team") *value = H->last_team;
     else if (k == "queue_min_items") *value = H->queue_min_items;
     else if (k == "graph_sweeps") *value = H->graph_sweeps;
     else if (k == "auto_graph") *value = H->auto_graph;

@@ -191,4 +191,16 @@ hipError_t launch_queue(const InstTab* tab, const int32_t* ctab, const QueueItem
                         uint32_t* counters, int wave_lds, size_t lds, int grid, RepState* rs, CallStats* cs, int T,
                         uint64_t seed, int rule, int until_conv, hipStream_t st);
 
+// Sweeps of one packed instance in one launch (sg_team.hip): R teams of G
+// workgroups.  ct: its C + 1 colour slice offsets in device memory; words: per
+// replica 4 exchange words per slice, zero at launch (null for G = 1); rs, acc
+// as the per-phase kernels use them (k_begin before, k_end after).  With G > 1
+// the launch is cooperative: R G at most team_max_blocks, and no member
+// without a slice (G at most the slices of the largest colour).
+bool team_fits(int n, int C);
+int team_max_blocks(int n, bool tie, bool tri);
+hipError_t launch_team(const InstDev& I, const int32_t* ct, int C, int8_t* spins, int64_t stride, RepState* rs, int R,
+                       int G, int64_t* acc, int nslots, uint64_t* words, uint32_t* err, int T, uint64_t seed, int rule,
+                       int until_conv, hipStream_t st);
+
 }  // namespace sg

@@ -203,8 +203,8 @@ class Server:
         self.scratch = None
         self.shared_launches = 0
         self.shared_batch_sizes: List[int] = []
-        # Large lattices under a fixed sweep count use the co-resident tile
-        # launch; two such grids must not be resident at once (each could
+        # Large lattices and large irregular graphs use co-resident launches;
+        # two such grids must not be resident at once (each could
         # hold CUs the other needs), so they take turns.
         self.coop_lock = threading.Lock()
         self.loop_error: Optional[BaseException] = None
@@ -453,8 +453,10 @@ class Server:
             h.init_spins(req.seed)
             info = h.info(0)
             # a lattice beyond one workgroup runs on the co-resident tile launch
-            # (fixed budgets, and GREEDY until converged on the bit-plane kernel)
-            coop = info["lattice"] and info["n"] > h.query("lattice_wg_max_n")
+            # (fixed budgets, and GREEDY until converged on the bit-plane
+            # kernel), a larger irregular graph on a co-resident launch of
+            # several workgroups per replica
+            coop = info["n"] > (h.query("lattice_wg_max_n") if info["lattice"] else 4096)
             if coop:
                 with self.coop_lock:
                     stats = h.run_sweeps(seed=req.seed, rule=req.rule, max_sweeps=req.max_sweeps,

@@ -1,0 +1,81 @@
+"""GPU parity of the sweeps of one instance in one launch, a team of
+workgroups per replica (SG_SCHED_AUTO on few replicas of an irregular graph):
+one workgroup, forced and chosen team sizes, one colour and many, colours
+smaller than the team, hyper-couplings, rows longer than what is loaded at
+once, both rules, resumed runs with frozen replicas.  Results are integers and
+equal the oracle's bit for bit."""
+import numpy as np
+import pytest
+
+import instances as gen
+import oracle
+from parity import compare, log
+
+pytestmark = pytest.mark.gpu
+
+GREEDY, TIE = 0, 1
+
+
+def _lone():
+    rng = np.random.default_rng(3)
+    e = np.zeros(0, np.int32)
+    return gen.Instance(700, e, e, e, rng.integers(-3, 4, 700), restarts=3, instance_id=4, name="fields700")
+
+
+CASES = {
+    "one": lambda: gen.chain(1, seed=1).replace(h=np.array([2], np.int32)),
+    "fields": _lone,
+    "regular": lambda: gen.random_regular3(6002, seed=2, instance_id=3, restarts=2),
+    "triples": lambda: gen.erdos_renyi_triples(5000, seed=4, restarts=3),
+    "dense": lambda: gen.random_small(400, seed=5, p_edge=0.08, n_triples=900, j_range=(-100, 100), h_range=(-9, 9),
+                                      k_range=(-50, 50)).replace(restarts=2),
+}
+
+
+@pytest.mark.parametrize("rule,uc,runs", [(GREEDY, True, [1000]), (TIE, False, [7]), (TIE, True, [2, 3, 9]),
+                                          (GREEDY, False, [1, 3])])
+@pytest.mark.parametrize("name", list(CASES))
+def test_team(gpu, name, rule, uc, runs):
+    import paper_0912_3912_amd as sg
+    inst = CASES[name]()
+    st = None
+    for r in runs:
+        st, _ = oracle.run(inst, seed=3, rule=rule, max_sweeps=r, until_converged=uc, state=st, threads=8)
+    for wgs in (1, 2, 7):
+        log(f"team case: {name} n={inst.n} restarts={inst.restarts} rule={rule} uc={uc} runs={runs} wgs={wgs}")
+        h = sg.load_instance([inst])
+        h.tune("team_wgs", wgs)
+        h.bind()
+        h.init_spins(3)
+        for r in runs:
+            s = h.run_sweeps(seed=3, rule=rule, max_sweeps=r, until_converged=uc)
+        assert s["schedule_used"] == sg.SCHED_PHASE and 1 <= h.query("last_team") <= wgs
+        compare(h, [inst], [st])
+        h.free()
+
+
+@pytest.mark.parametrize("rule,uc", [(GREEDY, True), (TIE, False)])
+def test_chosen_teams(gpu, rule, uc):
+    """Sizes where SG_SCHED_AUTO splits a replica by itself, a small instance
+    beside it, and the per-phase launches asked for."""
+    import paper_0912_3912_amd as sg
+    insts = [gen.random_regular3(70000, seed=6, instance_id=1, restarts=2),
+             gen.erdos_renyi_triples(900, seed=7, instance_id=2, restarts=2)]
+    log(f"chosen teams: rule={rule} uc={uc}")
+    ref = [oracle.run(i, seed=5, rule=rule, max_sweeps=12, until_converged=uc, threads=8)[0] for i in insts]
+    for wgs, want in ((0, (1,)), (-1, (0,))):
+        h = sg.load_instance(insts)
+        h.tune("team_wgs", wgs)
+        h.bind()
+        h.init_spins(5)
+        h.run_sweeps(seed=5, rule=rule, max_sweeps=12, until_converged=uc)
+        assert h.query("last_team") in want
+        compare(h, insts, ref)
+        h.free()
+    h = sg.load_instance(insts[:1]).bind()
+    h.init_spins(5)
+    h.run_sweeps(seed=5, rule=rule, max_sweeps=12, until_converged=uc)
+    assert h.query("last_team") >= 2
+    compare(h, insts[:1], ref[:1])
+    assert np.array_equal(h.spins_out(0, 1), ref[0].spins[1])  # beyond the pinned buffer
+    h.free()
