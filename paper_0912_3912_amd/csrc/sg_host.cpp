@@ -118,6 +118,7 @@ struct HostInst {
     int32_t fmb_dc = 0, fmb_tt = 0;      // their coupling and hyper-coupling widths
     int32_t lat_msc = 0;               // every lattice bond is +-1 and |h| <= 2 (bit-plane kernel)
     int64_t max_w = 0;                 // largest sum of |coefficients| over one spin's terms
+    int32_t max_ew = 0;                // couplings of the widest slice (packed form)
     uint64_t fml_off = UINT64_MAX;     // word offset of its per-spin term rows (lane pass kernel), or none
     int32_t fml_dc = 0, fml_tt = 0;    // coupling words / hyper-couplings per row
     int32_t bits_ok = 0;               // at most 2048 spins, every |coefficient| <= 15 and per spin
@@ -1076,6 +1077,7 @@ sg_status ingest(const sg_instance_desc& d, int idx, HostInst& q)
             S.tw = (uint8_t)tw;
             S.rows = (uint8_t)rows;
             q.slices.push_back(S);
+            q.max_ew = std::max(q.max_ew, w);
             ebase += (uint64_t)w * sg::kSlice;
             tbase += (uint64_t)tw * sg::kSlice;
             if (ebase > 0xFFFFFFFFull || tbase > 0xFFFFFFFFull)
@@ -1832,19 +1834,20 @@ sg_status run_phase_schedule(sg_handle H, const sg_run_params* p, const std::vec
 // Workgroups per replica of the team kernel for a run of instance q that
 // SG_SCHED_AUTO would otherwise give to per-phase launches; 0: not used.  A
 // workgroup's sixteen wavefronts take a phase's slices in turn, a microsecond
-// or so each, an exchange costs about three, and one workgroup needs no
+// or so each, an exchange costs about two, and one workgroup needs no
 // cooperative launch.  Whole calls on 3-regular graphs, one replica, in
 // microseconds (per-phase launches / one workgroup / best team): 1000 spins
-// 157 / 67 / -, 10000 spins 156 / 104 / -, 20000 spins 165 / 153 / 115 (16),
-// 100000 spins 174 / 506 / 136 (64), 500000 spins 330 / - / 206; teams of a
-// twelfth of the largest colour's slices are within 10% of the best.
+// 157 / 62 / -, 10000 spins 156 / 87 / -, 100000 spins 174 / 384 / 119 (128),
+// 500000 spins 330 / 1950 / 159 (245); teams of a twelfth of the largest
+// colour's slices are within 10% of the best (20000 spins: 12.1 us a sweep
+// with 10 workgroups, 11.7 with 16; 100000: 14.5 with 49, 13.7 with 128).
 int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
 {
     if (H->team_wgs < 0 || p->schedule != SG_SCHED_AUTO || p->max_sweeps <= 0 || q.R > kTeamMaxR || !can_team(q)) return 0;
     const int ns = team_slices(q);
     int g = H->team_wgs > 0 ? std::min(H->team_wgs, ns) : ns > kTeamSplit ? (ns + 11) / 12 : 1;
     if (g > 1) {
-        const int most = sg::team_max_blocks(q.n, p->rule == SG_RULE_GREEDY_TIE, q.t > 0);
+        const int most = sg::team_max_blocks(q.n, p->rule == SG_RULE_GREEDY_TIE, q.t > 0, q.max_ew);
         g = q.off_team == UINT64_MAX ? 1 : std::min(g, most / q.R);
     }
     if (g >= 2 || ns <= 2 * kTeamSplit || H->team_wgs > 0) return std::max(g, 1);
@@ -1873,7 +1876,7 @@ sg_status run_team(sg_handle H, const sg_run_params* p, const std::vector<int>& 
             SG_HIP(sg::launch_fill_u32(words, (uint64_t)q.R * q.slices.size() * 8, 0u, st), "fill kernel");
         }
         SG_HIP(sg::launch_begin(rs, q.R, acc, (int64_t)q.R * q.acc_slots * 2, st), "begin kernel");
-        SG_HIP(sg::launch_team(H->view(q), H->at<int32_t>(H->off_ctab) + ct, q.C, H->at<int8_t>(q.off_spins),
+        SG_HIP(sg::launch_team(H->view(q), q.max_ew, H->at<int32_t>(H->off_ctab) + ct, q.C, H->at<int8_t>(q.off_spins),
                                (int64_t)q.spin_stride, rs, q.R, G, acc, q.acc_slots, words, err, p->max_sweeps,
                                p->seed, p->rule, p->until_converged, st),
                "team kernel");

@@ -198,8 +198,8 @@ hipError_t launch_queue(const InstTab* tab, const int32_t* ctab, const QueueItem
 // the launch is cooperative: R G at most team_max_blocks, and no member
 // without a slice (G at most the slices of the largest colour).
 bool team_fits(int n, int C);
-int team_max_blocks(int n, bool tie, bool tri);
-hipError_t launch_team(const InstDev& I, const int32_t* ct, int C, int8_t* spins, int64_t stride, RepState* rs, int R,
+int team_max_blocks(int n, bool tie, bool tri, int ew);
+hipError_t launch_team(const InstDev& I, int ew, const int32_t* ct, int C, int8_t* spins, int64_t stride, RepState* rs, int R,
                        int G, int64_t* acc, int nslots, uint64_t* words, uint32_t* err, int T, uint64_t seed, int rule,
                        int until_conv, hipStream_t st);
 
