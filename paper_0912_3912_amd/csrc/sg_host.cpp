@@ -2443,7 +2443,7 @@ sg_status run_queue_schedule(sg_handle H, const sg_run_params* p, const std::vec
         }
     }
     const int wave_lds = (nmax_small + 15) / 16 * 16;
-    size_t lds = std::max<size_t>((size_t)nmax_big, (size_t)wave_lds * 16);
+    size_t lds = std::max<size_t>(sg::queue_big_lds(nmax_big), (size_t)wave_lds * 16);
     lds = std::max<size_t>((lds + 15) / 16 * 16, 16);
     if (lds > kLdsBudget) return fail(SG_EINVAL, "queue schedule: an item needs %zu bytes of LDS", lds);
     int grid = H->queue_grid;
@@ -3235,7 +3235,7 @@ sg_status bind_impl(sg_handle H, void* dev_ptr, uint64_t bytes, void* hip_stream
             T.n_eh = q.n_eh;
             T.n_ee = q.n_ee;
             T.n_et = q.n_et;
-            T.eterm_pad = 0;
+            T.max_ew = q.max_ew;
             T.fml = q.fml_off == UINT64_MAX ? nullptr : H->at<uint32_t>(H->off_fml) + q.fml_off;
             fm_row_widths(q, T.fml_dc, T.fml_tt);
             for (int32_t c = 0; c <= q.C; ++c) ctab.push_back(q.colour_slice[c]);
@@ -4039,6 +4039,7 @@ sg_status sg_run_group(const sg_handle* hs, int32_t count, const sg_run_params* 
             T.n_eh = q.n_eh;
             T.n_ee = q.n_ee;
             T.n_et = q.n_et;
+            T.max_ew = q.max_ew;
             for (int32_t c = 0; c <= q.C; ++c) ctab.push_back(q.colour_slice[c]);
             const int32_t gi = (int32_t)tab.size();
             tab.push_back(T);
@@ -4060,7 +4061,7 @@ sg_status sg_run_group(const sg_handle* hs, int32_t count, const sg_run_params* 
         }
     }
     const int wave_lds = (nmax_small + 15) / 16 * 16;
-    size_t lds = std::max<size_t>((size_t)nmax_big, (size_t)wave_lds * 16);
+    size_t lds = std::max<size_t>(sg::queue_big_lds(nmax_big), (size_t)wave_lds * 16);
     lds = std::max<size_t>((lds + 15) / 16 * 16, 16);
     if (lds > kLdsBudget) return fail(SG_EINVAL, "sg_run_group: an item needs %zu bytes of LDS", lds);
     int grid = H0->queue_grid;

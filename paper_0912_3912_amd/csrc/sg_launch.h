@@ -187,6 +187,7 @@ hipError_t launch_start_lanes(const InstTab* tab, const BlockItem* items, int ni
 hipError_t launch_start_units(const InstTab* tab, const StartUnit* start_units, int64_t n_start,
                               const StartUnit* energy_units, int64_t n_energy, const EnergySeg* segs, int64_t nsegs,
                               int64_t* part, RepState* rs, int64_t* out, uint64_t seed, bool init, hipStream_t st);
+inline size_t queue_big_lds(int n) { return (size_t)n; }  // LDS of an item on a whole workgroup
 hipError_t launch_queue(const InstTab* tab, const int32_t* ctab, const QueueItem* items, int n_big, int n_items,
                         uint32_t* counters, int wave_lds, size_t lds, int grid, RepState* rs, CallStats* cs, int T,
                         uint64_t seed, int rule, int until_conv, hipStream_t st);

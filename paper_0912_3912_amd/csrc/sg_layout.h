@@ -130,7 +130,8 @@ struct InstTab {
     // (i | j << 11 | J << 22), then n_et hyper-couplings as word pairs
     // (i | a << 11 | K << 22, b); coefficients as 8-bit two's complement
     const uint32_t* eterm;
-    int32_t n_eh, n_ee, n_et, eterm_pad;
+    int32_t n_eh, n_ee, n_et;
+    int32_t max_ew;          // couplings of the widest slice
     // Per-spin term rows in external order for the lane-per-replica pass
     // kernel (null when the instance does not qualify; layout in
     // sg_fm_lanes.hip): fml_dc coupling words and fml_tt hyper-couplings per

@@ -1,8 +1,11 @@
 // sg_queue.hip -- the persistent queue schedule for many instances of uneven
 // size: workgroups take (instance, restart) items from a queue sorted by
-// decreasing size.  Large items run on the whole workgroup (rows of the
-// sliced layout on lanes, couplings streamed from memory, spins in LDS);
-// small items run one per wavefront in a private LDS window, 16 at a time.
+// decreasing size.  Large items run on the whole workgroup (sg_team_core.h:
+// rows of the sliced layout on lanes, couplings streamed from memory a slice
+// ahead, spins in LDS as bytes); small items run one per wavefront in a
+// private LDS window, 16 at a time.  Bound by the largest items: 96 instances
+// of 100 to 100000 spins, 8 restarts each: 1.27 ms a call, against 2.43 ms
+// with loads under branches and an LDS wait per coupling.
 // Each replica runs to its own stopping point, and the replica state and the
 // call totals follow the per-phase kernels exactly: with until_converged a
 // replica stops after its first sweep without a flip (that sweep counts).
@@ -17,32 +20,24 @@
 #include "sg_device.h"
 #include "sg_launch.h"
 #include "sg_layout.h"
+#include "sg_team_core.h"
 
 namespace sg {
 
 __device__ __forceinline__ int bat_j(uint32_t w) { return (int)(int8_t)(w & 0xffu); }
 
-constexpr int kBatThreads = 1024;
+constexpr int kBatThreads = kTeamThreads;
 constexpr int kBatWaves = kBatThreads / 64;
 
 // ---------------------------------------------------------------------------
 // k_queue
 
-// One colour phase of one replica on `nw` wavefronts (wave index w among
-// them): lane = row of a slice, couplings from memory, spins in LDS.  All
-// coupling and hyper-coupling words of a slice (up to kPreW and kPreT of
-// them, predicated on the slice's widths) are loaded before any is used, so a
-// wavefront keeps a whole slice's loads in flight (measured on 2000 uneven
-// instances: 3.26 ms, against 4.67 ms with four loads at a time and 3.78 ms
-// when loading the next slice while evaluating the current one with fewer
-// words each).  The slice descriptors are read with scalar loads one slice
-// ahead and the instance arrays addressed as device memory (2.78 ms; with
-// the descriptor read per lane before the words and generic loads, 3.25 ms;
-// 2.70 ms once a workgroup item's next-phase first slices are loaded before
-// the phase barrier, queue_phase_wg).
-// Loading the next slice's words as well, with both buffers at full width,
-// measured 2.82-2.89 ms: the extra registers and copies cost more than the
-// latency they hide.
+// One colour phase of one replica on one wavefront: lane = row of a slice,
+// couplings from memory, spins in LDS.  All coupling and hyper-coupling words
+// of a slice (up to kPreW and kPreT of them, predicated on the slice's widths)
+// are loaded before any is used, so a wavefront keeps a whole slice's loads in
+// flight.  The slice descriptors are read with scalar loads one slice ahead
+// and the instance arrays addressed as device memory.
 constexpr int kPreW = 16, kPreT = 8;
 
 struct SliceWords {
@@ -152,7 +147,7 @@ __device__ __forceinline__ void queue_eval(const InstDev& I, const Slice& S, con
 
 template <bool TIE>
 __device__ __forceinline__ void queue_phase(const InstDev& I0, const Slice* __restrict__ slices0, int s_lo, int s_hi,
-                                            int8_t* __restrict__ sp, int w, int nw, int lane, uint32_t sweep,
+                                            int8_t* __restrict__ sp, int lane, uint32_t sweep,
                                             uint64_t seed, uint32_t r, long long& dE, int& my, long long& e6)
 {
     InstDev I = I0;
@@ -164,60 +159,20 @@ __device__ __forceinline__ void queue_phase(const InstDev& I0, const Slice* __re
     const Slice* slices = queue_uniform(slices0);
     // the next slice's descriptor is read while this slice's words are in
     // flight, so a slice costs one memory latency, not two
-    int sl = __builtin_amdgcn_readfirstlane(s_lo + w);
+    int sl = __builtin_amdgcn_readfirstlane(s_lo);
     q_v4 nx = {0u, 0u, 0u, 0u};
     if (sl < s_hi) nx = queue_slice_raw(slices, sl);
-    for (; sl < s_hi; sl += nw) {
+    for (; sl < s_hi; ++sl) {
         // the descriptor is first used here, one slice after its load was
         // issued (the empty statement keeps the compiler from unpacking, and
         // so waiting for, it right after the load)
         asm volatile("" : "+s"(nx.x), "+s"(nx.y), "+s"(nx.z), "+s"(nx.w));
         const Slice S = queue_unpack(nx);
-        if (sl + nw < s_hi) nx = queue_slice_raw(slices, sl + nw);
+        if (sl + 1 < s_hi) nx = queue_slice_raw(slices, sl + 1);
         SliceWords cur;
         queue_load(I, S, lane, cur);
         queue_eval<TIE>(I, S, cur, sp, lane, sweep, seed, r, dE, my, e6);
     }
-}
-
-// A wavefront's first slice of a phase, loaded before the barrier that
-// opens the phase (couplings and fields are read-only).
-struct QueueCarry {
-    Slice S;
-    SliceWords W;
-    bool valid;
-};
-
-// One colour phase of a workgroup item: the wavefront's first slice comes
-// loaded in `cy`, the rest as in queue_phase.
-template <bool TIE>
-__device__ __forceinline__ void queue_phase_wg(const InstDev& I, const Slice* slices, int s_lo, int s_hi,
-                                               int8_t* __restrict__ sp, int w, int nw, int lane, uint32_t sweep,
-                                               uint64_t seed, uint32_t r, long long& dE, int& my, long long& e6,
-                                               const QueueCarry& cy)
-{
-    if (!cy.valid) return;
-    int sl = __builtin_amdgcn_readfirstlane(s_lo + w);
-    q_v4 nx = {0u, 0u, 0u, 0u};
-    if (sl + nw < s_hi) nx = queue_slice_raw(slices, sl + nw);
-    queue_eval<TIE>(I, cy.S, cy.W, sp, lane, sweep, seed, r, dE, my, e6);
-    for (sl += nw; sl < s_hi; sl += nw) {
-        asm volatile("" : "+s"(nx.x), "+s"(nx.y), "+s"(nx.z), "+s"(nx.w));
-        const Slice S = queue_unpack(nx);
-        if (sl + nw < s_hi) nx = queue_slice_raw(slices, sl + nw);
-        SliceWords cur;
-        queue_load(I, S, lane, cur);
-        queue_eval<TIE>(I, S, cur, sp, lane, sweep, seed, r, dE, my, e6);
-    }
-}
-
-// Workgroup barrier that orders LDS only: device-memory loads issued before
-// it (the next phase's first slice) stay in flight across it.
-__device__ __forceinline__ void queue_lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // e6: -6 E of the last sweep's fields, exact when that sweep flipped nothing.
@@ -239,22 +194,29 @@ __device__ __forceinline__ void queue_finish(const InstTab& Q, int r, long long 
     if (until_conv && !conv) atomicAdd(&cs->unconverged, 1ull);
 }
 
+struct QueueLds {
+    TeamLds team;
+    long long pd[kBatWaves], pe[kBatWaves];
+    int pf[kBatWaves], item;
+};
+
 template <bool TIE>
 __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict__ tab, const int32_t* __restrict__ ctab,
                                                        const QueueItem* __restrict__ items, int n_big, int n_items,
                                                        uint32_t* __restrict__ counters, int wave_lds,
                                                        RepState* __restrict__ rs, CallStats* __restrict__ cs, int T,
-                                                       uint64_t seed, int until_conv)
+                                                       uint64_t seed, int until_conv, uint32_t fixed_off)
 {
-    extern __shared__ uint64_t lds64[];
-    int8_t* lds = reinterpret_cast<int8_t*>(lds64);
+    // the items' spins at the start of LDS (their addresses need no base
+    // added), the fixed part behind them
+    extern __shared__ __align__(16) int8_t lds[];
+    QueueLds& F = *reinterpret_cast<QueueLds*>(lds + fixed_off);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    __shared__ int s_item, s_any[3];
     // ---- large items: the whole workgroup on one replica
     for (;;) {
-        if (tid == 0) s_item = (int)atomicAdd(&counters[0], 1u);
+        if (tid == 0) F.item = (int)atomicAdd(&counters[0], 1u);
         __syncthreads();
-        const int q = __builtin_amdgcn_readfirstlane(s_item);
+        const int q = __builtin_amdgcn_readfirstlane(F.item);
         __syncthreads();
         if (q >= n_big) break;
         const QueueItem it = items[q];
@@ -265,9 +227,6 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
         const bool frozen = st0->converged != 0;
         if (frozen) continue;
         const uint32_t base = (uint32_t)st0->sweeps;
-        for (int k = tid; k < I.n; k += kBatThreads) lds[k] = gsp[k];
-        if (tid < 3) s_any[tid] = 0;
-        __syncthreads();
         // the instance arrays and slice table in scalar registers
         InstDev J = I;
         J.nbr = queue_uniform(I.nbr);
@@ -275,96 +234,46 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
         J.tb = queue_uniform(I.tb);
         J.h = queue_uniform(I.h);
         J.ext = queue_uniform(I.ext);
-        const Slice* sls = queue_uniform(I.slices);
-        const int C = Q.C;
-        const int32_t* ct = ctab + Q.ctab_off;
-        // this wavefront's first slice of colour 0
-        QueueCarry cy;
-        {
-            const int sl0 = __builtin_amdgcn_readfirstlane(ct[0] + wave);
-            cy.valid = sl0 < ct[1];
-            if (cy.valid) {
-                cy.S = queue_unpack(queue_slice_raw(sls, sl0));
-                queue_load(J, cy.S, lane, cy.W);
-            }
-        }
-        long long dE = 0, e6 = 0;
-        int nflip = 0, performed = 0, lastflip = 0;
-        for (int t = 0; t < T; ++t) {
-            int my = 0;
-            e6 = 0;
-            for (int c = 0; c < C; ++c) {
-                // the descriptor of this wavefront's first slice of the next
-                // phase, read while this phase runs
-                const int cn = c + 1 < C ? c + 1 : 0;
-                const int sln = __builtin_amdgcn_readfirstlane(ct[cn] + wave);
-                const bool nval = sln < ct[cn + 1];
-                q_v4 nraw = {0u, 0u, 0u, 0u};
-                if (nval) nraw = queue_slice_raw(sls, sln);
-                queue_phase_wg<TIE>(J, sls, ct[c], ct[c + 1], lds, wave, kBatWaves, lane, base + t, seed,
-                                    (uint32_t)it.r, dE, my, e6, cy);
-                // that slice's words, in flight across the barrier
-                asm volatile("" : "+s"(nraw.x), "+s"(nraw.y), "+s"(nraw.z), "+s"(nraw.w));
-                cy.valid = nval;
-                if (nval) {
-                    cy.S = queue_unpack(nraw);
-                    queue_load(J, cy.S, lane, cy.W);
-                }
-                if (c + 1 < C) {
-                    queue_lds_barrier();
-                } else {
-                    // the sweep's last barrier also tells whether it flipped
-                    // anything: slot t % 3 is set before the barrier and read
-                    // after it; slot (t + 2) % 3 is cleared for sweep t + 2,
-                    // after every read of it (sweep t - 1) and a barrier before
-                    // any write of it
-                    if (__ballot(my != 0) != 0 && lane == 0) s_any[t % 3] = 1;
-                    queue_lds_barrier();
-                }
-            }
-            nflip += my;
-            performed = t + 1;
-            const bool tot = s_any[t % 3] != 0;
-            if (tid == 0) s_any[(t + 2) % 3] = 0;
-            if (tot) lastflip = t + 1;
-            if (until_conv && !tot) break;
-        }
-        for (int k = tid; k < I.n; k += kBatThreads) gsp[k] = lds[k];
+        J.slices = queue_uniform(I.slices);
+        J.n = __builtin_amdgcn_readfirstlane(I.n);
+        const TeamArgs A{J,    queue_uniform(ctab + Q.ctab_off),
+                         __builtin_amdgcn_readfirstlane(Q.C),
+                         1,    0,
+                         it.r, gsp,
+                         nullptr, nullptr,
+                         base, T,
+                         until_conv, seed,
+                         reinterpret_cast<uint32_t*>(lds), &F.team};
+        TeamOut o;
+        if (__builtin_amdgcn_readfirstlane(I.has_tri)) o = team_run<true, TIE, true, true, kTeamW>(A);
+        else if (__builtin_amdgcn_readfirstlane(Q.max_ew) <= 4) o = team_run<true, TIE, false, true, 4>(A);
+        else o = team_run<true, TIE, false, true, kTeamW>(A);
         // fold the workgroup's dE, energy sum and flips
-        long long wd = dE, we = e6;
-        int wf = nflip;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            wd += __shfl_xor(wd, off, 64);
-            we += __shfl_xor(we, off, 64);
-            wf += __shfl_xor(wf, off, 64);
-        }
-        __shared__ long long pd[kBatWaves], pe[kBatWaves];
-        __shared__ int pf[kBatWaves];
+        const long long wd = team_wave_sum(o.dE), we = team_wave_sum(o.e6);
         if (lane == 0) {
-            pd[wave] = wd;
-            pe[wave] = we;
-            pf[wave] = wf;
+            F.pd[wave] = wd;
+            F.pe[wave] = we;
+            F.pf[wave] = (int)o.nf;
         }
         __syncthreads();
         if (tid == 0) {
             long long a = 0, e = 0;
             int b = 0;
             for (int w = 0; w < kBatWaves; ++w) {
-                a += pd[w];
-                e += pe[w];
-                b += pf[w];
+                a += F.pd[w];
+                e += F.pe[w];
+                b += F.pf[w];
             }
-            queue_finish(Q, it.r, a, e, b, performed, lastflip, T, until_conv, rs, cs);
+            queue_finish(Q, it.r, a, e, b, o.performed, o.lastflip, T, until_conv, rs, cs);
         }
         __syncthreads();
     }
     // ---- small items: one wavefront per replica, 16 at a time
     int8_t* wl = lds + wave * wave_lds;
     for (;;) {
-        if (tid == 0) s_item = n_big + (int)atomicAdd(&counters[1], (unsigned)kBatWaves);
+        if (tid == 0) F.item = n_big + (int)atomicAdd(&counters[1], (unsigned)kBatWaves);
         __syncthreads();
-        const int q0 = __builtin_amdgcn_readfirstlane(s_item);
+        const int q0 = __builtin_amdgcn_readfirstlane(F.item);
         __syncthreads();
         if (q0 >= n_items) break;
         const int q = __builtin_amdgcn_readfirstlane(q0 + wave);
@@ -386,7 +295,7 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
                     int my = 0;
                     e6 = 0;
                     for (int c = 0; c < Q.C; ++c) {
-                        queue_phase<TIE>(I, I.slices, ctab[Q.ctab_off + c], ctab[Q.ctab_off + c + 1], wl, 0, 1, lane,
+                        queue_phase<TIE>(I, I.slices, ctab[Q.ctab_off + c], ctab[Q.ctab_off + c + 1], wl, lane,
                                          base + t, seed, (uint32_t)it.r, dE, my, e6);
                         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                         __builtin_amdgcn_wave_barrier();
@@ -416,11 +325,14 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
     }
 }
 
+// LDS of a workgroup whose items take `lds` bytes.
+static size_t queue_lds(size_t lds) { return (lds + 15) / 16 * 16 + sizeof(QueueLds); }
 
 int queue_max_blocks(size_t lds)
 {
     const void* kern = (const void*)k_queue<true>;
     int per_cu = 0, dev = 0, cus = 0;
+    lds = queue_lds(lds);
     if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kBatThreads, lds) != hipSuccess ||
         hipGetDevice(&dev) != hipSuccess ||
@@ -436,14 +348,16 @@ hipError_t launch_queue(const InstTab* tab, const int32_t* ctab, const QueueItem
                         uint64_t seed, int rule, int until_conv, hipStream_t st)
 {
     const void* kern = rule == 1 ? (const void*)k_queue<true> : (const void*)k_queue<false>;
+    const uint32_t fixed = (uint32_t)((lds + 15) / 16 * 16);
+    lds = queue_lds(lds);
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     if (rule == 1)
         hipLaunchKernelGGL(k_queue<true>, dim3(grid), dim3(kBatThreads), lds, st, tab, ctab, items, n_big, n_items,
-                           counters, wave_lds, rs, cs, T, seed, until_conv);
+                           counters, wave_lds, rs, cs, T, seed, until_conv, fixed);
     else
         hipLaunchKernelGGL(k_queue<false>, dim3(grid), dim3(kBatThreads), lds, st, tab, ctab, items, n_big, n_items,
-                           counters, wave_lds, rs, cs, T, seed, until_conv);
+                           counters, wave_lds, rs, cs, T, seed, until_conv, fixed);
     return hipGetLastError();
 }
 
