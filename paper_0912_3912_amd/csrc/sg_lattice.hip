@@ -408,10 +408,18 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_tiles(LatticeDev Lt, Ti
     }
 }
 
-// Whole lattice of replica r = blockIdx.x in one workgroup (spins in LDS,
-// records read through the cache).  until_conv: stop after the first sweep
-// without flips, recording lastflip as the per-phase kernels do.
-template <int D, bool TIE>
+// Whole lattice of replica r = blockIdx.x in one workgroup (spins in LDS).
+// until_conv: stop after the first sweep without flips, recording lastflip as
+// the per-phase kernels do.  A phase is a chain of LDS reads, a decision and a
+// barrier, so a thread keeps its NS sites of each colour (records and
+// neighbours' addresses) in registers, and a workgroup has no more threads
+// than a colour has sites (the launch's threads x NS are at least that many).
+// NS = 0: any number of sites, records read through the cache one site ahead.
+// 100 sweeps under TIE with 1024 threads, records read and sites worked out in
+// each phase, and now: 16 x 16 142 and 75 us, 64 x 64 488 and 212 us, 90 x 90
+// 900 and 362 us (registers); 240 x 240 5.9 and 3.9 ms.  64 greedy descents
+// from random starts at 16 x 16, whole call: 54 and 48 us.
+template <int D, bool TIE, int NS>
 __global__ __launch_bounds__(kLatThreads) void k_lattice_wg(LatticeDev Lt, int8_t* __restrict__ canon, int64_t stride,
                                                             RepState* __restrict__ rs, int64_t* __restrict__ acc,
                                                             int nslots, int T, uint64_t seed, int until_conv,
@@ -419,90 +427,151 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_wg(LatticeDev Lt, int8_
 {
     extern __shared__ uint64_t lds64[];
     int8_t* s = reinterpret_cast<int8_t*>(lds64);
+    const uint8_t* su = reinterpret_cast<const uint8_t*>(lds64);
     const int r = blockIdx.x;
     RepState* stp = rs + r;
     if (!solve && stp->converged) return;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, nth = blockDim.x, nwaves = nth >> 6;
     const int L0 = Lt.L[0], L1 = Lt.L[1], L2 = Lt.L[2];
     const int n = Lt.n, half = n / 2;
     int8_t* cs = canon + (int64_t)r * stride;
+    // a site's coordinates and neighbours
+    struct Site {
+        int g, xp, xm, yp, ym, zp, zm;
+    };
+    const uint32_t mL1 = fdiv_magic((uint32_t)L1);
+    const int hz = L2 >> 1;  // sites of one colour per z row
+    const int total = L0 * L1 * hz;
+    const uint32_t mhz = fdiv_magic((uint32_t)hz);
+    auto site = [&](int c, int row, int j) {
+        const int x = D == 3 ? (int)fdiv((uint32_t)row, mL1) : 0;
+        const int y = row - x * L1;
+        const int z = ((c - Lt.c0 - x - y) & 1) + 2 * j;
+        const int g = row * L2 + z;
+        Site q;
+        q.g = g;
+        q.zp = z + 1 == L2 ? g + 1 - L2 : g + 1;
+        q.zm = z == 0 ? g - 1 + L2 : g - 1;
+        q.yp = y + 1 == L1 ? g + L2 - L1 * L2 : g + L2;
+        q.ym = y == 0 ? g - L2 + L1 * L2 : g - L2;
+        q.xp = q.xm = 0;
+        if (D == 3) {
+            q.xp = x + 1 == L0 ? g + L1 * L2 - n : g + L1 * L2;
+            q.xm = x == 0 ? g - L1 * L2 + n : g - L1 * L2;
+        }
+        return q;
+    };
+    // sites in registers: addresses in pairs (they are below 2^14)
+    constexpr int NR = NS > 0 ? NS : 1;
+    uint64_t rec[2][NR];
+    uint32_t gz[2][NR], zy[2][NR], yx[2][NR];
+    int xx[2][NR];
+    if (NS > 0) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int u = 0; u < NR; ++u) {
+                const int id = min(u * nth + tid, total - 1);
+                const int row = (int)fdiv((uint32_t)id, mhz);
+                const Site q = site(c, row, id - row * hz);
+                rec[c][u] = Lt.rec[q.g];
+                gz[c][u] = (uint32_t)q.g | (uint32_t)q.zp << 16;
+                zy[c][u] = (uint32_t)q.zm | (uint32_t)q.yp << 16;
+                yx[c][u] = (uint32_t)q.ym | (uint32_t)q.xp << 16;
+                xx[c][u] = q.xm;
+            }
+    }
     // load: site g <- internal index; a solve draws the random start instead
     // (the start rule of every other start kernel: the Philox bit of (site,
     // 0xFFFFFFFF, instance, restart), set meaning s = -1)
-    for (int g = tid; g < n; g += kLatThreads) {
+    for (int g = tid; g < n; g += nth) {
         if (solve) {
             s[g] = (int8_t)(rng_bit(seed, (uint32_t)g, 0xFFFFFFFFu, Lt.instance_id, (uint32_t)r) ? -1 : 1);
         } else {
-            const int gz = g % L2, gy = (g / L2) % L1, gx = g / (L1 * L2);
-            s[g] = cs[((gx + gy + gz + Lt.c0) & 1) * half + (g >> 1)];
+            const int z = g % L2, gy = (g / L2) % L1, gx = g / (L1 * L2);
+            s[g] = cs[((gx + gy + z + Lt.c0) & 1) * half + (g >> 1)];
         }
     }
-    __shared__ int sweep_flips;
-    if (tid == 0) sweep_flips = 0;
     __syncthreads();
     const uint32_t base = solve ? 0u : (uint32_t)stp->sweeps;
-    const uint32_t mL2 = fdiv_magic((uint32_t)L2), mL1 = fdiv_magic((uint32_t)L1);
-    const int hz = L2 >> 1;  // sites of one colour per z row
     long long dE = 0, nflip = 0;
     int lastflip = 0;
+    // steps of the walk over a colour's sites when they are not in registers
+    const int drow = (int)fdiv((uint32_t)nth, mhz), dj = nth - drow * hz;
+    const int row0 = (int)fdiv((uint32_t)tid, mhz), j0 = tid - row0 * hz;
     for (int t = 0; t < T; ++t) {
-        int my = 0;
+        int my = 0, dhalf = 0;
+        auto decide = [&](int g, int f, uint32_t si) {
+            const int m = __builtin_amdgcn_sbfe((int)si, 7, 1);  // -1 for s = -1
+            const int hd = (f ^ m) - m;                          // half the energy change
+            bool flip = hd < 0;
+            if (TIE && hd == 0) flip = rng_bit(seed, (uint32_t)g, base + t, Lt.instance_id, (uint32_t)r) != 0;
+            if (flip) {
+                s[g] = (int8_t)(0u - si);
+                dhalf += hd;
+                ++my;
+            }
+        };
+        bool more = true;
+#pragma unroll
         for (int c = 0; c < 2; ++c) {
-            const int total = L0 * L1 * hz;
-            for (int id = tid; id < total; id += kLatThreads) {
-                const uint32_t row = fdiv((uint32_t)id, fdiv_magic((uint32_t)hz));
-                const int j = id - (int)row * hz;
-                const int x = (int)fdiv(row, mL1);
-                const int y = (int)row - x * L1;
-                const int z = ((c - Lt.c0 - x - y) & 1) + 2 * j;
-                const int g = (x * L1 + y) * L2 + z;
-                const uint64_t rc = Lt.rec[g];
-                const int yp = y + 1 == L1 ? 0 : y + 1, ym = y == 0 ? L1 - 1 : y - 1;
-                const int zp = z + 1 == L2 ? 0 : z + 1, zm = z == 0 ? L2 - 1 : z - 1;
-                const int rowb = x * L1;
-                int f = jb(rc, 6) + jb(rc, 2) * s[(rowb + yp) * L2 + z] + jb(rc, 3) * s[(rowb + ym) * L2 + z] +
-                        jb(rc, 4) * s[(rowb + y) * L2 + zp] + jb(rc, 5) * s[(rowb + y) * L2 + zm];
-                if (D == 3) {
-                    const int xp = x + 1 == L0 ? 0 : x + 1, xm = x == 0 ? L0 - 1 : x - 1;
-                    f += jb(rc, 0) * s[(xp * L1 + y) * L2 + z] + jb(rc, 1) * s[(xm * L1 + y) * L2 + z];
-                }
-                const int si = s[g];
-                const int d = 2 * si * f;
-                bool flip = d < 0;
-                if (TIE && d == 0) flip = rng_bit(seed, (uint32_t)g, base + t, Lt.instance_id, (uint32_t)r) != 0;
-                if (flip) {
-                    s[g] = (int8_t)(-si);
-                    dE += d;
-                    ++my;
+            if (NS > 0) {
+#pragma unroll
+                for (int u = 0; u < NR; ++u)
+                    if (u * nth + tid < total) {
+                        const int g = (int)(gz[c][u] & 0xFFFFu);
+                        decide(g,
+                               lat_field<D>(rec[c][u], D == 3 ? su[yx[c][u] >> 16] : 0u, D == 3 ? su[xx[c][u]] : 0u,
+                                            su[zy[c][u] >> 16], su[yx[c][u] & 0xFFFFu], su[gz[c][u] >> 16],
+                                            su[zy[c][u] & 0xFFFFu]),
+                               su[g]);
+                    }
+            } else if (tid < total) {
+                int row = row0, j = j0;
+                Site q = site(c, row, j);
+                uint64_t rc = Lt.rec[q.g];
+                for (int id = tid; id < total; id += nth) {
+                    const Site a = q;
+                    const uint64_t ra = rc;
+                    if (id + nth < total) {
+                        row += drow;
+                        j += dj;
+                        if (j >= hz) {
+                            j -= hz;
+                            ++row;
+                        }
+                        q = site(c, row, j);
+                        rc = Lt.rec[q.g];
+                    }
+                    decide(a.g,
+                           lat_field<D>(ra, D == 3 ? su[a.xp] : 0u, D == 3 ? su[a.xm] : 0u, su[a.yp], su[a.ym], su[a.zp],
+                                        su[a.zm]),
+                           su[a.g]);
                 }
             }
-            __syncthreads();
+            if (c == 1 && until_conv) more = __syncthreads_or(my) != 0;
+            else __syncthreads();
         }
-        (void)mL2;
         nflip += my;
+        dE += 2 * (long long)dhalf;
         if (until_conv) {
-            if (my) atomicAdd(&sweep_flips, my);
-            __syncthreads();
-            const int tot = sweep_flips;
-            __syncthreads();
-            if (tid == 0) sweep_flips = 0;
-            if (tot == 0) break;
+            if (!more) break;
             lastflip = t + 1;
         }
     }
     // a solve ends with the exact energy of the final spins (Sec. II eq. (1)):
     // every site adds its field and its +x, +y, +z bonds, so each term counts once
     long long Efin = 0;
-    for (int g = tid; g < n; g += kLatThreads) {
-        const int gz = g % L2, gy = (g / L2) % L1, gx = g / (L1 * L2);
-        cs[((gx + gy + gz + Lt.c0) & 1) * half + (g >> 1)] = s[g];
+    for (int g = tid; g < n; g += nth) {
+        const int gzi = g % L2, gy = (g / L2) % L1, gx = g / (L1 * L2);
+        cs[((gx + gy + gzi + Lt.c0) & 1) * half + (g >> 1)] = s[g];
         if (solve) {
             const uint64_t rc = Lt.rec[g];
-            const int yp = gy + 1 == L1 ? 0 : gy + 1, zp = gz + 1 == L2 ? 0 : gz + 1;
-            int f = jb(rc, 6) + jb(rc, 2) * s[(gx * L1 + yp) * L2 + gz] + jb(rc, 4) * s[(gx * L1 + gy) * L2 + zp];
+            const int yp = gy + 1 == L1 ? 0 : gy + 1, zp = gzi + 1 == L2 ? 0 : gzi + 1;
+            int f = jb(rc, 6) + jb(rc, 2) * s[(gx * L1 + yp) * L2 + gzi] + jb(rc, 4) * s[(gx * L1 + gy) * L2 + zp];
             if (D == 3) {
                 const int xp = gx + 1 == L0 ? 0 : gx + 1;
-                f += jb(rc, 0) * s[(xp * L1 + gy) * L2 + gz];
+                f += jb(rc, 0) * s[(xp * L1 + gy) * L2 + gzi];
             }
             Efin -= (long long)(s[g] * f);
         }
@@ -522,7 +591,7 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_wg(LatticeDev Lt, int8_
     __syncthreads();
     if (tid == 0) {
         long long a = 0, b2 = 0, e2 = 0;
-        for (int w = 0; w < kLatWaves; ++w) {
+        for (int w = 0; w < nwaves; ++w) {
             a += pd[w];
             b2 += pf[w];
             e2 += pe[w];
@@ -569,7 +638,7 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_wg(LatticeDev Lt, int8_
     const int R = (int)gridDim.x;
     long long bE = 0x7FFFFFFFFFFFFFFFll;
     int bR = 0x7FFFFFFF;
-    for (int k = tid; k < R; k += kLatThreads) {  // restarts rise along a thread: the first of equal energies stays
+    for (int k = tid; k < R; k += nth) {  // restarts rise along a thread: the first of equal energies stays
         const long long e = __hip_atomic_load(&rs[k].E, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (e < bE) {
             bE = e;
@@ -593,7 +662,7 @@ __global__ __launch_bounds__(kLatThreads) void k_lattice_wg(LatticeDev Lt, int8_
     }
     __syncthreads();
     if (tid == 0) {
-        for (int w = 1; w < kLatWaves; ++w)
+        for (int w = 1; w < nwaves; ++w)
             if (wE[w] < wE[0] || (wE[w] == wE[0] && wR[w] < wR[0])) {
                 wE[0] = wE[w];
                 wR[0] = wR[w];
@@ -716,37 +785,31 @@ hipError_t launch_lattice_wg(const LatticeDev& Lt, int8_t* canon, int64_t stride
 {
     const int solve = solve_p ? 1 : 0;
     const WgSolve sv = solve_p ? *solve_p : WgSolve{};
+    // sites in registers up to 4096 of a colour; more threads than sites only
+    // make the barriers longer
+    const int total = Lt.n / 2;
+    const int threads = std::min((total + 63) / 64 * 64, kLatThreads);
+    const int ns = total > 4 * threads ? 0 : total > 2 * threads ? 4 : total > threads ? 2 : 1;
+    const bool tie = rule == 1;
+    const int v = (Lt.D == 3 ? 8 : 0) + (tie ? 4 : 0) + (ns == 4 ? 3 : ns);
+    typedef void (*Kern)(LatticeDev, int8_t*, int64_t, RepState*, int64_t*, int, int, uint64_t, int, WgSolve, int);
+#define SG_WG(D, T) k_lattice_wg<D, T, 0>, k_lattice_wg<D, T, 1>, k_lattice_wg<D, T, 2>, k_lattice_wg<D, T, 4>
+    static const Kern kerns[16] = {SG_WG(2, false), SG_WG(2, true), SG_WG(3, false), SG_WG(3, true)};
+#undef SG_WG
     // the LDS size is raised once per kernel variant (a call per launch costs
     // as much host time as the launch of a small lattice itself)
-    static std::atomic<size_t> lds_set[4];
+    static std::atomic<size_t> lds_set[16];
     const size_t lds = ((size_t)Lt.n + 7) / 8 * 8;
-    const bool tie = rule == 1;
-    const void* kern;
-    if (Lt.D == 3) kern = tie ? (const void*)k_lattice_wg<3, true> : (const void*)k_lattice_wg<3, false>;
-    else kern = tie ? (const void*)k_lattice_wg<2, true> : (const void*)k_lattice_wg<2, false>;
-    std::atomic<size_t>& set = lds_set[(Lt.D == 3 ? 2 : 0) + (tie ? 1 : 0)];
+    std::atomic<size_t>& set = lds_set[v];
     if (lds > set.load(std::memory_order_relaxed)) {
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void*)kerns[v], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         size_t cur = set.load(std::memory_order_relaxed);
         while (lds > cur && !set.compare_exchange_weak(cur, lds)) {
         }
     }
-    if (Lt.D == 3) {
-        if (tie)
-            hipLaunchKernelGGL((k_lattice_wg<3, true>), dim3(R), dim3(kLatThreads), lds, st, Lt, canon, stride, rs, acc,
-                               nslots, T, seed, until_conv, sv, solve);
-        else
-            hipLaunchKernelGGL((k_lattice_wg<3, false>), dim3(R), dim3(kLatThreads), lds, st, Lt, canon, stride, rs,
-                               acc, nslots, T, seed, until_conv, sv, solve);
-    } else {
-        if (tie)
-            hipLaunchKernelGGL((k_lattice_wg<2, true>), dim3(R), dim3(kLatThreads), lds, st, Lt, canon, stride, rs, acc,
-                               nslots, T, seed, until_conv, sv, solve);
-        else
-            hipLaunchKernelGGL((k_lattice_wg<2, false>), dim3(R), dim3(kLatThreads), lds, st, Lt, canon, stride, rs,
-                               acc, nslots, T, seed, until_conv, sv, solve);
-    }
+    hipLaunchKernelGGL(kerns[v], dim3(R), dim3(threads), lds, st, Lt, canon, stride, rs, acc, nslots, T, seed,
+                       until_conv, sv, solve);
     return hipGetLastError();
 }
 
