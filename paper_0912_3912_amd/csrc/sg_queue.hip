@@ -4,7 +4,7 @@
 // rows of the sliced layout on lanes, couplings streamed from memory a slice
 // ahead, spins in LDS as bytes); small items run one per wavefront in a
 // private LDS window, 16 at a time.  Bound by the largest items: 96 instances
-// of 100 to 100000 spins, 8 restarts each: 1.27 ms a call, against 2.43 ms
+// of 100 to 100000 spins, 8 restarts each: 1.24 ms a call, against 2.43 ms
 // with loads under branches and an LDS wait per coupling.
 // Each replica runs to its own stopping point, and the replica state and the
 // call totals follow the per-phase kernels exactly: with until_converged a
@@ -207,8 +207,7 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
                                                        RepState* __restrict__ rs, CallStats* __restrict__ cs, int T,
                                                        uint64_t seed, int until_conv, uint32_t fixed_off)
 {
-    // the items' spins at the start of LDS (their addresses need no base
-    // added), the fixed part behind them
+    // the items' spins start LDS, the fixed part stands behind them
     extern __shared__ __align__(16) int8_t lds[];
     QueueLds& F = *reinterpret_cast<QueueLds*>(lds + fixed_off);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -243,7 +242,7 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
                          nullptr, nullptr,
                          base, T,
                          until_conv, seed,
-                         reinterpret_cast<uint32_t*>(lds), &F.team};
+                         &F.team};
         TeamOut o;
         if (__builtin_amdgcn_readfirstlane(I.has_tri)) o = team_run<true, TIE, true, true, kTeamW>(A);
         else if (__builtin_amdgcn_readfirstlane(Q.max_ew) <= 4) o = team_run<true, TIE, false, true, 4>(A);
@@ -348,6 +347,8 @@ hipError_t launch_queue(const InstTab* tab, const int32_t* ctab, const QueueItem
                         uint64_t seed, int rule, int until_conv, hipStream_t st)
 {
     const void* kern = rule == 1 ? (const void*)k_queue<true> : (const void*)k_queue<false>;
+    static const bool free0 = team_lds_free((const void*)k_queue<true>) && team_lds_free((const void*)k_queue<false>);
+    if (!free0) return hipErrorInvalidDeviceFunction;
     const uint32_t fixed = (uint32_t)((lds + 15) / 16 * 16);
     lds = queue_lds(lds);
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -33,13 +33,13 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(const InstDev I, const in
                                                        uint32_t tl_off)
 {
     extern __shared__ __align__(16) uint32_t bits[];
-    // the spins at the start of LDS: their addresses need no base added
+    // behind the spins, which start LDS
     TeamLds& tl = *reinterpret_cast<TeamLds*>(bits + tl_off);
     const int r = (int)blockIdx.x / G, m = (int)blockIdx.x % G;
     RepState* st = rs + r;
     if (st->converged) return;  // the same for the whole team
     const TeamArgs A{I,   ct,  C, G,          m,    r,    spins + stride * r, words + (size_t)r * I.nslices * 4,
-                     err, (uint32_t)st->sweeps, T, until_conv, seed, bits, &tl};
+                     err, (uint32_t)st->sweeps, T, until_conv, seed, &tl};
     const TeamOut o = team_run<false, TIE, TRI, false, W>(A);
     if (o.dead) return;
     const long long wd = team_wave_sum(o.dE);
@@ -87,6 +87,12 @@ hipError_t launch_team(const InstDev& I, int ew, const int32_t* ct, int C, int8_
     if (G < 1 || !team_fits(I.n, C) || (G > 1 && !words)) return hipErrorInvalidValue;
     const void* kern = team_kernel(rule == 1, I.has_tri != 0, ew);
     const size_t lds = team_lds(I.n);
+    static const bool free0 = [] {
+        bool ok = true;
+        for (int v = 0; v < 6; ++v) ok = ok && team_lds_free(team_kernel(v & 1, v >= 4, v & 2 ? 4 : kTeamW));
+        return ok;
+    }();
+    if (!free0) return hipErrorInvalidDeviceFunction;
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     InstDev a0 = I;

@@ -14,7 +14,7 @@
 // flight; all LDS reads of a slice are issued before the first is used; a
 // coupling takes two vector instructions beside its LDS read (bytes).  100000
 // spins of an Erdos-Renyi graph with triples, one workgroup per replica,
-// 12 sweeps of about 12 phases: 1.2 ms, against 2.33 ms with loads under
+// 12 sweeps of about 12 phases: 1.12 ms, against 2.33 ms with loads under
 // branches and an LDS wait per coupling.
 //
 // A team splits a colour's slices (64 rows each) evenly; after its share of a
@@ -110,10 +110,16 @@ __device__ __forceinline__ void team_load(const InstDev& I, const TeamSlice& S, 
 // the four-byte dot product multiplies that byte by a value held alone in the
 // low byte of the other operand: two vector instructions a coupling for bytes,
 // five for bits.
+// The spins begin at LDS address 0 (the kernels have no LDS but the launch's,
+// team_lds_free), so that a partner's index is its address.
 typedef __attribute__((address_space(3))) uint8_t team_l8;
+typedef __attribute__((address_space(3))) uint16_t team_l16;
+typedef __attribute__((address_space(3))) uint32_t team_l32;
+typedef __attribute__((address_space(3))) team_v4 team_l128;
+__device__ __forceinline__ team_l8* team_lds(uint32_t address) { return (team_l8*)(uintptr_t)address; }
 struct TeamBytes {
-    team_l8* s;
-    __device__ __forceinline__ uint32_t at(uint32_t j) const { return s[j]; }
+    static constexpr bool kCheap = true;  // adding a zero word costs less than a branch
+    static __device__ __forceinline__ uint32_t at(uint32_t j) { return *team_lds(j); }
     // product of two spins, from their bytes: (a ^ b) | 1
     static __device__ __forceinline__ uint32_t product(uint32_t a, uint32_t b) { return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, 1, 0xBE); }
     static __device__ __forceinline__ int add(uint32_t w, uint32_t v, int f) { return __builtin_amdgcn_sdot4((int)w, (int)v, f, false); }
@@ -121,8 +127,8 @@ struct TeamBytes {
     static __device__ __forceinline__ int sign(uint32_t v, uint32_t) { return __builtin_amdgcn_sbfe((int)v, 7, 1); }  // 0 or -1
 };
 struct TeamBits {
-    team_l8* s;
-    __device__ __forceinline__ uint32_t at(uint32_t j) const { return s[j >> 3]; }
+    static constexpr bool kCheap = false;
+    static __device__ __forceinline__ uint32_t at(uint32_t j) { return *team_lds(j >> 3); }
     static __device__ __forceinline__ uint32_t product(uint32_t a, uint32_t b) { return a ^ b; }
     static __device__ __forceinline__ int add(uint32_t w, uint32_t v, int f)
     {
@@ -134,18 +140,23 @@ struct TeamBits {
 };
 
 // A row's field, the coupling part in f1 (with h).  All LDS reads are issued
-// before the first is used; words beyond the slice's width are zero.
+// before the first is used; words beyond the slice's width are zero and add
+// nothing.
 template <class SP, bool TRI, int W>
-__device__ __forceinline__ int team_field(const InstDev& I, const TeamSlice& S, const TeamWords<W>& L, int lane, SP sp,
-                                          int h, int& f1)
+__device__ __forceinline__ int team_field(const InstDev& I, const TeamSlice& S, const TeamWords<W>& L, int lane, int h,
+                                          int& f1)
 {
     const uint32_t l = lane < S.rows ? (uint32_t)lane : 0u;
     uint32_t v[W], ua[kTeamT], ub[kTeamT];
 #pragma unroll
+    for (int k = 0; k < W; ++k) v[k] = 0u;
+#pragma unroll
+    for (int k = 0; k < kTeamT; ++k) ua[k] = ub[k] = 0u;
+#pragma unroll
     for (int k0 = 0; k0 < W; k0 += 4)
         if (k0 < S.ew) {
 #pragma unroll
-            for (int k = k0; k < k0 + 4; ++k) v[k] = sp.at(L.w[k] >> 8);
+            for (int k = k0; k < k0 + 4; ++k) v[k] = SP::at(L.w[k] >> 8);
         }
     if (TRI) {
 #pragma unroll
@@ -153,27 +164,27 @@ __device__ __forceinline__ int team_field(const InstDev& I, const TeamSlice& S, 
             if (k0 < S.tw) {
 #pragma unroll
                 for (int k = k0; k < k0 + 2; ++k) {
-                    ua[k] = sp.at(L.a[k] >> 8);
-                    ub[k] = sp.at(L.b[k]);
+                    ua[k] = SP::at(L.a[k] >> 8);
+                    ub[k] = SP::at(L.b[k]);
                 }
             }
     }
     int f = h;
 #pragma unroll
     for (int k0 = 0; k0 < W; k0 += 4)
-        if (k0 < S.ew) {
+        if (SP::kCheap || k0 < S.ew) {
 #pragma unroll
             for (int k = k0; k < k0 + 4; ++k) f = SP::add(L.w[k], SP::pick(v[k], L.w[k] >> 8), f);
         }
     for (int k = W; k < S.ew; ++k) {
         const uint32_t w = ((team_g32*)I.nbr + S.ebase)[l + (uint32_t)(k * kSlice)];
-        f = SP::add(w, SP::pick(sp.at(w >> 8), w >> 8), f);
+        f = SP::add(w, SP::pick(SP::at(w >> 8), w >> 8), f);
     }
     f1 = f;
     if (TRI) {
 #pragma unroll
         for (int k0 = 0; k0 < kTeamT; k0 += 2)
-            if (k0 < S.tw) {
+            if (SP::kCheap || k0 < S.tw) {
 #pragma unroll
                 for (int k = k0; k < k0 + 2; ++k)
                     f = SP::add(L.a[k], SP::product(SP::pick(ua[k], L.a[k] >> 8), SP::pick(ub[k], L.b[k])), f);
@@ -181,10 +192,17 @@ __device__ __forceinline__ int team_field(const InstDev& I, const TeamSlice& S, 
         for (int k = kTeamT; k < S.tw; ++k) {
             const uint32_t a = ((team_g32*)I.ta + S.tbase)[l + (uint32_t)(k * kSlice)];
             const uint32_t b = ((team_g32*)I.tb + S.tbase)[l + (uint32_t)(k * kSlice)];
-            f = SP::add(a, SP::product(SP::pick(sp.at(a >> 8), a >> 8), SP::pick(sp.at(b), b)), f);
+            f = SP::add(a, SP::product(SP::pick(SP::at(a >> 8), a >> 8), SP::pick(SP::at(b), b)), f);
         }
     }
     return f;
+}
+
+// Whether a kernel has no LDS of its own.
+inline bool team_lds_free(const void* kern)
+{
+    hipFuncAttributes a;
+    return hipFuncGetAttributes(&a, kern) == hipSuccess && a.sharedSizeBytes == 0;
 }
 
 // LDS of a kernel that calls team_run, beside the spins.
@@ -195,8 +213,8 @@ struct TeamLds {
     int any[3], dead;  // see the end of a sweep; 1 + the sweep in which a wait gave up
 };
 
-// A member's view of its replica.  bits: LDS, the replica's spins: n bytes, or as
-// bits (n + 31) / 32 + 1 words, from a multiple of 16 bytes on.
+// A member's view of its replica.  LDS from address 0 on: the replica's spins, n
+// bytes (to a multiple of 16), or as bits (n + 31) / 32 + 1 words.
 struct TeamArgs {
     InstDev I;
     const int32_t* ct;  // the C + 1 slice offsets of the colours
@@ -207,7 +225,6 @@ struct TeamArgs {
     uint32_t base;      // sweeps before the call
     int T, until_conv;
     uint64_t seed;
-    uint32_t* bits;
     TeamLds* L;
 };
 
@@ -236,7 +253,6 @@ __device__ __forceinline__ TeamOut team_run(const TeamArgs& A)
     const int G = A.G, m = A.m, C = A.C, n = I.n;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    uint32_t* bits = A.bits;
     if (tid < 3) T.any[tid] = 0;
     if (tid == 0) T.dead = 0;
     for (int c = tid; c < C && C <= kTeamColours; c += kTeamThreads) {
@@ -246,11 +262,10 @@ __device__ __forceinline__ TeamOut team_run(const TeamArgs& A)
         T.row[c] = s1 > s0 ? I.slices[s0].row0 : 0u;
     }
     using SP = typename std::conditional<BYTES, TeamBytes, TeamBits>::type;
-    const SP spins{(team_l8*)bits};
     // the spins, or their signs, sixteen a thread
     if (BYTES) {
         for (int k = tid; k * 16 < n; k += kTeamThreads)
-            reinterpret_cast<uint4*>(bits)[k] = *reinterpret_cast<const uint4*>(A.sp + k * 16);
+            *(team_l128*)team_lds((uint32_t)k * 16u) = *(const team_v4*)(A.sp + k * 16);
     } else {
         for (int k = tid; k * 16 < n; k += kTeamThreads) {
             const uint4 v = *reinterpret_cast<const uint4*>(A.sp + k * 16);
@@ -260,15 +275,16 @@ __device__ __forceinline__ TeamOut team_run(const TeamArgs& A)
             for (int u = 0; u < 4; ++u)
                 b |= ((w[u] >> 7 & 1u) | (w[u] >> 14 & 2u) | (w[u] >> 21 & 4u) | (w[u] >> 28 & 8u)) << (4 * u);
             if (n - k * 16 < 16) b &= (1u << (n - k * 16)) - 1u;
-            reinterpret_cast<uint16_t*>(bits)[k] = (uint16_t)b;
+            *(team_l16*)team_lds((uint32_t)k * 2u) = (uint16_t)b;
         }
     }
     __syncthreads();
     // 32 flips from row p on
     auto flip_at = [&](uint32_t p, uint32_t f) {
-        atomicXor(&bits[p >> 5], f << (p & 31));
+        team_l32* at = (team_l32*)team_lds((p >> 5) * 4u);
+        __hip_atomic_fetch_xor(at, f << (p & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         const uint32_t up = (p & 31) ? f >> (32 - (p & 31)) : 0u;
-        if (up) atomicXor(&bits[(p >> 5) + 1], up);
+        if (up) __hip_atomic_fetch_xor(at + 1, up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
 
     // this member's share of colour c: slices [lo, hi) (more colours than the
@@ -349,14 +365,14 @@ __device__ __forceinline__ TeamOut team_run(const TeamArgs& A)
         auto eval = [&](int sl, const TeamSlice& S, const TeamWords<W>& L) {
             const uint32_t i = S.row0 + (uint32_t)lane;
             const bool in = lane < S.rows;
-            const uint32_t own = spins.at(in ? i : S.row0);
+            const uint32_t own = SP::at(in ? i : S.row0);
             const int h = __builtin_amdgcn_sbfe((int)L.h, (in ? i : S.row0) * 8u, 8u);
             int f1;
-            const int f = team_field<SP, TRI, W>(I, S, L, lane, spins, h, f1);
+            const int f = team_field<SP, TRI, W>(I, S, L, lane, h, f1);
             const int mi = SP::sign(own, i);
-            const int d = 2 * ((f ^ mi) - mi);
-            bool flip = in && d < 0;
-            if (TIE && in && d == 0)
+            const int d = in ? 2 * ((f ^ mi) - mi) : 1;
+            bool flip = d < 0;
+            if (TIE && d == 0)
                 flip = rng_bit(A.seed, L.x, A.base + (uint32_t)t, I.instance_id, (uint32_t)A.r) != 0;
             if (E6) {
                 const int e = ((3 * h + f1 + 2 * f) ^ mi) - mi;
@@ -365,7 +381,7 @@ __device__ __forceinline__ TeamOut team_run(const TeamArgs& A)
             const uint64_t mask = __ballot(flip);
             out.dE += flip ? d : 0;
             if (BYTES) {
-                if (flip) spins.s[i] = (uint8_t)(0u - own);
+                if (flip) *team_lds(i) = (uint8_t)(0u - own);
             } else if (lane < 2) {
                 const uint32_t half = (uint32_t)(lane ? mask >> 32 : mask);
                 if (G > 1)
@@ -488,7 +504,7 @@ __device__ __forceinline__ TeamOut team_run(const TeamArgs& A)
         for (int k = share(c).x + wave, hi = share(c).y; k < hi; k += kTeamWaves) {
             const TeamSlice Z = team_unpack(team_raw(I.slices, k, zero));
             const uint32_t i = Z.row0 + (uint32_t)lane;
-            if (lane < Z.rows) ((team_gw8*)A.sp)[i] = BYTES ? (int8_t)spins.s[i] : SP::pick(spins.at(i), i) ? (int8_t)-1 : (int8_t)1;
+            if (lane < Z.rows) ((team_gw8*)A.sp)[i] = BYTES ? (int8_t)SP::at(i) : SP::pick(SP::at(i), i) ? (int8_t)-1 : (int8_t)1;
         }
     return out;
 }
