@@ -1509,7 +1509,8 @@ int team_slices(const HostInst& q)
 // exchange words those large enough to split, unless a batch (which the queue
 // schedule takes).
 constexpr int32_t kTeamMaxR = 64;
-constexpr int32_t kTeamSplit = 64;  // slices of a colour from which a replica is split over workgroups
+constexpr int32_t kTeamSplit = 80;   // slices of a colour beyond which a replica is split over workgroups
+constexpr int32_t kTeamAlone = 128;  // and up to which one workgroup beats per-phase launches
 bool can_team(const HostInst& q) { return !q.wide && !q.dense && sg::team_fits(q.n, q.C); }
 bool team_words(const sg_ctx* H, const HostInst& q)
 {
@@ -1835,12 +1836,16 @@ sg_status run_phase_schedule(sg_handle H, const sg_run_params* p, const std::vec
 // SG_SCHED_AUTO would otherwise give to per-phase launches; 0: not used.  A
 // workgroup's sixteen wavefronts take a phase's slices in turn, a microsecond
 // or so each, an exchange costs about two, and one workgroup needs no
-// cooperative launch.  Whole calls on 3-regular graphs, one replica, in
-// microseconds (per-phase launches / one workgroup / best team): 1000 spins
-// 157 / 62 / -, 10000 spins 156 / 87 / -, 100000 spins 174 / 384 / 119 (128),
-// 500000 spins 330 / 1950 / 159 (245); teams of a twelfth of the largest
-// colour's slices are within 10% of the best (20000 spins: 12.1 us a sweep
-// with 10 workgroups, 11.7 with 16; 100000: 14.5 with 49, 13.7 with 128).
+// cooperative launch.  Kernel times in microseconds, GREEDY to convergence /
+// 16 sweeps under TIE, 3-regular graphs (slices of the largest colour = n / 200
+// or so): per-phase launches, one workgroup, a team (members):
+//   6000 spins    139 / 297     49 / 106
+//   20000         144 / 308     79 / 227     91 / 200 (10)
+//   26000         146 / 312     91 / 271     91 / 197 (13)
+//   60000         272 / 317    181 / 555    104 / 214 (30)
+//   500000                                   136 / 284 (245)
+// With triples, 20000: 539 / 810, 268 / 501, 298 / 540 (7).  Teams of a twelfth
+// of the largest colour's slices are within 10% of the best.
 int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
 {
     if (H->team_wgs < 0 || p->schedule != SG_SCHED_AUTO || p->max_sweeps <= 0 || q.R > kTeamMaxR || !can_team(q)) return 0;
@@ -1850,7 +1855,7 @@ int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
         const int most = sg::team_max_blocks(q.n, p->rule == SG_RULE_GREEDY_TIE, q.t > 0, q.max_ew);
         g = q.off_team == UINT64_MAX ? 1 : std::min(g, most / q.R);
     }
-    if (g >= 2 || ns <= 2 * kTeamSplit || H->team_wgs > 0) return std::max(g, 1);
+    if (g >= 2 || ns <= kTeamAlone || H->team_wgs > 0) return std::max(g, 1);
     return 0;  // large and not split: the per-phase launches use the whole device
 }
 

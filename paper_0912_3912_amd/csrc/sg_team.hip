@@ -22,9 +22,9 @@ namespace sg {
 // ct: the C + 1 slice offsets of the colours.  words: per replica two copies of
 // two words per slice, tags zero on entry.  acc slots (nslots per replica, zero
 // on entry) take the energy changes and flips, rs[r].lastflip 1 + the last
-// sweep that flipped.  Dynamic LDS: the spins' bits, then from word tl_off on a
+// sweep that flipped.  Dynamic LDS: the spins, then from word tl_off on a
 // TeamLds.
-template <bool TIE, bool TRI, int W>
+template <bool BYTES, bool TIE, bool TRI, int W>
 __global__ __launch_bounds__(kTeamThreads) void k_team(const InstDev I, const int32_t* __restrict__ ct, int C,
                                                        int8_t* __restrict__ spins, int64_t stride,
                                                        RepState* __restrict__ rs, int G, int64_t* __restrict__ acc,
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(const InstDev I, const in
     if (st->converged) return;  // the same for the whole team
     const TeamArgs A{I,   ct,  C, G,          m,    r,    spins + stride * r, words + (size_t)r * I.nslices * 4,
                      err, (uint32_t)st->sweeps, T, until_conv, seed, &tl};
-    const TeamOut o = team_run<false, TIE, TRI, false, W>(A);
+    const TeamOut o = team_run<BYTES, TIE, TRI, false, W>(A);
     if (o.dead) return;
     const long long wd = team_wave_sum(o.dE);
     if ((threadIdx.x & 63) == 0) {
@@ -51,26 +51,37 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(const InstDev I, const in
     if (m == 0 && threadIdx.x == 0) st->lastflip = o.lastflip;
 }
 
-// Rows of at most four couplings take a third of the loads.  (Hyper-coupled
-// rows are not that short.)
-static const void* team_kernel(bool tie, bool tri, int ew)
+// Rows of at most four couplings take a third of the loads (hyper-coupled rows
+// are not that short).  A workgroup alone holds the spins as bytes where they
+// fit, which takes half the instructions of bits (6000 spins of a 3-regular
+// graph, 16 sweeps under TIE: 141 us as bits, 106 as bytes).
+constexpr int kTeamByteN = 150000;
+static bool team_bytes(int n, int G) { return G == 1 && n <= kTeamByteN; }
+template <bool BYTES>
+static const void* team_variant(bool tie, bool tri, int ew)
 {
-    if (tri) return tie ? (const void*)k_team<true, true, kTeamW> : (const void*)k_team<false, true, kTeamW>;
-    if (ew <= 4) return tie ? (const void*)k_team<true, false, 4> : (const void*)k_team<false, false, 4>;
-    return tie ? (const void*)k_team<true, false, kTeamW> : (const void*)k_team<false, false, kTeamW>;
+    if (tri) return tie ? (const void*)k_team<BYTES, true, true, kTeamW> : (const void*)k_team<BYTES, false, true, kTeamW>;
+    if (ew <= 4) return tie ? (const void*)k_team<BYTES, true, false, 4> : (const void*)k_team<BYTES, false, false, 4>;
+    return tie ? (const void*)k_team<BYTES, true, false, kTeamW> : (const void*)k_team<BYTES, false, false, kTeamW>;
+}
+static const void* team_kernel(bool bytes, bool tie, bool tri, int ew)
+{
+    return bytes ? team_variant<true>(tie, tri, ew) : team_variant<false>(tie, tri, ew);
 }
 
 static size_t team_bits(int n) { return (((size_t)(n + 31) / 32 + 1) * 4 + 15) / 16 * 16; }
-static size_t team_lds(int n) { return team_bits(n) + sizeof(TeamLds); }
+// LDS before TeamLds
+static size_t team_spins(int n, int G) { return team_bytes(n, G) ? ((size_t)n + 15) / 16 * 16 : team_bits(n); }
 
 bool team_fits(int n, int C) { return team_bits(n) <= 150 * 1024 && C >= 1 && C <= kTeamColours; }
 
 int team_max_blocks(int n, bool tie, bool tri, int ew)
 {
-    const void* kern = team_kernel(tie, tri, ew);
+    const void* kern = team_kernel(false, tie, tri, ew);
+    const size_t lds = team_bits(n) + sizeof(TeamLds);
     int per_cu = 0, dev = 0, cus = 0;
-    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)team_lds(n)) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kTeamThreads, team_lds(n)) != hipSuccess ||
+    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kTeamThreads, lds) != hipSuccess ||
         hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
         (void)hipGetLastError();
@@ -85,18 +96,18 @@ hipError_t launch_team(const InstDev& I, int ew, const int32_t* ct, int C, int8_
 {
     if (R <= 0 || T <= 0) return hipSuccess;
     if (G < 1 || !team_fits(I.n, C) || (G > 1 && !words)) return hipErrorInvalidValue;
-    const void* kern = team_kernel(rule == 1, I.has_tri != 0, ew);
-    const size_t lds = team_lds(I.n);
+    const void* kern = team_kernel(team_bytes(I.n, G), rule == 1, I.has_tri != 0, ew);
+    const size_t lds = team_spins(I.n, G) + sizeof(TeamLds);
     static const bool free0 = [] {
         bool ok = true;
-        for (int v = 0; v < 6; ++v) ok = ok && team_lds_free(team_kernel(v & 1, v >= 4, v & 2 ? 4 : kTeamW));
+        for (int v = 0; v < 12; ++v) ok = ok && team_lds_free(team_kernel(v >= 6, v & 1, v % 6 >= 4, v & 2 ? 4 : kTeamW));
         return ok;
     }();
     if (!free0) return hipErrorInvalidDeviceFunction;
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     InstDev a0 = I;
-    uint32_t tl_off = (uint32_t)(team_bits(I.n) / 4);
+    uint32_t tl_off = (uint32_t)(team_spins(I.n, G) / 4);
     void* args[] = {&a0, &ct, &C, &spins, &stride, &rs, &G, &acc, &nslots, &words, &err, &T, &seed, &until_conv, &tl_off};
     // members wait for each other: the cooperative launch has them all resident
     if (G > 1) return hipLaunchCooperativeKernel(kern, dim3((unsigned)(R * G)), dim3(kTeamThreads), args, (unsigned)lds, st);

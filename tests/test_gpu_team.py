@@ -79,3 +79,39 @@ def test_chosen_teams(gpu, rule, uc):
     compare(h, insts[:1], ref[:1])
     assert np.array_equal(h.spins_out(0, 1), ref[0].spins[1])  # beyond the pinned buffer
     h.free()
+
+
+def _wide_rows():
+    """Rows of about 16 couplings (more than are loaded ahead), a few spins in
+    many triples, fields."""
+    rng = np.random.default_rng(8)
+    n = 26001
+    e = rng.integers(0, n, (8 * n, 2))
+    e = np.unique(np.sort(e[e[:, 0] != e[:, 1]], axis=1), axis=0)
+    t = np.unique(np.sort(np.stack([rng.integers(0, 300, 900), rng.integers(300, 600, 900), rng.integers(600, 900, 900)], 1),
+                          axis=1), axis=0)
+    return gen.Instance(n, e[:, 0], e[:, 1], rng.integers(1, 128, len(e)) * rng.choice([-1, 1], len(e)),
+                        rng.integers(-127, 128, n), tri=t, K=rng.integers(1, 100, len(t)), restarts=2, instance_id=6)
+
+
+@pytest.mark.parametrize("rule,uc,runs", [(GREEDY, True, [1000]), (TIE, False, [3, 4])])
+@pytest.mark.parametrize("name", ["triples", "wide rows"])
+def test_split_replicas(gpu, name, rule, uc, runs):
+    """Teams whose replicas hold the spins as bits, with hyper-couplings."""
+    import paper_0912_3912_amd as sg
+    inst = gen.erdos_renyi_triples(40003, seed=4, restarts=2) if name == "triples" else _wide_rows()
+    log(f"split replicas: {name} rule={rule} uc={uc} runs={runs}")
+    st = None
+    for r in runs:
+        st, _ = oracle.run(inst, seed=3, rule=rule, max_sweeps=r, until_converged=uc, state=st, threads=8)
+    for wgs in (0, 2, 33):
+        h = sg.load_instance([inst])
+        h.tune("team_wgs", wgs)
+        h.bind()
+        h.init_spins(3)
+        for r in runs:
+            h.run_sweeps(seed=3, rule=rule, max_sweeps=r, until_converged=uc)
+        log(f"  team of {h.query('last_team')}")
+        assert h.query("last_team") >= (2 if name == "triples" else 1)
+        compare(h, [inst], [st])
+        h.free()
