@@ -229,6 +229,7 @@ struct sg_ctx {
     hipStream_t cap_stream = nullptr;  // private stream used only to record graphs
     uint64_t off_tbase = 0;            // one sweep base per instance (graph replays)
     uint64_t off_tab = 0, off_ctab = 0, off_bitems = 0, off_qitems = 0, off_qcnt = 0;
+    uint64_t off_qteam = 0, off_qteam_tab = 0, qteam_bytes = 0;  // sums and exchange words of the queue schedule's teams
     uint64_t off_rep_inst = 0;
     // batched start / energy of the replicas not started one lane each: units
     // of 1024 spins (start) and of four slices (energy)
@@ -241,6 +242,7 @@ struct sg_ctx {
     bool lanes_on = false;
     int64_t n_block_item_cap = 0, ctab_len = 0;
     std::vector<sg::BlockItem> h_bitems;
+    std::vector<sg::QueueItem> h_qteams;  // see queue_teams
     std::vector<sg::QueueItem> h_qitems;
     uint8_t* dev = nullptr;
     hipStream_t stream = nullptr;
@@ -272,7 +274,7 @@ struct sg_ctx {
     // cost (microseconds), and how many of each the launch holds
     double last_model_phase_us = 0.0, last_model_ex_us = 0.0;
     int64_t last_model_phases = 0, last_model_exchanges = 0;
-    int32_t last_queue_grid = 0;
+    int32_t last_queue_grid = 0, last_queue_teams = 0;
 
     template <class T>
     T* at(uint64_t off) const { return reinterpret_cast<T*>(dev + off); }
@@ -1518,6 +1520,16 @@ bool team_words(const sg_ctx* H, const HostInst& q)
            (q.n > kQueueMaxN || q.lat_ok || H->total_reps < 64);
 }
 
+// Teams of the queue schedule: items that may run on several workgroups, at
+// most kQueueTeams of them on kQueueTeamWgs workgroups.
+constexpr int32_t kQueueTeams = 64, kQueueTeamWgs = 256;
+constexpr int32_t kQueueTeamMinN = 16384;
+bool queue_team_fits(const HostInst& q)
+{
+    return can_team(q) && !q.lat_ok && q.n >= kQueueTeamMinN && q.n <= kQueueMaxN && team_slices(q) > kTeamSplit;
+}
+uint64_t queue_team_bytes(const HostInst& q) { return 32 * (1 + (uint64_t)q.slices.size()); }
+
 // Energy tables (sg_dense.hip) for the pass-based search of a dense handle:
 // instances of at most kDenseTableMaxN spins share room for up to 32 MiB of
 // tables and run in rounds of as many instances as that holds.  A step takes
@@ -1735,6 +1747,21 @@ void layout(sg_ctx* H)
         if (off > SG_NOALLOC_MAX_BYTES || off + need <= SG_NOALLOC_MAX_BYTES)
             for (HostInst& q : H->insts)
                 if (team_words(H, q)) q.off_team = take((uint64_t)q.R * q.slices.size() * 32);
+    }
+    // and of the queue schedule's teams
+    {
+        std::vector<uint64_t> need;
+        for (const HostInst& q : H->insts)
+            if (H->total_reps >= 64 && queue_team_fits(q)) need.insert(need.end(), (size_t)std::min<int64_t>(q.R, kQueueTeams), queue_team_bytes(q));
+        std::sort(need.rbegin(), need.rend());
+        H->qteam_bytes = 0;
+        for (size_t k = 0; k < need.size() && k < (size_t)kQueueTeams; ++k) H->qteam_bytes += need[k];
+        constexpr uint64_t tab = 2 * kQueueTeamWgs * sizeof(sg::QueueItem);
+        if (off <= SG_NOALLOC_MAX_BYTES && off + tab + align_up(H->qteam_bytes) > SG_NOALLOC_MAX_BYTES) H->qteam_bytes = 0;
+        if (H->qteam_bytes) {
+            H->off_qteam = take(H->qteam_bytes);
+            H->off_qteam_tab = take(tab);
+        }
     }
     dense_tables(H, off);
     if (H->dense_tables) H->off_dense_table = take((uint64_t)H->dense_tables * 8 << H->dense_table_n);
@@ -2425,6 +2452,67 @@ sg_status run_block_schedule(sg_handle H, const sg_run_params* p, const std::vec
     return SG_OK;
 }
 
+// Teams for the first items of the sorted queue, listed per workgroup in
+// h_qteams; returns the bytes of words they take.  A workgroup runs an item
+// of n spins in about n + 3000 units of time (11 ns) and a team of g in
+// 1.28 n / g + 30000 (bits instead of bytes; an exchange every phase): 100000
+// spins with triples take 1121 us alone, 742, 527 and 426 us in teams of 2, 4
+// and 8.  With the first k items in teams that end with the largest of the
+// others, the call takes that long or the mean load of the workgroups; k
+// minimises it, if it saves a twelfth.
+uint64_t queue_teams(sg_handle H, const sg_run_params* p, int n_big, int grid, size_t lds, sg::QueueTeams& teams)
+{
+    if (H->team_wgs < 0 || !H->qteam_bytes || p->max_sweeps <= 0 || n_big < 1 || grid < 64 || H->queue_grid > 0) return 0;
+    auto inst = [&](int k) -> const HostInst& { return H->insts[(size_t)H->h_qitems[(size_t)k].inst]; };
+    auto alone = [&](int k) { return inst(k).n + 3000.0; };
+    if (!queue_team_fits(inst(0))) return 0;
+    double rest = 0;  // load of the items not in teams
+    for (const sg::QueueItem& it : H->h_qitems) rest += H->insts[(size_t)it.inst].n;
+    const int most = std::min(grid * 3 / 4, kQueueTeamWgs);
+    const double base = std::max(alone(0), rest / grid);
+    double best = base * 11 / 12;
+    int best_k = 0;
+    uint64_t bytes = 0, best_bytes = 0;
+    auto size = [&](int i, double end) { return std::max(2, (int)std::ceil(1.28 * inst(i).n / (end - 30000.0))); };
+    for (int k = 1; k <= kQueueTeams && k < n_big; ++k) {
+        if (!queue_team_fits(inst(k - 1))) break;
+        bytes += queue_team_bytes(inst(k - 1));
+        if (bytes > H->qteam_bytes) break;
+        rest -= inst(k - 1).n;
+        const double end = std::max(alone(k), 50000.0);
+        int wgs = 0;
+        double load = rest;
+        for (int i = 0; i < k; ++i) {
+            const int g = size(i, end);
+            wgs += g;
+            load += 1.28 * inst(i).n + 30000.0 * g;
+        }
+        if (wgs > most) break;
+        const double t = std::max(end, 1.1 * load / grid);
+        if (t < best) {
+            best = t;
+            best_k = k;
+            best_bytes = bytes;
+        }
+    }
+    if (!best_k || grid > sg::queue_max_blocks(lds)) return 0;
+    H->h_qteams.clear();
+    const double end = std::max(alone(best_k), 50000.0);
+    uint32_t at = 0;
+    for (int i = 0; i < best_k; ++i) {
+        const int g = size(i, end);
+        const sg::QueueItem it = H->h_qitems[(size_t)i];
+        for (int m = 0; m < g; ++m) {
+            H->h_qteams.push_back(it);
+            H->h_qteams.push_back(sg::QueueItem{m | g << 16, (int32_t)at});
+        }
+        teams.nwg += g;
+        at += (uint32_t)(queue_team_bytes(inst(i)) / 32);
+    }
+    teams.n = best_k;
+    return best_bytes;
+}
+
 sg_status run_queue_schedule(sg_handle H, const sg_run_params* p, const std::vector<int>& which)
 {
     if (which.empty()) return SG_OK;
@@ -2455,21 +2543,35 @@ sg_status run_queue_schedule(sg_handle H, const sg_run_params* p, const std::vec
     if (grid <= 0) grid = sg::queue_max_blocks(lds);
     if (grid <= 0) grid = 256;
     grid = std::min<int>(grid, (int)H->h_qitems.size());
+    const int n_items = (int)H->h_qitems.size();
+    sg::QueueItem* dit = H->at<sg::QueueItem>(H->off_qitems);
+    sg::QueueTeams teams;
+    const uint64_t tbytes = queue_teams(H, p, n_big, grid, lds, teams);
+    if (teams.n) {
+        teams.tab = H->at<sg::QueueItem>(H->off_qteam_tab);
+        teams.words = H->at<uint64_t>(H->off_qteam);
+        teams.err = H->at<uint32_t>(H->off_err);
+        SG_HIP(sg::launch_fill_u32(teams.words, tbytes / 4, 0u, st), "fill kernel");
+        if (!H->lat_err_check) SG_HIP(sg::launch_fill_u32(teams.err, 1, 0u, st), "fill kernel");
+        H->lat_err_check = true;
+        SG_HIP(hipMemcpyAsync(H->at<sg::QueueItem>(H->off_qteam_tab), H->h_qteams.data(),
+                              H->h_qteams.size() * sizeof(sg::QueueItem), hipMemcpyHostToDevice, st),
+               "upload queue teams");
+    }
     uint32_t* cnt = H->at<uint32_t>(H->off_qcnt);
     SG_HIP(sg::launch_fill_u32(cnt, 2, 0u, st), "fill kernel");
-    sg::QueueItem* dit = H->at<sg::QueueItem>(H->off_qitems);
     SG_HIP(hipMemcpyAsync(dit, H->h_qitems.data(), H->h_qitems.size() * sizeof(sg::QueueItem), hipMemcpyHostToDevice,
                           st),
            "upload queue items");
     SG_HIP(hipEventRecord(H->evh0, st), "event record");
     H->hot_launches = 1;
-    SG_HIP(sg::launch_queue(H->at<sg::InstTab>(H->off_tab), H->at<int32_t>(H->off_ctab), dit, n_big,
-                            (int)H->h_qitems.size(), cnt, wave_lds, lds, grid, H->reps(),
-                            H->at<sg::CallStats>(H->off_stats), p->max_sweeps, p->seed, p->rule, p->until_converged,
-                            st),
+    SG_HIP(sg::launch_queue(H->at<sg::InstTab>(H->off_tab), H->at<int32_t>(H->off_ctab), dit, n_big, n_items, cnt,
+                            wave_lds, lds, grid, H->reps(), H->at<sg::CallStats>(H->off_stats), p->max_sweeps, p->seed,
+                            p->rule, p->until_converged, st, teams),
            "queue kernel");
     SG_HIP(hipEventRecord(H->evh1, st), "event record");
     SG_HIP(hipStreamSynchronize(st), "stream sync");  // the host item list is reused
+    H->last_queue_teams = teams.n;
     H->last_queue_grid = grid;
     return SG_OK;
 }
@@ -3459,6 +3561,7 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
     H->hot_launches = 0;
     H->lat_err_check = false;
     H->last_team = 0;
+    H->last_queue_teams = 0;
     H->e_written.assign(H->insts.size(), 0);
     for (int kind : {SG_SCHED_LATTICE, SG_SCHED_BLOCK, SG_SCHED_QUEUE, SG_SCHED_GRAPH, SG_SCHED_FIELDS, SG_SCHED_PHASE}) {
         std::vector<int> which;
@@ -3905,6 +4008,7 @@ sg_status sg_query(sg_handle H, const char* key, int64_t* value)
     else if (k == "last_msc") *value = H->last_msc;
     else if (k == "last_bits") *value = H->last_bits;
     else if (k == "last_queue_grid") *value = H->last_queue_grid;
+    else if (k == "last_queue_teams") *value = H->last_queue_teams;
     else if (k == "hot_ns") *value = (int64_t)(H->hot_us * 1000.0);
     else if (k == "hot_launches") *value = H->hot_launches;
     else if (k == "last_tiles") *value = (int64_t)H->last_tiles[0] * 1000000 + H->last_tiles[1] * 1000 + H->last_tiles[2];

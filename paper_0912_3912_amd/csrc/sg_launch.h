@@ -188,9 +188,20 @@ hipError_t launch_start_units(const InstTab* tab, const StartUnit* start_units, 
                               const StartUnit* energy_units, int64_t n_energy, const EnergySeg* segs, int64_t nsegs,
                               int64_t* part, RepState* rs, int64_t* out, uint64_t seed, bool init, hipStream_t st);
 inline size_t queue_big_lds(int n) { return (size_t)n; }  // LDS of an item on a whole workgroup
+// The first n items run on teams of workgroups before the queue starts.  Per
+// workgroup below nwg, tab holds its item and {member | members << 16, offset}:
+// the item's part of words, in units of 32 bytes; 32 bytes of sums and 32 bytes
+// per slice, all zero at launch.  The grid must be co-resident (at most
+// queue_max_blocks of its LDS).
+struct QueueTeams {
+    const QueueItem* tab = nullptr;
+    int nwg = 0, n = 0;
+    uint64_t* words = nullptr;
+    uint32_t* err = nullptr;
+};
 hipError_t launch_queue(const InstTab* tab, const int32_t* ctab, const QueueItem* items, int n_big, int n_items,
                         uint32_t* counters, int wave_lds, size_t lds, int grid, RepState* rs, CallStats* cs, int T,
-                        uint64_t seed, int rule, int until_conv, hipStream_t st);
+                        uint64_t seed, int rule, int until_conv, hipStream_t st, const QueueTeams& teams = QueueTeams{});
 
 // Sweeps of one packed instance in one launch (sg_team.hip): R teams of G
 // workgroups.  ct: its C + 1 colour slice offsets in device memory; words: per

@@ -3,8 +3,10 @@
 // decreasing size.  Large items run on the whole workgroup (sg_team_core.h:
 // rows of the sliced layout on lanes, couplings streamed from memory a slice
 // ahead, spins in LDS as bytes); small items run one per wavefront in a
-// private LDS window, 16 at a time.  Bound by the largest items: 96 instances
-// of 100 to 100000 spins, 8 restarts each: 1.24 ms a call, against 2.43 ms
+// private LDS window, 16 at a time.  Items that would outlast the rest run on
+// teams of workgroups first (QueueTeams).  Bound by the largest items: 96 instances
+// of 100 to 100000 spins, 8 restarts each: 1.07 ms a call (1.21 without
+// teams), against 2.43 ms
 // with loads under branches and an LDS wait per coupling.
 // Each replica runs to its own stopping point, and the replica state and the
 // call totals follow the per-phase kernels exactly: with until_converged a
@@ -194,6 +196,21 @@ __device__ __forceinline__ void queue_finish(const InstTab& Q, int r, long long 
     if (until_conv && !conv) atomicAdd(&cs->unconverged, 1ull);
 }
 
+// An instance whose arrays and sizes are in scalar registers.
+__device__ __forceinline__ InstDev queue_inst(const InstDev& I)
+{
+    InstDev J = I;
+    J.nbr = queue_uniform(I.nbr);
+    J.ta = queue_uniform(I.ta);
+    J.tb = queue_uniform(I.tb);
+    J.h = queue_uniform(I.h);
+    J.ext = queue_uniform(I.ext);
+    J.slices = queue_uniform(I.slices);
+    J.n = __builtin_amdgcn_readfirstlane(I.n);
+    J.nslices = __builtin_amdgcn_readfirstlane(I.nslices);
+    return J;
+}
+
 struct QueueLds {
     TeamLds team;
     long long pd[kBatWaves], pe[kBatWaves];
@@ -205,15 +222,49 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
                                                        const QueueItem* __restrict__ items, int n_big, int n_items,
                                                        uint32_t* __restrict__ counters, int wave_lds,
                                                        RepState* __restrict__ rs, CallStats* __restrict__ cs, int T,
-                                                       uint64_t seed, int until_conv, uint32_t fixed_off)
+                                                       uint64_t seed, int until_conv, uint32_t fixed_off,
+                                                       QueueTeams teams)
 {
     // the items' spins start LDS, the fixed part stands behind them
     extern __shared__ __align__(16) int8_t lds[];
     QueueLds& F = *reinterpret_cast<QueueLds*>(lds + fixed_off);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // ---- the first items by teams of workgroups, each workgroup in one team
+    if ((int)blockIdx.x < teams.nwg) {
+        const QueueItem it = teams.tab[2 * blockIdx.x], mb = teams.tab[2 * blockIdx.x + 1];
+        const int m = __builtin_amdgcn_readfirstlane(mb.inst & 0xFFFF), G = __builtin_amdgcn_readfirstlane(mb.inst >> 16);
+        unsigned long long* w = (unsigned long long*)teams.words + (int64_t)mb.r * 4;
+        const InstTab& Q = tab[it.inst];
+        const RepState* st0 = rs + Q.rep_base + it.r;
+        if (!st0->converged) {  // (the same for the whole team: its last member alone writes the state)
+            const TeamArgs A{queue_inst(Q.I), queue_uniform(ctab + Q.ctab_off), __builtin_amdgcn_readfirstlane(Q.C), G, m,
+                             it.r, Q.spins + (int64_t)it.r * Q.spin_stride, (uint64_t*)w + 4, teams.err,
+                             (uint32_t)st0->sweeps, T, until_conv, seed, &F.team};
+            TeamOut o;
+            if (__builtin_amdgcn_readfirstlane(Q.I.has_tri)) o = team_run<false, TIE, true, true, kTeamW>(A);
+            else o = team_run<false, TIE, false, true, kTeamW>(A);
+            if (o.dead) return;
+            const long long wd = team_wave_sum(o.dE), we = team_wave_sum(o.e6);
+            if (lane == 0) {
+                atomicAdd(w, (unsigned long long)wd);
+                atomicAdd(w + 1, (unsigned long long)we);
+                atomicAdd(w + 2, (unsigned long long)o.nf);
+                __threadfence();
+            }
+            __syncthreads();
+            // the member that arrives last has everyone's sums
+            if (tid == 0 && __hip_atomic_fetch_add(w + 3, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned long long)G) {
+                const long long a = (long long)__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const long long e = (long long)__hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const int b = (int)__hip_atomic_load(w + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                queue_finish(Q, it.r, a, e, b, o.performed, o.lastflip, T, until_conv, rs, cs);
+            }
+        }
+        __syncthreads();
+    }
     // ---- large items: the whole workgroup on one replica
     for (;;) {
-        if (tid == 0) F.item = (int)atomicAdd(&counters[0], 1u);
+        if (tid == 0) F.item = teams.n + (int)atomicAdd(&counters[0], 1u);
         __syncthreads();
         const int q = __builtin_amdgcn_readfirstlane(F.item);
         __syncthreads();
@@ -226,23 +277,8 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
         const bool frozen = st0->converged != 0;
         if (frozen) continue;
         const uint32_t base = (uint32_t)st0->sweeps;
-        // the instance arrays and slice table in scalar registers
-        InstDev J = I;
-        J.nbr = queue_uniform(I.nbr);
-        J.ta = queue_uniform(I.ta);
-        J.tb = queue_uniform(I.tb);
-        J.h = queue_uniform(I.h);
-        J.ext = queue_uniform(I.ext);
-        J.slices = queue_uniform(I.slices);
-        J.n = __builtin_amdgcn_readfirstlane(I.n);
-        const TeamArgs A{J,    queue_uniform(ctab + Q.ctab_off),
-                         __builtin_amdgcn_readfirstlane(Q.C),
-                         1,    0,
-                         it.r, gsp,
-                         nullptr, nullptr,
-                         base, T,
-                         until_conv, seed,
-                         &F.team};
+        const TeamArgs A{queue_inst(I), queue_uniform(ctab + Q.ctab_off), __builtin_amdgcn_readfirstlane(Q.C), 1, 0,
+                         it.r, gsp, nullptr, nullptr, base, T, until_conv, seed, &F.team};
         TeamOut o;
         if (__builtin_amdgcn_readfirstlane(I.has_tri)) o = team_run<true, TIE, true, true, kTeamW>(A);
         else if (__builtin_amdgcn_readfirstlane(Q.max_ew) <= 4) o = team_run<true, TIE, false, true, 4>(A);
@@ -344,22 +380,22 @@ int queue_max_blocks(size_t lds)
 
 hipError_t launch_queue(const InstTab* tab, const int32_t* ctab, const QueueItem* items, int n_big, int n_items,
                         uint32_t* counters, int wave_lds, size_t lds, int grid, RepState* rs, CallStats* cs, int T,
-                        uint64_t seed, int rule, int until_conv, hipStream_t st)
+                        uint64_t seed, int rule, int until_conv, hipStream_t st, const QueueTeams& teams0)
 {
     const void* kern = rule == 1 ? (const void*)k_queue<true> : (const void*)k_queue<false>;
     static const bool free0 = team_lds_free((const void*)k_queue<true>) && team_lds_free((const void*)k_queue<false>);
     if (!free0) return hipErrorInvalidDeviceFunction;
-    const uint32_t fixed = (uint32_t)((lds + 15) / 16 * 16);
+    uint32_t fixed = (uint32_t)((lds + 15) / 16 * 16);
     lds = queue_lds(lds);
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    if (rule == 1)
-        hipLaunchKernelGGL(k_queue<true>, dim3(grid), dim3(kBatThreads), lds, st, tab, ctab, items, n_big, n_items,
-                           counters, wave_lds, rs, cs, T, seed, until_conv, fixed);
-    else
-        hipLaunchKernelGGL(k_queue<false>, dim3(grid), dim3(kBatThreads), lds, st, tab, ctab, items, n_big, n_items,
-                           counters, wave_lds, rs, cs, T, seed, until_conv, fixed);
-    return hipGetLastError();
+    QueueTeams teams = teams0;
+    if (teams.nwg > grid || teams.n > n_big) return hipErrorInvalidValue;
+    void* args[] = {&tab, &ctab, &items, &n_big, &n_items, &counters, &wave_lds, &rs, &cs, &T, &seed, &until_conv,
+                    &fixed, &teams};
+    // members wait for each other: the cooperative launch has them all resident
+    if (teams.nwg) return hipLaunchCooperativeKernel(kern, dim3(grid), dim3(kBatThreads), args, (unsigned)lds, st);
+    return hipLaunchKernel(kern, dim3(grid), dim3(kBatThreads), args, lds, st);
 }
 
 }  // namespace sg

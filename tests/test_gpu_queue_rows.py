@@ -62,3 +62,33 @@ def test_queue_items(gpu, rule, uc, runs):
         assert s["schedule_used"] == sg.SCHED_QUEUE
         compare(h, insts, ref)
         h.free()
+
+
+@pytest.mark.parametrize("rule,uc,runs", [(GREEDY, True, [1000]), (TIE, False, [5]), (TIE, True, [2, 4])])
+def test_queue_teams(gpu, rule, uc, runs):
+    """Batches whose largest items outlast the rest run on teams of workgroups:
+    with and without hyper-couplings, start energies pending or read, replicas
+    frozen by an earlier run; and the same batch without teams."""
+    import paper_0912_3912_amd as sg
+    insts = [gen.erdos_renyi_triples(60011, seed=1, restarts=3, instance_id=1),
+             gen.random_regular3(90002, seed=2, restarts=2, instance_id=2)]
+    insts += [gen.erdos_renyi_triples(700 + 37 * i, seed=10 + i, restarts=8, instance_id=10 + i) for i in range(12)]
+    ref = []
+    for i in insts:
+        st = None
+        for r in runs:
+            st, _ = oracle.run(i, seed=3, rule=rule, max_sweeps=r, until_converged=uc, state=st, threads=8)
+        ref.append(st)
+    for wgs, pending in ((0, False), (0, True), (-1, True)):
+        log(f"queue teams: rule={rule} uc={uc} runs={runs} team_wgs={wgs} pending={pending}")
+        h = sg.load_instance(insts)
+        h.tune("team_wgs", wgs)
+        h.bind()
+        h.init_spins(3)
+        if not pending:
+            h.energy()
+        for r in runs:
+            h.run_sweeps(seed=3, rule=rule, max_sweeps=r, until_converged=uc, schedule=sg.SCHED_QUEUE)
+            assert (h.query("last_queue_teams") > 0) == (wgs == 0)
+        compare(h, insts, ref)
+        h.free()
