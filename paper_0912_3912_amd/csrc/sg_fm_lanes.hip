@@ -30,6 +30,16 @@
 // order) are read from device memory; they are shared by all lanes and stay
 // in the caches.
 //
+// Bound by latency and issue at one wavefront per SIMD (at 512 spins a
+// wavefront's LDS takes a quarter of the compute unit's): a move of 64
+// replicas takes about 6900 cycles, a quarter of them vector issue, and 40%
+// waits for the row's load and for the chain of LDS reads.  1024 instances of
+// 512 spins, 256 restarts: 28.6 ms; 30.9 ms with a branch for each unused
+// entry and sign in the half-gains, a loop that cleared the touched keys, and
+// 64-bit energies in the moves.  Two or four wavefronts on one instance (its
+// rows then stay in the L1) take 34 and 38 ms: they end with their slowest
+// replica.
+//
 // The move order that undoes the moves after the best prefix is kept as a
 // tag per spin in the replica's own spin row in device memory (free while
 // the pass runs): tag = step >> sh (sh = 0, 1, 2 for n <= 256, 512, 1024), so
@@ -209,7 +219,8 @@ __global__ __launch_bounds__(256) void k_fm_lanes(const InstTab* __restrict__ ta
             uint32_t sreg[32];
 #pragma unroll
             for (int g = 0; g < 32; ++g) sreg[g] = g < G ? sl[g * 64] : 0u;
-            auto sr = [&](uint32_t wi, uint32_t bi) { return ((sreg[wi] >> bi) & 1u) ? -1 : 1; };
+            // 0 or -1: a spin's sign
+            auto sr = [&](uint32_t wi, uint32_t bi) { return __builtin_amdgcn_sbfe((int)sreg[wi], bi, 1u); };
             for (int g = G; g < Gp; ++g) bl[g * 64] = 0u;
             for (int g = 0; g < G; ++g) {
                 uint32_t best = 0;
@@ -232,25 +243,32 @@ __global__ __launch_bounds__(256) void k_fm_lanes(const InstTab* __restrict__ ta
                     for (int u = 0; u < 4; ++u) {
                         const int e = e0 + u;
                         if (e < n) {
-                            // the row's counts are wavefront-uniform: unused entries are skipped
+                            // the row's counts are wavefront-uniform: unused entries
+                            // are skipped in pairs.  f = (sum of the coefficients, a
+                            // scalar) + 2 (sum of those with a sign, as 0 or -1)
                             const int nc = (hq[u] >> 8) & 0xFF, nt = hq[u] >> 16;
-                            int f = (int)(int8_t)(hq[u] & 0xFF);
+                            int f0 = (int)(int8_t)(hq[u] & 0xFF), f2 = 0;
 #pragma unroll
-                            for (int c = 0; c < DC / 2; ++c) {
-                                const uint32_t wq[2] = {cr[u][c].x, cr[u][c].y};
+                            for (int c = 0; c < DC / 2; ++c)
+                                if (2 * c < nc) {
+                                    const uint32_t wq[2] = {cr[u][c].x, cr[u][c].y};
 #pragma unroll
-                                for (int k = 0; k < 2; ++k)
-                                    if (2 * c + k < nc)
-                                        f += (int)(int8_t)(wq[k] & 0xFFu) * sr(wq[k] >> 27, (wq[k] >> 11) & 31u);
-                            }
+                                    for (int k = 0; k < 2; ++k) {
+                                        const int J = (int)(int8_t)(wq[k] & 0xFFu);
+                                        f0 += J;
+                                        f2 = __mul24(sr(wq[k] >> 27, (wq[k] >> 11) & 31u), J) + f2;
+                                    }
+                                }
 #pragma unroll
-                            for (int c = 0; c < TT; ++c) {
-                                const uint32_t w0 = tr[u][c].x, w1 = tr[u][c].y;
-                                if (c < nt)
-                                    f += (int)(int8_t)(w1 & 0xFFu) * sr(w0 >> 27, (w1 >> 24) & 31u) *
-                                         sr((w0 & 0xFFFFu) >> 11, (w1 >> 16) & 31u);
-                            }
-                            const uint32_t vb = (uint32_t)(128 - sr((uint32_t)e >> 5, (uint32_t)e & 31u) * f);
+                            for (int c = 0; c < TT; ++c)
+                                if (c < nt) {
+                                    const uint32_t w0 = tr[u][c].x, w1 = tr[u][c].y;
+                                    const int K = (int)(int8_t)(w1 & 0xFFu);
+                                    f0 += K;
+                                    f2 = __mul24(sr(w0 >> 27, (w1 >> 24) & 31u) ^ sr((w0 & 0xFFFFu) >> 11, (w1 >> 16) & 31u), K) + f2;
+                                }
+                            const int f = f0 + 2 * f2, me = sr((uint32_t)e >> 5, (uint32_t)e & 31u);
+                            const uint32_t vb = (uint32_t)(128 + me - (f ^ me));  // 128 - s f
                             word |= vb << (8 * u);
                             const uint32_t key = vb << 16 | (0xFFFFu - (uint32_t)(g * 2048 + d * 256 + u));
                             best = key > best ? key : best;
@@ -263,9 +281,9 @@ __global__ __launch_bounds__(256) void k_fm_lanes(const InstTab* __restrict__ ta
         }
 
         // the n moves of the pass; top is the largest group key
-        long long E = Estar, Elow = Estar;
+        int E = 0, Elow = 0;  // half the energy from the pass's start, and its least
         int blen = 0;
-        uint64_t ring = 0, saved = 0;
+        uint32_t ring0 = 0, ring1 = 0, saved0 = 0, saved1 = 0;  // the last four moves, newest lowest
         uint32_t top = 0;
         for (int g0 = 0; g0 < Gp; g0 += 8) {
             uint32_t b[8];
@@ -296,13 +314,14 @@ __global__ __launch_bounds__(256) void k_fm_lanes(const InstTab* __restrict__ ta
             gl8[fe] = 0;                   // locked
             uint32_t* sp = &sl[(fe >> 11) * 64];
             const uint32_t sword = *sp;
-            ring = ring << 16 | (uint32_t)e;
-            E -= 2 * (vb - 128);
-            if (E < Elow) {
-                Elow = E;
-                blen = step + 1;
-                saved = ring;
-            }
+            ring1 = __builtin_amdgcn_alignbit(ring1, ring0, 16);
+            ring0 = ring0 << 16 | (uint32_t)e;
+            E -= vb - 128;
+            const bool low = E < Elow;
+            Elow = low ? E : Elow;
+            blen = low ? step + 1 : blen;
+            saved0 = low ? ring0 : saved0;
+            saved1 = low ? ring1 : saved1;
             // every read of the partners' state issued together (an unused
             // entry names spin e itself, now locked, with coefficient 0: it
             // changes nothing), then every change computed, then written
@@ -351,7 +370,8 @@ __global__ __launch_bounds__(256) void k_fm_lanes(const InstTab* __restrict__ ta
                     const int dv = ((spv[2 * c + k] >> ((w >> 11) & 31u)) & 1u) ? -dj : dj;
                     const uint32_t nb = b ? (uint32_t)((int)b + dv) : 0u;  // a locked partner keeps 0
                     const uint32_t lo = 0xFFFFu - fb;
-                    dirty |= (nb < b && kv[2 * c + k] == (b << 16 | lo)) ? 1u << (fb >> 11) : 0u;
+                    const bool was = kv[2 * c + k] == (b << 16 | lo), falls = nb < b;
+                    dirty |= (uint32_t)(was & falls) << (fb >> 11);
                     gl8[fb] = (uint8_t)nb;
                     atomicMax(&bl[(fb >> 11) * 64], nb << 16 | lo);
                 }
@@ -376,15 +396,16 @@ __global__ __launch_bounds__(256) void k_fm_lanes(const InstTab* __restrict__ ta
                     dirty |= 1u << (fa >> 11) | 1u << (fbb >> 11);
                 }
             }
-            // the next move's key: the touched groups' keys are set aside (zero),
-            // every key is read in the same round trip as the rescan's gain
-            // words, and the rescanned keys join the maximum
-            for (uint32_t z = dirty; z; z &= z - 1u) bl[__builtin_ctz(z) * 64] = 0u;
+            // the next move's key: the touched groups' keys are left out, every
+            // key is read in the same round trip as the rescan's gain words, and
+            // the rescanned keys join the maximum
             top = 0;
             for (int g0 = 0; g0 < Gp; g0 += 8) {
                 uint32_t b[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) b[u] = bl[(g0 + u) * 64];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) b[u] &= ~(uint32_t)__builtin_amdgcn_sbfe((int)dirty, (uint32_t)(g0 + u), 1u);
 #pragma unroll
                 for (int u = 0; u < 8; ++u) top = b[u] > top ? b[u] : top;
             }
@@ -436,14 +457,14 @@ __global__ __launch_bounds__(256) void k_fm_lanes(const InstTab* __restrict__ ta
                 // the moves of the last kept step's block up to that step (tag T) were flipped back above
                 const int c = ((blen - 1) & ((1 << sh) - 1)) + 1;
                 for (int q = 0; q < c; ++q) {
-                    const int e = (int)((saved >> (16 * q)) & 0xFFFFu);
+                    const int e = (int)(((q & 2 ? saved1 : saved0) >> (16 * (q & 1))) & 0xFFFFu);
                     sl[(e >> 5) * 64] ^= 1u << (e & 31);
                 }
             }
             ++pc;
             kept += blen;
-            const bool improved = Elow < Estar;
-            Estar = Elow;
+            const bool improved = Elow < 0;
+            Estar += 2 * (long long)Elow;
             const bool conv = until_conv && !improved;
             if (conv || pc >= max_passes) {
                 for (int i0 = 0; i0 < n; i0 += 4) {
