@@ -2455,11 +2455,15 @@ sg_status run_block_schedule(sg_handle H, const sg_run_params* p, const std::vec
 // Teams for the first items of the sorted queue, listed per workgroup in
 // h_qteams; returns the bytes of words they take.  A workgroup runs an item
 // of n spins in about n + 3000 units of time (11 ns) and a team of g in
-// 1.28 n / g + 30000 (bits instead of bytes; an exchange every phase): 100000
+// 1.28 n / g + 25000 (bits instead of bytes; an exchange every phase): 100000
 // spins with triples take 1121 us alone, 742, 527 and 426 us in teams of 2, 4
 // and 8.  With the first k items in teams that end with the largest of the
-// others, the call takes that long or the mean load of the workgroups; k
-// minimises it, if it saves a twelfth.
+// others, the call takes that long, or the mean load of the workgroups and
+// three tenths for what an uneven queue leaves idle; k minimises it, if it
+// saves a twelfth.  Kernel times without teams / with: 96 graphs up to 100000
+// spins, 8 restarts 1076 / 985 us (32 items in teams); 82 graphs up to 81550,
+// one restart 762 / 504 us (10); 38 graphs up to 83236, 8 restarts, 20 sweeps
+// under TIE 1891 / 1214 us (24).
 uint64_t queue_teams(sg_handle H, const sg_run_params* p, int n_big, int grid, size_t lds, sg::QueueTeams& teams)
 {
     if (H->team_wgs < 0 || !H->qteam_bytes || p->max_sweeps <= 0 || n_big < 1 || grid < 64 || H->queue_grid > 0) return 0;
@@ -2468,27 +2472,27 @@ uint64_t queue_teams(sg_handle H, const sg_run_params* p, int n_big, int grid, s
     if (!queue_team_fits(inst(0))) return 0;
     double rest = 0;  // load of the items not in teams
     for (const sg::QueueItem& it : H->h_qitems) rest += H->insts[(size_t)it.inst].n;
-    const int most = std::min(grid * 3 / 4, kQueueTeamWgs);
+    const int most = std::min(grid * 9 / 10, kQueueTeamWgs);
     const double base = std::max(alone(0), rest / grid);
     double best = base * 11 / 12;
     int best_k = 0;
     uint64_t bytes = 0, best_bytes = 0;
-    auto size = [&](int i, double end) { return std::max(2, (int)std::ceil(1.28 * inst(i).n / (end - 30000.0))); };
+    auto size = [&](int i, double end) { return std::max(2, (int)std::ceil(1.28 * inst(i).n / (end - 25000.0))); };
     for (int k = 1; k <= kQueueTeams && k < n_big; ++k) {
         if (!queue_team_fits(inst(k - 1))) break;
         bytes += queue_team_bytes(inst(k - 1));
         if (bytes > H->qteam_bytes) break;
         rest -= inst(k - 1).n;
-        const double end = std::max(alone(k), 50000.0);
+        const double end = std::max(alone(k), 40000.0);
         int wgs = 0;
         double load = rest;
         for (int i = 0; i < k; ++i) {
             const int g = size(i, end);
             wgs += g;
-            load += 1.28 * inst(i).n + 30000.0 * g;
+            load += 1.28 * inst(i).n + 25000.0 * g;
         }
         if (wgs > most) break;
-        const double t = std::max(end, 1.1 * load / grid);
+        const double t = std::max(end, 1.3 * load / grid);
         if (t < best) {
             best = t;
             best_k = k;
@@ -2497,7 +2501,7 @@ uint64_t queue_teams(sg_handle H, const sg_run_params* p, int n_big, int grid, s
     }
     if (!best_k || grid > sg::queue_max_blocks(lds)) return 0;
     H->h_qteams.clear();
-    const double end = std::max(alone(best_k), 50000.0);
+    const double end = std::max(alone(best_k), 40000.0);
     uint32_t at = 0;
     for (int i = 0; i < best_k; ++i) {
         const int g = size(i, end);
