@@ -401,7 +401,7 @@ def run_chimera_fm(args, sg, gen, torch, count=4096):
                          "avg_launch_us": round(hot_us, 1), "ops_per_attempt": round(ops, 2),
                          "attempt": "one move of a pass",
                          "note": "one replica per lane: each move is a serial chain of LDS round trips and "
-                                 "one row load; the lane kernel issues about 600 instructions per wavefront "
+                                 "one row load; the lane kernel issues about 700 instructions per wavefront "
                                  "step, so the algorithmic integer rate stays a small fraction of the VALU peak"},
             "cpu_baseline": cpu}
 

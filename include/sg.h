@@ -418,9 +418,9 @@ sg_status sg_solve(sg_handle h, const sg_run_params* p, sg_run_stats* stats, int
  *   "fm_waves"           most wavefronts per SG_RULE_FM workgroup (0 = 16);
  *                        among the sizes that fit LDS the one with the most
  *                        wavefronts resident per compute unit is used
- *   "fm_key32"           1: SG_RULE_FM picks moves on 32-bit keys when every
- *                        gain is below 2^19 in magnitude; 0: 64-bit keys
- *                        (default 1)
+ *   "fm_key32"           1: SG_RULE_FM picks moves on 32-bit keys where they
+ *                        hold every gain; 0: 64-bit keys, and no row tables in
+ *                        LDS (default 1)
  *   "fm_slots"           replicas of instances beyond 4096 spins that
  *                        SG_RULE_FM runs at once (0 = none: such instances
  *                        are rejected); sizes the workspace (before sg_bind)
@@ -453,7 +453,9 @@ sg_status sg_solve(sg_handle h, const sg_run_params* p, sg_run_stats* stats, int
  *                        one launch (at most 64 restarts, 1.2 million spins,
  *                        64 colours, packed form): 0 chosen by size, 1..256,
  *                        -1 per-phase launches as under SG_SCHED_PHASE itself
- *                        (default 0; stats report SG_SCHED_PHASE either way)
+ *                        (default 0; stats report SG_SCHED_PHASE either way).
+ *                        -1 also keeps the queue schedule from running its
+ *                        largest items on several workgroups
  *   "graph_sweeps"       sweeps per captured HIP graph of SG_SCHED_GRAPH
  *                        (1..1024, default 32)
  *   "auto_graph"         1: SG_SCHED_AUTO records the per-phase launches of the
@@ -490,8 +492,10 @@ sg_status sg_tune(sg_handle h, const char* key, int64_t value);
  * replicas run one per lane), "last_fm_lane_nr" (its restarts per lane-kernel
  * wavefront), "last_fm_big" (its replicas on the kernel for instances beyond
  * 4096 spins), "energy_pending" (1 while start energies
- * left out by sg_init_spins are not yet computed), "last_queue_grid", "last_team" (workgroups per replica of the last such
- * launch of the last call, 0 for none),
+ * left out by sg_init_spins are not yet computed), "last_queue_grid",
+ * "last_queue_teams" (queue items the last call ran on several workgroups),
+ * "last_team" (workgroups per replica of the last such launch of the last
+ * call, 0 for none),
  * "total_replicas", "queue_ok" (1 when every instance can join sg_run_group),
  * "wide_instances" (instances stored in the wide form: a
  * coefficient beyond int8, a spin with |h|+sum|J|+sum|K| >= 2^23 or more than

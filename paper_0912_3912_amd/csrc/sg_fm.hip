@@ -1,5 +1,8 @@
 // sg_fm.hip -- the paper's pass-based local search with hill-climbing
-// (Sec. IV, Fig. 3), one wavefront per replica.
+// (Sec. IV, Fig. 3), one wavefront per replica: the instances of at most 4096
+// spins whose term rows do not fit LDS (the others: sg_fm_rows.hip and, one
+// replica per lane, sg_fm_lanes.hip), those beside them in a launch where one
+// launch is the faster, and 64-bit keys when asked for.
 //
 // A pass starts from the replica's state SP* and its tracked energy.  All
 // gains g_i = -dE_i = -2 s_i f_i are evaluated; then, n times, the unlocked
