@@ -1,8 +1,8 @@
 // sg_fm_big.hip -- the paper's pass-based local search with hill-climbing
 // (Sec. IV, Fig. 3) on instances of more than 4096 spins whose half-gains do
-// not fit LDS, or with many replicas at once (the others: sg_fm_mid.hip): one wavefront per replica, the replica's state in device
-// memory, and the unlocked spin of largest gain found through two levels of
-// maxima.  The pass, its tie-break, best prefix, stopping rule and counters
+// not fit LDS, or with many replicas at once (the others: sg_fm_mid.hip): one
+// wavefront per replica, the replica's state in device memory, and the
+// unlocked spin of largest gain found through two levels of maxima.  The pass, its tie-break, best prefix, stopping rule and counters
 // are those of the other pass kernels (sg_fm.hip).
 //
 // Everything here is in external order, so that the largest key names its

@@ -15,8 +15,8 @@ pytestmark = pytest.mark.gpu
 GREEDY, TIE = 0, 1
 SCHED_LATTICE = 3
 
-DIMS = [(4, 4), (8, 16), (16, 18), (32, 64), (46, 46), (64, 64), (64, 66), (64, 128), (92, 92), (4, 6, 8), (12, 14, 16),
-        (16, 16, 16), (20, 20, 20), (22, 22, 18)]
+DIMS = [(4, 4), (8, 16), (16, 18), (32, 64), (46, 46), (64, 64), (64, 66), (64, 128), (92, 92), (94, 130), (4, 6, 8), (12, 14, 16),
+        (16, 16, 16), (20, 20, 20), (22, 22, 18), (6, 100, 130), (130, 64)]
 
 
 def _inst(dims, jm, hm):
