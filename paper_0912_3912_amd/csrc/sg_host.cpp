@@ -139,6 +139,7 @@ struct HostInst {
     uint64_t off_nbr = 0, off_ta = 0, off_tb = 0, off_h = 0, off_ext = 0, off_slices = 0, off_eterm = 0;
     uint64_t off_spins = 0, spin_stride = 0, off_acc = 0;
     uint64_t off_team = UINT64_MAX;             // exchange words of the team kernel, or none
+    mutable int32_t team_most[2] = {-1, -1};    // its co-resident workgroups per rule, once asked for
     uint64_t off_fields = 0, field_stride = 0;  // maintained local fields (ints per replica), when enabled
     // wide form (values or sizes beyond the packed words, sg_layout.h)
     int32_t wide = 0;
@@ -251,7 +252,7 @@ struct sg_ctx {
     std::vector<uint8_t> started;
     // Start energies left out by sg_init_spins: e_deferred marks the instances
     // (1: lane start, the bit-sliced kernel writes the energies; 2: unit start,
-    // the queue kernel writes them at convergence), e_pending is set until a
+    // the queue or team kernel writes them at convergence), e_pending is set until a
     // run has written them or an energy pass has computed them.
     std::vector<uint8_t> e_deferred;
     bool e_pending = false;
@@ -1742,6 +1743,7 @@ void layout(sg_ctx* H)
         uint64_t need = 0;
         for (HostInst& q : H->insts) {
             q.off_team = UINT64_MAX;
+            q.team_most[0] = q.team_most[1] = -1;
             if (team_words(H, q)) need += align_up((uint64_t)q.R * q.slices.size() * 32);
         }
         if (off > SG_NOALLOC_MAX_BYTES || off + need <= SG_NOALLOC_MAX_BYTES)
@@ -1879,7 +1881,8 @@ int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
     const int ns = team_slices(q);
     int g = H->team_wgs > 0 ? std::min(H->team_wgs, ns) : ns > kTeamSplit ? (ns + 11) / 12 : 1;
     if (g > 1) {
-        const int most = sg::team_max_blocks(q.n, p->rule == SG_RULE_GREEDY_TIE, q.t > 0, q.max_ew);
+        int32_t& most = q.team_most[p->rule == SG_RULE_GREEDY_TIE];
+        if (most < 0) most = sg::team_max_blocks(q.n, p->rule == SG_RULE_GREEDY_TIE, q.t > 0, q.max_ew);
         g = q.off_team == UINT64_MAX ? 1 : std::min(g, most / q.R);
     }
     if (g >= 2 || ns <= kTeamAlone || H->team_wgs > 0) return std::max(g, 1);
@@ -1914,7 +1917,9 @@ sg_status run_team(sg_handle H, const sg_run_params* p, const std::vector<int>& 
                "team kernel");
         ++H->hot_launches;
         H->last_team = G;
-        SG_HIP(sg::launch_end(rs, q.R, acc, q.acc_slots, p->max_sweeps, p->until_converged, q.n, cs, st), "end kernel");
+        SG_HIP(sg::launch_end(rs, q.R, acc, q.acc_slots, p->max_sweeps, p->until_converged, q.n, cs, st,
+                              p->until_converged ? 2 : 0),
+               "end kernel");
     }
     SG_HIP(hipEventRecord(H->evh1, st), "event record");
     return SG_OK;
@@ -2268,7 +2273,7 @@ sg_status run_lattice_schedule(sg_handle H, const sg_run_params* p, const std::v
                 H->last_model_phases = msc ? (int64_t)phases : 0;
             }
         }
-        SG_HIP(sg::launch_end(rs, q.R, acc, q.acc_slots, T_done, p->until_converged, q.n, cs, st, absolute),
+        SG_HIP(sg::launch_end(rs, q.R, acc, q.acc_slots, T_done, p->until_converged, q.n, cs, st, absolute ? 1 : 0),
                "end kernel");
     }
     return SG_OK;
@@ -3069,9 +3074,9 @@ sg_status sg_internal_validate(const sg_instance_desc* d) { return validate(*d, 
 // A drawn start leaves its energy out when the kernel that SG_SCHED_AUTO
 // would run next computes the energies of the final spins itself: the
 // bit-sliced block kernel for lane-started instances (always), for the
-// others the queue kernel (at convergence) or the bit-plane lattice tile
-// kernel (taken only when every unit-started instance would run on one of
-// these two).  A wrong guess costs an energy pass, never a wrong energy.
+// others the queue or team kernel (at convergence) or the bit-plane lattice
+// tile kernel (taken only when every unit-started instance would run on one of
+// these).  A wrong guess costs an energy pass, never a wrong energy.
 bool defer_lane_energy(const sg_ctx* H, const HostInst& q)
 {
     return H->defer_energy && H->block_bits && q.bits_ok && !q.lat_ok && q.R >= H->block_min_restarts &&
@@ -3085,6 +3090,19 @@ bool lattice_msc_bound(const sg_ctx* H, const HostInst& q)
     return q.lat_ok && q.lat_msc && H->lattice_msc && !lattice_wg_fits(H, q);
 }
 
+// SG_SCHED_AUTO would run this instance, unless the queue schedule takes it, on
+// the team kernel, which writes a converged replica's energy.
+bool team_bound(const sg_ctx* H, const HostInst& q)
+{
+    sg_run_params p{};
+    p.rule = SG_RULE_GREEDY;
+    p.max_sweeps = 1;
+    p.until_converged = 1;
+    p.schedule = SG_SCHED_AUTO;
+    return !H->fields_ws && !H->auto_graph && !can_lattice(H, q, &p) &&
+           !(q.R >= H->block_min_restarts && can_block(H, q)) && team_groups(H, q, &p) > 0;
+}
+
 bool defer_unit_energy(const sg_ctx* H)
 {
     if (!H->defer_energy || H->h_esegs.empty()) return false;
@@ -3095,7 +3113,7 @@ bool defer_unit_energy(const sg_ctx* H)
         if (q.dense || (H->lanes_on && lane_start_candidate(q))) continue;
         const bool queue = !q.lat_ok && !(q.R >= H->block_min_restarts && can_block(H, q)) && can_queue(q) &&
                            queue_items >= H->queue_min_items;
-        if (!queue && !lattice_msc_bound(H, q)) return false;
+        if (!queue && !lattice_msc_bound(H, q) && !team_bound(H, q)) return false;
     }
     return true;
 }
@@ -3105,6 +3123,7 @@ bool run_writes_energy(const sg_ctx* H, const sg_run_params* p, int kind, int sc
 {
     if (kind == 1) return sched == SG_SCHED_BLOCK && bits_path(H, p, q);
     if (sched == SG_SCHED_LATTICE) return lattice_msc_bound(H, q) && !p->until_converged && p->max_sweeps > 0;
+    if (sched == SG_SCHED_PHASE) return p->until_converged && team_groups(H, q, p) > 0;
     return sched == SG_SCHED_QUEUE && p->until_converged && p->max_sweeps > 0;
 }
 
@@ -3554,7 +3573,7 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
     if (sched < 0 && p->schedule != SG_SCHED_AUTO)
         return fail(SG_EINVAL, "schedule %d is not available for this handle (rule %d, until_converged %d)",
                     p->schedule, p->rule, p->until_converged);
-    // left-out start energies are written by the bit-sliced or the queue
+    // left-out start energies are written by the bit-sliced, queue or team
     // kernel; any other kernel continues from them, so they are computed first
     for (size_t k = 0; H->e_pending && k < assign.size(); ++k)
         if (H->e_deferred[k] && !run_writes_energy(H, p, H->e_deferred[k], assign[k], H->insts[k]))
@@ -3601,13 +3620,13 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
         return fail(SG_EDEVICE, "lattice tile or team kernel: a neighbour wait timed out (replica state is undefined; "
                                 "start again with sg_init_spins)");
     if (H->e_pending) {
-        // the queue kernel wrote the energies of the replicas that converged,
-        // the bit-plane lattice kernel those of its instances; if any replica
+        // the queue and team kernels wrote the energies of the replicas that
+        // converged, the bit-plane lattice kernel those of its instances; if any replica
         // is left without, all are computed from their final spins
         bool missing = false;
         for (size_t k = 0; k < H->e_deferred.size(); ++k) {
             if (H->e_deferred[k] != 2) continue;
-            if (assign[k] == SG_SCHED_QUEUE) missing = missing || cs.unconverged != 0;
+            if (assign[k] == SG_SCHED_QUEUE || assign[k] == SG_SCHED_PHASE) missing = missing || cs.unconverged != 0;
             else missing = missing || !H->e_written[k];
         }
         if (missing) {

@@ -329,7 +329,10 @@ __global__ void k_end(RepState* __restrict__ rs, const int64_t* __restrict__ acc
             performed = T;
         }
     }
-    if (!absolute) st->E += td;
+    // absolute: 0 a change; 1 the energy; 2 a change, or -6 times the energy of a
+    // replica that converges in this call
+    if (absolute == 2 && !frozen && conv) st->E = -td / 6;
+    else if (absolute != 1) st->E += td;
     else if (!frozen) st->E = td;
     st->flips += tf;
     st->sweeps += performed;
@@ -535,11 +538,11 @@ hipError_t launch_bump(int32_t* t_base, int d, hipStream_t st)
 }
 
 hipError_t launch_end(RepState* rs, int R, const int64_t* acc, int nslots, int T, int until_conv, int64_t n,
-                      CallStats* cs, hipStream_t st, bool absolute)
+                      CallStats* cs, hipStream_t st, int absolute)
 {
     const unsigned threads = nslots <= 64 ? 64 : 256;
     hipLaunchKernelGGL(k_end, dim3(R), dim3(threads), 0, st, rs, acc, nslots, T, until_conv, n, cs,
-                       absolute ? 1 : 0);
+                       absolute);
     return hipGetLastError();
 }
 

@@ -24,10 +24,11 @@ hipError_t launch_phase(const InstDev& I, int8_t* spins, int64_t stride, RepStat
 hipError_t launch_fields(const InstDev& I, const int8_t* spins, int64_t stride, int R, int32_t* fields, int64_t fstride,
                          hipStream_t st);
 hipError_t launch_bump(int32_t* t_base, int d, hipStream_t st);
-// Fold a call's per-slot accumulators into the replicas (absolute: the slots
-// hold shares of the final energy instead of energy changes).
+// Fold a call's per-slot accumulators into the replicas.  absolute: the slots
+// hold 0 energy changes, 1 shares of the final energy, 2 energy changes, or for
+// a replica that converges in the call shares of -6 times its final energy.
 hipError_t launch_end(RepState* rs, int R, const int64_t* acc, int nslots, int T, int until_conv, int64_t n,
-                      CallStats* cs, hipStream_t st, bool absolute = false);
+                      CallStats* cs, hipStream_t st, int absolute = 0);
 hipError_t launch_any_active(const RepState* rs, int R, int T, uint32_t* flag, hipStream_t st);
 // Word 0 of Philox4x32-10 of count counters (4 uint32 each) under key seed.
 hipError_t launch_philox_word0(const uint32_t* ctr, uint32_t* out, int64_t count, uint64_t seed, hipStream_t st);

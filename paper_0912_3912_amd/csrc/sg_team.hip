@@ -21,15 +21,17 @@ namespace sg {
 // Grid: R teams of G workgroups (workgroup r G + m: member m of replica r's).
 // ct: the C + 1 slice offsets of the colours.  words: per replica two copies of
 // two words per slice, tags zero on entry.  acc slots (nslots per replica, zero
-// on entry) take the energy changes and flips, rs[r].lastflip 1 + the last
+// on entry) take the energy changes (of a replica that converged, -6 times its
+// energy) and flips, rs[r].lastflip 1 + the last
 // sweep that flipped.  Dynamic LDS: the spins, then from word tl_off on a
 // TeamLds.
-template <bool BYTES, bool TIE, bool TRI, int W>
+// CONV: run until converged.
+template <bool BYTES, bool TIE, bool TRI, int W, bool CONV>
 __global__ __launch_bounds__(kTeamThreads) void k_team(const InstDev I, const int32_t* __restrict__ ct, int C,
                                                        int8_t* __restrict__ spins, int64_t stride,
                                                        RepState* __restrict__ rs, int G, int64_t* __restrict__ acc,
                                                        int nslots, uint64_t* __restrict__ words,
-                                                       uint32_t* __restrict__ err, int T, uint64_t seed, int until_conv,
+                                                       uint32_t* __restrict__ err, int T, uint64_t seed,
                                                        uint32_t tl_off)
 {
     extern __shared__ __align__(16) uint32_t bits[];
@@ -39,10 +41,12 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(const InstDev I, const in
     RepState* st = rs + r;
     if (st->converged) return;  // the same for the whole team
     const TeamArgs A{I,   ct,  C, G,          m,    r,    spins + stride * r, words + (size_t)r * I.nslices * 4,
-                     err, (uint32_t)st->sweeps, T, until_conv, seed, &tl};
-    const TeamOut o = team_run<BYTES, TIE, TRI, false, W>(A);
+                     err, (uint32_t)st->sweeps, T, CONV, seed, &tl};
+    const TeamOut o = team_run<BYTES, TIE, TRI, CONV, W>(A);
     if (o.dead) return;
-    const long long wd = team_wave_sum(o.dE);
+    // a sweep without a flip evaluates every spin on the final configuration:
+    // its fields give the energy itself, which k_end takes in place of the change
+    const long long wd = team_wave_sum(CONV && o.lastflip < o.performed ? o.e6 : o.dE);
     if ((threadIdx.x & 63) == 0) {
         int64_t* a = acc + 2 * ((int64_t)r * nslots + m % nslots);
         if (wd) atomicAdd((unsigned long long*)a, (unsigned long long)wd);
@@ -57,16 +61,17 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(const InstDev I, const in
 // graph, 16 sweeps under TIE: 141 us as bits, 106 as bytes).
 constexpr int kTeamByteN = 150000;
 static bool team_bytes(int n, int G) { return G == 1 && n <= kTeamByteN; }
-template <bool BYTES>
+template <bool BYTES, bool CONV>
 static const void* team_variant(bool tie, bool tri, int ew)
 {
-    if (tri) return tie ? (const void*)k_team<BYTES, true, true, kTeamW> : (const void*)k_team<BYTES, false, true, kTeamW>;
-    if (ew <= 4) return tie ? (const void*)k_team<BYTES, true, false, 4> : (const void*)k_team<BYTES, false, false, 4>;
-    return tie ? (const void*)k_team<BYTES, true, false, kTeamW> : (const void*)k_team<BYTES, false, false, kTeamW>;
+    if (tri) return tie ? (const void*)k_team<BYTES, true, true, kTeamW, CONV> : (const void*)k_team<BYTES, false, true, kTeamW, CONV>;
+    if (ew <= 4) return tie ? (const void*)k_team<BYTES, true, false, 4, CONV> : (const void*)k_team<BYTES, false, false, 4, CONV>;
+    return tie ? (const void*)k_team<BYTES, true, false, kTeamW, CONV> : (const void*)k_team<BYTES, false, false, kTeamW, CONV>;
 }
-static const void* team_kernel(bool bytes, bool tie, bool tri, int ew)
+static const void* team_kernel(bool bytes, bool conv, bool tie, bool tri, int ew)
 {
-    return bytes ? team_variant<true>(tie, tri, ew) : team_variant<false>(tie, tri, ew);
+    if (conv) return bytes ? team_variant<true, true>(tie, tri, ew) : team_variant<false, true>(tie, tri, ew);
+    return bytes ? team_variant<true, false>(tie, tri, ew) : team_variant<false, false>(tie, tri, ew);
 }
 
 static size_t team_bits(int n) { return (((size_t)(n + 31) / 32 + 1) * 4 + 15) / 16 * 16; }
@@ -77,7 +82,7 @@ bool team_fits(int n, int C) { return team_bits(n) <= 150 * 1024 && C >= 1 && C 
 
 int team_max_blocks(int n, bool tie, bool tri, int ew)
 {
-    const void* kern = team_kernel(false, tie, tri, ew);
+    const void* kern = team_kernel(false, true, tie, tri, ew);  // (the one with more registers)
     const size_t lds = team_bits(n) + sizeof(TeamLds);
     int per_cu = 0, dev = 0, cus = 0;
     if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
@@ -96,11 +101,11 @@ hipError_t launch_team(const InstDev& I, int ew, const int32_t* ct, int C, int8_
 {
     if (R <= 0 || T <= 0) return hipSuccess;
     if (G < 1 || !team_fits(I.n, C) || (G > 1 && !words)) return hipErrorInvalidValue;
-    const void* kern = team_kernel(team_bytes(I.n, G), rule == 1, I.has_tri != 0, ew);
+    const void* kern = team_kernel(team_bytes(I.n, G), until_conv != 0, rule == 1, I.has_tri != 0, ew);
     const size_t lds = team_spins(I.n, G) + sizeof(TeamLds);
     static const bool free0 = [] {
         bool ok = true;
-        for (int v = 0; v < 12; ++v) ok = ok && team_lds_free(team_kernel(v >= 6, v & 1, v % 6 >= 4, v & 2 ? 4 : kTeamW));
+        for (int v = 0; v < 32; ++v) ok = ok && team_lds_free(team_kernel(v & 16, v & 8, v & 1, v & 4, v & 2 ? 4 : kTeamW));
         return ok;
     }();
     if (!free0) return hipErrorInvalidDeviceFunction;
@@ -108,7 +113,7 @@ hipError_t launch_team(const InstDev& I, int ew, const int32_t* ct, int C, int8_
     if (e != hipSuccess) return e;
     InstDev a0 = I;
     uint32_t tl_off = (uint32_t)(team_spins(I.n, G) / 4);
-    void* args[] = {&a0, &ct, &C, &spins, &stride, &rs, &G, &acc, &nslots, &words, &err, &T, &seed, &until_conv, &tl_off};
+    void* args[] = {&a0, &ct, &C, &spins, &stride, &rs, &G, &acc, &nslots, &words, &err, &T, &seed, &tl_off};
     // members wait for each other: the cooperative launch has them all resident
     if (G > 1) return hipLaunchCooperativeKernel(kern, dim3((unsigned)(R * G)), dim3(kTeamThreads), args, (unsigned)lds, st);
     return hipLaunchKernel(kern, dim3((unsigned)R), dim3(kTeamThreads), args, lds, st);

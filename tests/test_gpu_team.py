@@ -115,3 +115,27 @@ def test_split_replicas(gpu, name, rule, uc, runs):
         assert h.query("last_team") >= (2 if name == "triples" else 1)
         compare(h, [inst], [st])
         h.free()
+
+
+@pytest.mark.parametrize("first", ["run", "capped", "fixed", "phase", "energy", "best"])
+def test_start_energies_left_out(gpu, first):
+    """The start energies that the team kernel makes unnecessary, read or needed
+    in every other way first: a run that converges, one that the sweep cap ends,
+    a fixed number of sweeps, per-phase launches, and the readers."""
+    import paper_0912_3912_amd as sg
+    inst = gen.erdos_renyi_triples(6001, seed=9, restarts=2)
+    log(f"start energies left out: {first}")
+    h = sg.load_instance([inst]).bind()
+    h.init_spins(3)
+    assert h.query("energy_pending") == 1
+    n, uc = {"run": (1000, True), "capped": (2, True), "fixed": (3, False)}.get(first, (1000, True))
+    if first == "energy":
+        assert np.array_equal(h.energy(), h.energy(recompute=True))
+    elif first == "best":
+        E, _ = h.best()
+        assert E[0] == h.energy(recompute=True).min()
+    h.run_sweeps(seed=3, rule=GREEDY, max_sweeps=n, until_converged=uc,
+                 schedule=sg.SCHED_PHASE if first == "phase" else sg.SCHED_AUTO)
+    assert h.query("energy_pending") == 0
+    compare(h, [inst], [oracle.run(inst, seed=3, rule=GREEDY, max_sweeps=n, until_converged=uc, threads=8)[0]])
+    h.free()
