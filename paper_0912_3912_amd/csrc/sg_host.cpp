@@ -3091,7 +3091,8 @@ bool lattice_msc_bound(const sg_ctx* H, const HostInst& q)
 }
 
 // SG_SCHED_AUTO would run this instance, unless the queue schedule takes it, on
-// the team kernel, which writes a converged replica's energy.
+// the team kernel, which writes a converged replica's energy.  (Lattices are
+// left out: a fixed number of sweeps runs on the tile kernels.)
 bool team_bound(const sg_ctx* H, const HostInst& q)
 {
     sg_run_params p{};
@@ -3099,8 +3100,8 @@ bool team_bound(const sg_ctx* H, const HostInst& q)
     p.max_sweeps = 1;
     p.until_converged = 1;
     p.schedule = SG_SCHED_AUTO;
-    return !H->fields_ws && !H->auto_graph && !can_lattice(H, q, &p) &&
-           !(q.R >= H->block_min_restarts && can_block(H, q)) && team_groups(H, q, &p) > 0;
+    return !q.lat_ok && !H->fields_ws && !H->auto_graph && !(q.R >= H->block_min_restarts && can_block(H, q)) &&
+           team_groups(H, q, &p) > 0;
 }
 
 bool defer_unit_energy(const sg_ctx* H)
