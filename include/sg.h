@@ -455,7 +455,21 @@ sg_status sg_solve(sg_handle h, const sg_run_params* p, sg_run_stats* stats, int
  *                        -1 per-phase launches as under SG_SCHED_PHASE itself
  *                        (default 0; stats report SG_SCHED_PHASE either way).
  *                        -1 also keeps the queue schedule from running its
- *                        largest items on several workgroups
+ *                        largest items on several workgroups.  The workgroups
+ *                        of one replica wait for one another, so they have to
+ *                        be on the device together.  Within a process the
+ *                        runtime runs such launches one after another; while
+ *                        another process on the device makes them it refuses
+ *                        them, and beside kernels that hold the compute units
+ *                        for seconds their waits give up ("team_polls"): the
+ *                        call then runs without them, with the same results,
+ *                        and -1 spares it the attempt
+ *   "team_polls"         looks (about a microsecond each) after which a wait
+ *                        between the workgroups of a replica gives up; the
+ *                        call then runs the replicas concerned again without
+ *                        such waits, from where they stood before it, with the
+ *                        same results (1..2^30, default 2^22; 0: as if
+ *                        every such launch were refused)
  *   "graph_sweeps"       sweeps per captured HIP graph of SG_SCHED_GRAPH
  *                        (1..1024, default 32)
  *   "auto_graph"         1: SG_SCHED_AUTO records the per-phase launches of the
@@ -495,7 +509,8 @@ sg_status sg_tune(sg_handle h, const char* key, int64_t value);
  * left out by sg_init_spins are not yet computed), "last_queue_grid",
  * "last_queue_teams" (queue items the last call ran on several workgroups),
  * "last_team" (workgroups per replica of the last such launch of the last
- * call, 0 for none),
+ * call, 0 for none), "last_team_reruns" (replicas that call ran again because
+ * a wait gave up),
  * "total_replicas", "queue_ok" (1 when every instance can join sg_run_group),
  * "wide_instances" (instances stored in the wide form: a
  * coefficient beyond int8, a spin with |h|+sum|J|+sum|K| >= 2^23 or more than

@@ -138,7 +138,7 @@ struct HostInst {
     // workspace offsets (bytes)
     uint64_t off_nbr = 0, off_ta = 0, off_tb = 0, off_h = 0, off_ext = 0, off_slices = 0, off_eterm = 0;
     uint64_t off_spins = 0, spin_stride = 0, off_acc = 0;
-    uint64_t off_team = UINT64_MAX;             // exchange words of the team kernel, or none
+    uint64_t off_team = UINT64_MAX;             // the team kernel's share of the workspace (TeamShare), or none
     mutable int32_t team_most[2] = {-1, -1};    // its co-resident workgroups per rule, once asked for
     uint64_t off_fields = 0, field_stride = 0;  // maintained local fields (ints per replica), when enabled
     // wide form (values or sizes beyond the packed words, sg_layout.h)
@@ -207,7 +207,9 @@ struct sg_ctx {
     int32_t queue_min_items = 32;      // AUTO uses the queue schedule from this many items
     int32_t graph_sweeps = 32;         // sweeps per captured graph (SG_SCHED_GRAPH)
     int32_t team_wgs = 0;              // workgroups per replica of the team kernel (0 = chosen, -1 = not used)
+    int32_t team_polls = 1 << 22;      // looks of a team's wait before it gives up (0: no such launch is made)
     int32_t last_team = 0;             // what the last call's last team launch used (0: none)
+    int32_t last_team_reruns = 0;      // replicas the last call ran again because their team gave up
     int32_t auto_graph = 0;            // SG_SCHED_AUTO records per-phase launches in graphs (SG_SCHED_GRAPH)
     int32_t conv_chunk = kConvChunk;   // sweeps per bit-plane launch under the stopping rule
     int32_t lattice_msc = 1;           // use the bit-plane tile kernel where it applies
@@ -257,7 +259,10 @@ struct sg_ctx {
     std::vector<uint8_t> e_deferred;
     bool e_pending = false;
     std::vector<uint8_t> e_written;  // this call's kernels wrote the final energies of the instance
-    bool lat_err_check = false;  // the current call launched tile kernels: read their error flag at its end
+    // the current call launched kernels whose workgroups wait for one another:
+    // read their error flags at its end (words of off_err: lattice tiles,
+    // teams, the queue schedule's teams)
+    bool err_check = false;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     hipEvent_t evh0 = nullptr, evh1 = nullptr;  // around the hot kernel(s) of the last schedule run
     // pinned host memory for the small results a call reads back (sg_bind;
@@ -1514,6 +1519,16 @@ int team_slices(const HostInst& q)
 constexpr int32_t kTeamMaxR = 64;
 constexpr int32_t kTeamSplit = 80;   // slices of a colour beyond which a replica is split over workgroups
 constexpr int32_t kTeamAlone = 128;  // and up to which one workgroup beats per-phase launches
+// Workspace of the teams of one instance, bytes from q.off_team: the error word
+// of their waits (64 bytes), four exchange words per slice and replica, and the
+// replicas' starts.
+struct TeamShare {
+    uint64_t save, bytes;
+    explicit TeamShare(const HostInst& q)
+        : save(64 + (uint64_t)q.R * q.slices.size() * 32), bytes(save + (uint64_t)q.R * sg::team_save_words(q.n) * 2)
+    {
+    }
+};
 bool can_team(const HostInst& q) { return !q.wide && !q.dense && sg::team_fits(q.n, q.C); }
 bool team_words(const sg_ctx* H, const HostInst& q)
 {
@@ -1529,7 +1544,7 @@ bool queue_team_fits(const HostInst& q)
 {
     return can_team(q) && !q.lat_ok && q.n >= kQueueTeamMinN && q.n <= kQueueMaxN && team_slices(q) > kTeamSplit;
 }
-uint64_t queue_team_bytes(const HostInst& q) { return 32 * (1 + (uint64_t)q.slices.size()); }
+uint64_t queue_team_bytes(const HostInst& q) { return sg::queue_team_bytes(q.n, q.slices.size()); }
 
 // Energy tables (sg_dense.hip) for the pass-based search of a dense handle:
 // instances of at most kDenseTableMaxN spins share room for up to 32 MiB of
@@ -1744,11 +1759,11 @@ void layout(sg_ctx* H)
         for (HostInst& q : H->insts) {
             q.off_team = UINT64_MAX;
             q.team_most[0] = q.team_most[1] = -1;
-            if (team_words(H, q)) need += align_up((uint64_t)q.R * q.slices.size() * 32);
+            if (team_words(H, q)) need += align_up(TeamShare(q).bytes);
         }
         if (off > SG_NOALLOC_MAX_BYTES || off + need <= SG_NOALLOC_MAX_BYTES)
             for (HostInst& q : H->insts)
-                if (team_words(H, q)) q.off_team = take((uint64_t)q.R * q.slices.size() * 32);
+                if (team_words(H, q)) q.off_team = take(TeamShare(q).bytes);
     }
     // and of the queue schedule's teams
     {
@@ -1889,13 +1904,21 @@ int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
     return 0;  // large and not split: the per-phase launches use the whole device
 }
 
-sg_status run_team(sg_handle H, const sg_run_params* p, const std::vector<int>& which)
+// The call's error flags, cleared by its first launch that needs them (so that a
+// failed wait in any launch of the call is reported).
+hipError_t clear_err(sg_handle H)
+{
+    if (H->err_check) return hipSuccess;
+    H->err_check = true;
+    return sg::launch_fill_u32(H->at<uint32_t>(H->off_err), 3, 0u, H->stream);
+}
+
+// The cooperative launch can be refused (while another process on the device
+// makes such launches): those instances are left to the caller, in `refused`.
+sg_status run_team(sg_handle H, const sg_run_params* p, const std::vector<int>& which, std::vector<int>& refused)
 {
     hipStream_t st = H->stream;
     sg::CallStats* cs = H->at<sg::CallStats>(H->off_stats);
-    uint32_t* err = H->at<uint32_t>(H->off_err);
-    if (!H->lat_err_check) SG_HIP(sg::launch_fill_u32(err, 1, 0u, st), "fill kernel");
-    H->lat_err_check = true;
     SG_HIP(hipEventRecord(H->evh0, st), "event record");
     H->hot_launches = 0;
     for (int qi : which) {
@@ -1906,19 +1929,31 @@ sg_status run_team(sg_handle H, const sg_run_params* p, const std::vector<int>& 
         int64_t ct = 0;  // its colour offsets in the handle's table
         for (int k = 0; k < qi; ++k) ct += H->insts[(size_t)k].C + 1;
         uint64_t* words = nullptr;
+        sg::TeamWait wait{};
         if (G > 1) {
-            words = H->at<uint64_t>(q.off_team);
-            SG_HIP(sg::launch_fill_u32(words, (uint64_t)q.R * q.slices.size() * 8, 0u, st), "fill kernel");
+            const TeamShare share(q);
+            wait = sg::TeamWait{H->at<uint32_t>(q.off_team), H->at<uint32_t>(H->off_err) + 1,
+                                H->at<uint16_t>(q.off_team + share.save), (uint32_t)H->team_polls};
+            words = H->at<uint64_t>(q.off_team + 64);
+            SG_HIP(sg::launch_fill_u32(wait.err, share.save / 4, 0u, st), "fill kernel");
+            SG_HIP(clear_err(H), "fill kernel");
         }
         SG_HIP(sg::launch_begin(rs, q.R, acc, (int64_t)q.R * q.acc_slots * 2, st), "begin kernel");
-        SG_HIP(sg::launch_team(H->view(q), q.max_ew, H->at<int32_t>(H->off_ctab) + ct, q.C, H->at<int8_t>(q.off_spins),
-                               (int64_t)q.spin_stride, rs, q.R, G, acc, q.acc_slots, words, err, p->max_sweeps,
-                               p->seed, p->rule, p->until_converged, st),
-               "team kernel");
+        hipError_t le = hipErrorCooperativeLaunchTooLarge;
+        if (G == 1 || H->team_polls)
+            le = sg::launch_team(H->view(q), q.max_ew, H->at<int32_t>(H->off_ctab) + ct, q.C,
+                                 H->at<int8_t>(q.off_spins), (int64_t)q.spin_stride, rs, q.R, G, acc, q.acc_slots,
+                                 words, wait, p->max_sweeps, p->seed, p->rule, p->until_converged, st);
+        if (le != hipSuccess && G > 1) {
+            (void)hipGetLastError();
+            refused.push_back(qi);
+            continue;
+        }
+        SG_HIP(le, "team kernel");
         ++H->hot_launches;
         H->last_team = G;
         SG_HIP(sg::launch_end(rs, q.R, acc, q.acc_slots, p->max_sweeps, p->until_converged, q.n, cs, st,
-                              p->until_converged ? 2 : 0),
+                              p->until_converged ? 2 : 0, wait.err),
                "end kernel");
     }
     SG_HIP(hipEventRecord(H->evh1, st), "event record");
@@ -2179,10 +2214,7 @@ sg_status run_lattice_schedule(sg_handle H, const sg_run_params* p, const std::v
     hipStream_t st = H->stream;
     sg::CallStats* cs = H->at<sg::CallStats>(H->off_stats);
     uint32_t* err = H->at<uint32_t>(H->off_err);
-    // the tile kernels' error flag: cleared once per call (so a failed wait in
-    // any launch of the call is reported), read with the call totals at its end
-    SG_HIP(sg::launch_fill_u32(err, 1, 0u, st), "fill kernel");
-    H->lat_err_check = true;
+    SG_HIP(clear_err(H), "fill kernel");
     for (int qi : which) {
         const HostInst& q = H->insts[qi];
         sg::RepState* rs = H->reps() + q.rep_base;
@@ -2522,19 +2554,11 @@ uint64_t queue_teams(sg_handle H, const sg_run_params* p, int n_big, int grid, s
     return best_bytes;
 }
 
-sg_status run_queue_schedule(sg_handle H, const sg_run_params* p, const std::vector<int>& which)
+// One queue launch over the items of h_qitems, which are sorted.
+sg_status run_queue_items(sg_handle H, const sg_run_params* p, bool may_team)
 {
-    if (which.empty()) return SG_OK;
     hipStream_t st = H->stream;
-    // items sorted by decreasing size (longest first), large items before wavefront items
-    H->h_qitems.clear();
-    int nmax_big = 0, nmax_small = 0;
-    for (int qi : which)
-        for (int r = 0; r < H->insts[qi].R; ++r) H->h_qitems.push_back(sg::QueueItem{qi, r});
-    std::stable_sort(H->h_qitems.begin(), H->h_qitems.end(), [&](const sg::QueueItem& a, const sg::QueueItem& b) {
-        return H->insts[a.inst].n > H->insts[b.inst].n;
-    });
-    int n_big = 0;
+    int nmax_big = 0, nmax_small = 0, n_big = 0;
     for (const sg::QueueItem& it : H->h_qitems) {
         const int n = H->insts[it.inst].n;
         if (n > H->queue_wave_max_n) {
@@ -2555,14 +2579,14 @@ sg_status run_queue_schedule(sg_handle H, const sg_run_params* p, const std::vec
     const int n_items = (int)H->h_qitems.size();
     sg::QueueItem* dit = H->at<sg::QueueItem>(H->off_qitems);
     sg::QueueTeams teams;
-    const uint64_t tbytes = queue_teams(H, p, n_big, grid, lds, teams);
+    const uint64_t tbytes = may_team ? queue_teams(H, p, n_big, grid, lds, teams) : 0;
     if (teams.n) {
         teams.tab = H->at<sg::QueueItem>(H->off_qteam_tab);
         teams.words = H->at<uint64_t>(H->off_qteam);
-        teams.err = H->at<uint32_t>(H->off_err);
+        teams.flag = H->at<uint32_t>(H->off_err) + 2;
+        teams.polls = (uint32_t)H->team_polls;
         SG_HIP(sg::launch_fill_u32(teams.words, tbytes / 4, 0u, st), "fill kernel");
-        if (!H->lat_err_check) SG_HIP(sg::launch_fill_u32(teams.err, 1, 0u, st), "fill kernel");
-        H->lat_err_check = true;
+        SG_HIP(clear_err(H), "fill kernel");
         SG_HIP(hipMemcpyAsync(H->at<sg::QueueItem>(H->off_qteam_tab), H->h_qteams.data(),
                               H->h_qteams.size() * sizeof(sg::QueueItem), hipMemcpyHostToDevice, st),
                "upload queue teams");
@@ -2574,15 +2598,36 @@ sg_status run_queue_schedule(sg_handle H, const sg_run_params* p, const std::vec
            "upload queue items");
     SG_HIP(hipEventRecord(H->evh0, st), "event record");
     H->hot_launches = 1;
-    SG_HIP(sg::launch_queue(H->at<sg::InstTab>(H->off_tab), H->at<int32_t>(H->off_ctab), dit, n_big, n_items, cnt,
-                            wave_lds, lds, grid, H->reps(), H->at<sg::CallStats>(H->off_stats), p->max_sweeps, p->seed,
-                            p->rule, p->until_converged, st, teams),
-           "queue kernel");
+    auto launch = [&] {
+        return sg::launch_queue(H->at<sg::InstTab>(H->off_tab), H->at<int32_t>(H->off_ctab), dit, n_big, n_items, cnt,
+                                wave_lds, lds, grid, H->reps(), H->at<sg::CallStats>(H->off_stats), p->max_sweeps,
+                                p->seed, p->rule, p->until_converged, st, teams);
+    };
+    hipError_t le = teams.n && !H->team_polls ? hipErrorCooperativeLaunchTooLarge : launch();
+    if (le != hipSuccess && teams.n) {  // the cooperative launch was refused (see run_team)
+        (void)hipGetLastError();
+        teams = sg::QueueTeams{};
+        le = launch();
+    }
+    SG_HIP(le, "queue kernel");
     SG_HIP(hipEventRecord(H->evh1, st), "event record");
     SG_HIP(hipStreamSynchronize(st), "stream sync");  // the host item list is reused
-    H->last_queue_teams = teams.n;
+    H->last_queue_teams += teams.n;
     H->last_queue_grid = grid;
     return SG_OK;
+}
+
+sg_status run_queue_schedule(sg_handle H, const sg_run_params* p, const std::vector<int>& which)
+{
+    if (which.empty()) return SG_OK;
+    // items sorted by decreasing size (longest first), large items before wavefront items
+    H->h_qitems.clear();
+    for (int qi : which)
+        for (int r = 0; r < H->insts[qi].R; ++r) H->h_qitems.push_back(sg::QueueItem{qi, r});
+    std::stable_sort(H->h_qitems.begin(), H->h_qitems.end(), [&](const sg::QueueItem& a, const sg::QueueItem& b) {
+        return H->insts[a.inst].n > H->insts[b.inst].n;
+    });
+    return run_queue_items(H, p, true);
 }
 
 // ---------------------------------------------------------------------------
@@ -3149,6 +3194,54 @@ sg_status ensure_energy(sg_handle H)
     return SG_OK;
 }
 
+// A wait of some team gave up (its members were not resident together for
+// seconds): the replicas of those teams go back to their starts and run again
+// without teams, in per-phase launches and as plain queue items.  Everything
+// else of the call stands.
+sg_status rerun_teams(sg_handle H, const sg_run_params* p, const std::vector<int>& team)
+{
+    hipStream_t st = H->stream;
+    std::vector<int> failed;
+    for (int qi : team) {
+        const HostInst& q = H->insts[(size_t)qi];
+        if (team_groups(H, q, p) < 2) continue;
+        uint32_t bad = 0;  // (stays 0 where the launch was refused)
+        SG_HIP(hipMemcpyAsync(&bad, H->at<uint32_t>(q.off_team), 4, hipMemcpyDeviceToHost, st), "error flag copy");
+        SG_HIP(hipStreamSynchronize(st), "stream sync");
+        if (!bad) continue;
+        SG_HIP(sg::launch_team_restore(H->at<uint16_t>(q.off_team + TeamShare(q).save), q.n, H->at<int8_t>(q.off_spins),
+                                       (int64_t)q.spin_stride, H->reps() + q.rep_base, q.R, st),
+               "restore kernel");
+        failed.push_back(qi);
+        H->last_team_reruns += q.R;
+    }
+    H->h_qitems.clear();
+    for (size_t k = 0; H->last_queue_teams && k < H->h_qteams.size(); k += 2) {
+        if (H->h_qteams[k + 1].inst & 0xFFFF) continue;  // its first member
+        const sg::QueueItem it = H->h_qteams[k];
+        const HostInst& q = H->insts[(size_t)it.inst];
+        const uint64_t at = H->off_qteam + (uint64_t)H->h_qteams[k + 1].r * 32;
+        uint32_t bad = 0;
+        SG_HIP(hipMemcpyAsync(&bad, H->at<uint32_t>(at) + sg::kQueueTeamErr, 4, hipMemcpyDeviceToHost, st),
+               "error flag copy");
+        SG_HIP(hipStreamSynchronize(st), "stream sync");
+        if (!bad) continue;
+        SG_HIP(sg::launch_team_restore(H->at<uint16_t>(at + 64 + 32 * (uint64_t)q.slices.size()), q.n,
+                                       H->at<int8_t>(q.off_spins) + (uint64_t)it.r * q.spin_stride,
+                                       (int64_t)q.spin_stride, H->reps() + q.rep_base + it.r, 1, st),
+               "restore kernel");
+        H->h_qitems.push_back(it);
+        ++H->last_team_reruns;
+    }
+    sg_status e = SG_OK;
+    if (!failed.empty()) {  // the per-phase launches need the start energies
+        if ((e = ensure_energy(H)) != SG_OK) return e;
+        e = run_phase_schedule(H, p, failed);
+    }
+    if (e == SG_OK && !H->h_qitems.empty()) e = run_queue_items(H, p, false);
+    return e;
+}
+
 extern "C" {
 
 const char* sg_last_error(void) { return g_err.c_str(); }
@@ -3583,10 +3676,12 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
     SG_HIP(sg::launch_fill_u32(H->at<uint32_t>(H->off_stats), sizeof(sg::CallStats) / 4, 0u, st), "fill kernel");
     SG_HIP(hipEventRecord(H->ev0, st), "event record");
     H->hot_launches = 0;
-    H->lat_err_check = false;
+    H->err_check = false;
     H->last_team = 0;
+    H->last_team_reruns = 0;
     H->last_queue_teams = 0;
     H->e_written.assign(H->insts.size(), 0);
+    std::vector<int> team, refused;  // instances of the team kernel
     for (int kind : {SG_SCHED_LATTICE, SG_SCHED_BLOCK, SG_SCHED_QUEUE, SG_SCHED_GRAPH, SG_SCHED_FIELDS, SG_SCHED_PHASE}) {
         std::vector<int> which;
         for (size_t k = 0; k < assign.size(); ++k)
@@ -3600,10 +3695,11 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
         case SG_SCHED_FIELDS: e = run_phase_schedule(H, p, which, true); break;
         default: {
             // SG_SCHED_AUTO: all phases in one launch where the team kernel takes the instance
-            std::vector<int> team, rest;
+            std::vector<int> rest;
             for (int qi : which) (team_groups(H, H->insts[(size_t)qi], p) > 0 ? team : rest).push_back(qi);
             e = rest.empty() ? SG_OK : run_phase_schedule(H, p, rest);
-            if (e == SG_OK && !team.empty()) e = run_team(H, p, team);
+            if (e == SG_OK && !team.empty()) e = run_team(H, p, team, refused);
+            if (e == SG_OK && !refused.empty() && (e = ensure_energy(H)) == SG_OK) e = run_phase_schedule(H, p, refused);
             break;
         }
         }
@@ -3611,15 +3707,21 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
     }
     SG_HIP(hipEventRecord(H->ev1, st), "event record");
     sg::CallStats cs;
-    uint32_t herr = 0;
+    uint32_t herr[3] = {0, 0, 0};
     CopiesOut out(H);
     SG_HIP(out.copy(&cs, H->at<sg::CallStats>(H->off_stats), sizeof cs, st), "stats copy");
-    if (H->lat_err_check) SG_HIP(out.copy(&herr, H->at<uint32_t>(H->off_err), 4, st), "error flag copy");
+    if (H->err_check) SG_HIP(out.copy(herr, H->at<uint32_t>(H->off_err), sizeof herr, st), "error flag copy");
     SG_HIP(hipStreamSynchronize(st), "stream sync");
     out.finish();
-    if (herr)
-        return fail(SG_EDEVICE, "lattice tile or team kernel: a neighbour wait timed out (replica state is undefined; "
-                                "start again with sg_init_spins)");
+    if (herr[0])
+        return fail(SG_EDEVICE, "lattice tile kernel: a neighbour wait timed out (replica state is undefined; start "
+                                "again with sg_init_spins)");
+    if (herr[1] || herr[2]) {
+        if ((e = rerun_teams(H, p, team)) != SG_OK) return e;
+        SG_HIP(hipEventRecord(H->ev1, st), "event record");
+        SG_HIP(hipMemcpyAsync(&cs, H->at<sg::CallStats>(H->off_stats), sizeof cs, hipMemcpyDeviceToHost, st), "stats copy");
+        SG_HIP(hipStreamSynchronize(st), "stream sync");
+    }
     if (H->e_pending) {
         // the queue and team kernels wrote the energies of the replicas that
         // converged, the bit-plane lattice kernel those of its instances; if any replica
@@ -3984,6 +4086,9 @@ sg_status sg_tune(sg_handle H, const char* key, int64_t value)
     } else if (k == "team_wgs") {
         if (value < -1 || value > 256) return fail(SG_EINVAL, "team_wgs must be -1..256");
         H->team_wgs = (int32_t)value;
+    } else if (k == "team_polls") {
+        if (value < 0 || value > (1 << 30)) return fail(SG_EINVAL, "team_polls must be in [0, 2^30]");
+        H->team_polls = (int32_t)value;
     } else if (k == "queue_min_items") {
         if (value < 1) return fail(SG_EINVAL, "queue_min_items must be >= 1");
         H->queue_min_items = (int32_t)std::min<int64_t>(value, INT32_MAX);
@@ -4021,7 +4126,9 @@ sg_status sg_query(sg_handle H, const char* key, int64_t* value)
     else if (k == "queue_wave_max_n") *value = H->queue_wave_max_n;
     else if (k == "queue_grid") *value = H->queue_grid;
     else if (k == "team_wgs") *value = H->team_wgs;
+    else if (k == "team_polls") *value = H->team_polls;
     else if (k == "last_team") *value = H->last_team;
+    else if (k == "last_team_reruns") *value = H->last_team_reruns;
     else if (k == "queue_min_items") *value = H->queue_min_items;
     else if (k == "graph_sweeps") *value = H->graph_sweeps;
     else if (k == "auto_graph") *value = H->auto_graph;

@@ -289,8 +289,10 @@ __global__ __launch_bounds__(kPhaseThreads) void k_phase(InstDev I, int8_t* __re
 // each slot is an energy change, or with `absolute` the slot's share of the
 // final energy (then it replaces E of every replica not frozen at entry).
 __global__ void k_end(RepState* __restrict__ rs, const int64_t* __restrict__ acc, int nslots, int T,
-                      int until_conv, int64_t n, CallStats* __restrict__ cs, int absolute)
+                      int until_conv, int64_t n, CallStats* __restrict__ cs, int absolute,
+                      const uint32_t* __restrict__ err)
 {
+    if (err && *err) return;  // the call's sweeps were given up
     const int r = blockIdx.x;
     RepState* st = rs + r;
     long long dE = 0, nf = 0;
@@ -538,11 +540,11 @@ hipError_t launch_bump(int32_t* t_base, int d, hipStream_t st)
 }
 
 hipError_t launch_end(RepState* rs, int R, const int64_t* acc, int nslots, int T, int until_conv, int64_t n,
-                      CallStats* cs, hipStream_t st, int absolute)
+                      CallStats* cs, hipStream_t st, int absolute, const uint32_t* err)
 {
     const unsigned threads = nslots <= 64 ? 64 : 256;
     hipLaunchKernelGGL(k_end, dim3(R), dim3(threads), 0, st, rs, acc, nslots, T, until_conv, n, cs,
-                       absolute);
+                       absolute, err);
     return hipGetLastError();
 }
 

@@ -27,8 +27,9 @@ hipError_t launch_bump(int32_t* t_base, int d, hipStream_t st);
 // Fold a call's per-slot accumulators into the replicas.  absolute: the slots
 // hold 0 energy changes, 1 shares of the final energy, 2 energy changes, or for
 // a replica that converges in the call shares of -6 times its final energy.
+// Where *err is set (err may be null) the replicas stay as they are.
 hipError_t launch_end(RepState* rs, int R, const int64_t* acc, int nslots, int T, int until_conv, int64_t n,
-                      CallStats* cs, hipStream_t st, int absolute = 0);
+                      CallStats* cs, hipStream_t st, int absolute = 0, const uint32_t* err = nullptr);
 hipError_t launch_any_active(const RepState* rs, int R, int T, uint32_t* flag, hipStream_t st);
 // Word 0 of Philox4x32-10 of count counters (4 uint32 each) under key seed.
 hipError_t launch_philox_word0(const uint32_t* ctr, uint32_t* out, int64_t count, uint64_t seed, hipStream_t st);
@@ -191,14 +192,20 @@ hipError_t launch_start_units(const InstTab* tab, const StartUnit* start_units, 
 inline size_t queue_big_lds(int n) { return (size_t)n; }  // LDS of an item on a whole workgroup
 // The first n items run on teams of workgroups before the queue starts.  Per
 // workgroup below nwg, tab holds its item and {member | members << 16, offset}:
-// the item's part of words, in units of 32 bytes; 32 bytes of sums and 32 bytes
-// per slice, all zero at launch.  The grid must be co-resident (at most
-// queue_max_blocks of its LDS).
+// the item's part of words, in units of 32 bytes; 64 bytes of sums, an arrival
+// count and the wait's error word (kQueueTeamErr, in 32-bit words), 32 bytes per
+// slice, and the start that the team keeps, all zero at launch.  The grid must
+// be co-resident (at most queue_max_blocks of its LDS).  A wait that takes
+// `polls` looks gives up: *flag is set then, and of the items whose error word
+// is set nothing but the spins has changed (launch_team_restore).
+constexpr uint64_t queue_team_bytes(int n, uint64_t nslices) { return 64 + 32 * nslices + 2 * team_save_words(n); }
+constexpr int kQueueTeamErr = 8;
 struct QueueTeams {
     const QueueItem* tab = nullptr;
     int nwg = 0, n = 0;
     uint64_t* words = nullptr;
-    uint32_t* err = nullptr;
+    uint32_t* flag = nullptr;
+    uint32_t polls = 0;
 };
 hipError_t launch_queue(const InstTab* tab, const int32_t* ctab, const QueueItem* items, int n_big, int n_items,
                         uint32_t* counters, int wave_lds, size_t lds, int grid, RepState* rs, CallStats* cs, int T,
@@ -209,11 +216,16 @@ hipError_t launch_queue(const InstTab* tab, const int32_t* ctab, const QueueItem
 // replica 4 exchange words per slice, zero at launch (null for G = 1); rs, acc
 // as the per-phase kernels use them (k_begin before, k_end after).  With G > 1
 // the launch is cooperative: R G at most team_max_blocks, and no member
-// without a slice (G at most the slices of the largest colour).
+// without a slice (G at most the slices of the largest colour).  Where a wait
+// gives up (wait.err and wait.flag set, zero at launch), launch_team_restore
+// puts the spins back that wait.save holds (team_save_words per replica), and
+// launch_end leaves the replicas as they were when it is given wait.err.
 bool team_fits(int n, int C);
 int team_max_blocks(int n, bool tie, bool tri, int ew);
 hipError_t launch_team(const InstDev& I, int ew, const int32_t* ct, int C, int8_t* spins, int64_t stride, RepState* rs, int R,
-                       int G, int64_t* acc, int nslots, uint64_t* words, uint32_t* err, int T, uint64_t seed, int rule,
-                       int until_conv, hipStream_t st);
+                       int G, int64_t* acc, int nslots, uint64_t* words, const TeamWait& wait, int T, uint64_t seed,
+                       int rule, int until_conv, hipStream_t st);
+hipError_t launch_team_restore(const uint16_t* save, int n, int8_t* spins, int64_t stride, const RepState* rs, int R,
+                               hipStream_t st);
 
 }  // namespace sg

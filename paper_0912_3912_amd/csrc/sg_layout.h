@@ -79,6 +79,19 @@ struct WideDev {
     int32_t has_tri;
 };
 
+// How a team gives up: the waits of its members take at most `polls` looks, and
+// the first that runs out sets *err, which ends the others, and *flag, which
+// tells the host.  save: where the team keeps the replica's start, bit k of
+// word w the sign of spin 16 w + k.
+struct TeamWait {
+    uint32_t *err, *flag;
+    uint16_t* save;
+    uint32_t polls;
+};
+
+// 16-bit words of a replica's start, to a multiple of 32 bytes.
+constexpr uint64_t team_save_words(int n) { return ((uint64_t)n + 255) / 256 * 16; }
+
 // Per-replica state, 32 bytes.
 struct RepState {
     int64_t E;          // tracked energy

@@ -237,13 +237,14 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
         const InstTab& Q = tab[it.inst];
         const RepState* st0 = rs + Q.rep_base + it.r;
         if (!st0->converged) {  // (the same for the whole team: its last member alone writes the state)
-            const TeamArgs A{queue_inst(Q.I), queue_uniform(ctab + Q.ctab_off), __builtin_amdgcn_readfirstlane(Q.C), G, m,
-                             it.r, Q.spins + (int64_t)it.r * Q.spin_stride, (uint64_t*)w + 4, teams.err,
+            const InstDev QI = queue_inst(Q.I);
+            const TeamWait wait{(uint32_t*)(w + 4), teams.flag, (uint16_t*)(w + 8 + 4 * (int64_t)QI.nslices), teams.polls};
+            const TeamArgs A{QI, queue_uniform(ctab + Q.ctab_off), __builtin_amdgcn_readfirstlane(Q.C), G, m,
+                             it.r, Q.spins + (int64_t)it.r * Q.spin_stride, (uint64_t*)w + 8, wait,
                              (uint32_t)st0->sweeps, T, until_conv, seed, &F.team};
             TeamOut o;
             if (__builtin_amdgcn_readfirstlane(Q.I.has_tri)) o = team_run<false, TIE, true, true, kTeamW>(A);
             else o = team_run<false, TIE, false, true, kTeamW>(A);
-            if (o.dead) return;
             const long long wd = team_wave_sum(o.dE), we = team_wave_sum(o.e6);
             if (lane == 0) {
                 atomicAdd(w, (unsigned long long)wd);
@@ -252,8 +253,9 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
                 __threadfence();
             }
             __syncthreads();
-            // the member that arrives last has everyone's sums
-            if (tid == 0 && __hip_atomic_fetch_add(w + 3, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned long long)G) {
+            // the member that arrives last has everyone's sums (none does where
+            // a wait gave up)
+            if (tid == 0 && !o.dead && __hip_atomic_fetch_add(w + 3, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned long long)G) {
                 const long long a = (long long)__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const long long e = (long long)__hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const int b = (int)__hip_atomic_load(w + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -278,7 +280,7 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
         if (frozen) continue;
         const uint32_t base = (uint32_t)st0->sweeps;
         const TeamArgs A{queue_inst(I), queue_uniform(ctab + Q.ctab_off), __builtin_amdgcn_readfirstlane(Q.C), 1, 0,
-                         it.r, gsp, nullptr, nullptr, base, T, until_conv, seed, &F.team};
+                         it.r, gsp, nullptr, TeamWait{}, base, T, until_conv, seed, &F.team};
         TeamOut o;
         if (__builtin_amdgcn_readfirstlane(I.has_tri)) o = team_run<true, TIE, true, true, kTeamW>(A);
         else if (__builtin_amdgcn_readfirstlane(Q.max_ew) <= 4) o = team_run<true, TIE, false, true, 4>(A);

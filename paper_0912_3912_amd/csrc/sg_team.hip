@@ -24,15 +24,14 @@ namespace sg {
 // on entry) take the energy changes (of a replica that converged, -6 times its
 // energy) and flips, rs[r].lastflip 1 + the last
 // sweep that flipped.  Dynamic LDS: the spins, then from word tl_off on a
-// TeamLds.
+// TeamLds.  save_words: the 16-bit words of a replica's start in wait.save.
 // CONV: run until converged.
 template <bool BYTES, bool TIE, bool TRI, int W, bool CONV>
 __global__ __launch_bounds__(kTeamThreads) void k_team(const InstDev I, const int32_t* __restrict__ ct, int C,
                                                        int8_t* __restrict__ spins, int64_t stride,
                                                        RepState* __restrict__ rs, int G, int64_t* __restrict__ acc,
-                                                       int nslots, uint64_t* __restrict__ words,
-                                                       uint32_t* __restrict__ err, int T, uint64_t seed,
-                                                       uint32_t tl_off)
+                                                       int nslots, uint64_t* __restrict__ words, TeamWait wait,
+                                                       int64_t save_words, int T, uint64_t seed, uint32_t tl_off)
 {
     extern __shared__ __align__(16) uint32_t bits[];
     // behind the spins, which start LDS
@@ -40,8 +39,9 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(const InstDev I, const in
     const int r = (int)blockIdx.x / G, m = (int)blockIdx.x % G;
     RepState* st = rs + r;
     if (st->converged) return;  // the same for the whole team
-    const TeamArgs A{I,   ct,  C, G,          m,    r,    spins + stride * r, words + (size_t)r * I.nslices * 4,
-                     err, (uint32_t)st->sweeps, T, CONV, seed, &tl};
+    if (G > 1) wait.save += save_words * r;
+    const TeamArgs A{I,    ct, C, G,          m,    r,    spins + stride * r, words + (size_t)r * I.nslices * 4,
+                     wait, (uint32_t)st->sweeps, T, CONV, seed, &tl};
     const TeamOut o = team_run<BYTES, TIE, TRI, CONV, W>(A);
     if (o.dead) return;
     // a sweep without a flip evaluates every spin on the final configuration:
@@ -53,6 +53,17 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(const InstDev I, const in
         if (o.nf) atomicAdd((unsigned long long*)a + 1, (unsigned long long)o.nf);
     }
     if (m == 0 && threadIdx.x == 0) st->lastflip = o.lastflip;
+}
+
+// Replicas r0 + blockIdx.y, those not frozen, back to the start that their team
+// kept, sixteen spins a thread.
+__global__ void k_team_restore(const uint16_t* __restrict__ save, int64_t save_words, int n, int8_t* __restrict__ spins,
+                               int64_t stride, const RepState* __restrict__ rs)
+{
+    const int r = (int)blockIdx.y, k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (rs[r].converged || k * 16 >= n) return;
+    const uint32_t b = save[save_words * r + k];
+    for (int u = 0; u < 16 && k * 16 + u < n; ++u) spins[stride * r + k * 16 + u] = (b >> u & 1u) ? (int8_t)-1 : (int8_t)1;
 }
 
 // Rows of at most four couplings take a third of the loads (hyper-coupled rows
@@ -96,11 +107,14 @@ int team_max_blocks(int n, bool tie, bool tri, int ew)
 }
 
 hipError_t launch_team(const InstDev& I, int ew, const int32_t* ct, int C, int8_t* spins, int64_t stride, RepState* rs, int R,
-                       int G, int64_t* acc, int nslots, uint64_t* words, uint32_t* err, int T, uint64_t seed, int rule,
-                       int until_conv, hipStream_t st)
+                       int G, int64_t* acc, int nslots, uint64_t* words, const TeamWait& wait0, int T, uint64_t seed,
+                       int rule, int until_conv, hipStream_t st)
 {
     if (R <= 0 || T <= 0) return hipSuccess;
-    if (G < 1 || !team_fits(I.n, C) || (G > 1 && !words)) return hipErrorInvalidValue;
+    if (G < 1 || !team_fits(I.n, C) || (G > 1 && !(words && wait0.err && wait0.flag && wait0.save)))
+        return hipErrorInvalidValue;
+    TeamWait wait = wait0;
+    int64_t save_words = (int64_t)team_save_words(I.n);
     const void* kern = team_kernel(team_bytes(I.n, G), until_conv != 0, rule == 1, I.has_tri != 0, ew);
     const size_t lds = team_spins(I.n, G) + sizeof(TeamLds);
     static const bool free0 = [] {
@@ -113,10 +127,18 @@ hipError_t launch_team(const InstDev& I, int ew, const int32_t* ct, int C, int8_
     if (e != hipSuccess) return e;
     InstDev a0 = I;
     uint32_t tl_off = (uint32_t)(team_spins(I.n, G) / 4);
-    void* args[] = {&a0, &ct, &C, &spins, &stride, &rs, &G, &acc, &nslots, &words, &err, &T, &seed, &tl_off};
+    void* args[] = {&a0, &ct, &C, &spins, &stride, &rs, &G, &acc, &nslots, &words, &wait, &save_words, &T, &seed, &tl_off};
     // members wait for each other: the cooperative launch has them all resident
     if (G > 1) return hipLaunchCooperativeKernel(kern, dim3((unsigned)(R * G)), dim3(kTeamThreads), args, (unsigned)lds, st);
     return hipLaunchKernel(kern, dim3((unsigned)R), dim3(kTeamThreads), args, lds, st);
+}
+
+hipError_t launch_team_restore(const uint16_t* save, int n, int8_t* spins, int64_t stride, const RepState* rs, int R,
+                               hipStream_t st)
+{
+    hipLaunchKernelGGL(k_team_restore, dim3((unsigned)((n + 4095) / 4096), (unsigned)R), dim3(256), 0, st, save,
+                       (int64_t)team_save_words(n), n, spins, stride, rs);
+    return hipGetLastError();
 }
 
 }  // namespace sg

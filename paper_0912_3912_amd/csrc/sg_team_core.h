@@ -28,6 +28,12 @@
 // whole of this one (every member has a slice of the largest colour).  Each
 // slice is published once a sweep.  Every member sees every flip, so all of
 // them take the same decision to stop.
+//
+// The members of a team have to be resident together.  The cooperative launch
+// sees to that, but not beside another process's grid of that kind, nor beside
+// kernels that hold the compute units for seconds; so every wait is bounded
+// (TeamWait), a team keeps its replica's start (one bit a spin), and the host
+// runs the replicas of a team that gave up again without one.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -43,7 +49,6 @@ constexpr int kTeamThreads = 1024;
 constexpr int kTeamWaves = kTeamThreads / 64;
 constexpr int kTeamW = 12, kTeamT = 4;  // coupling and hyper-coupling words of a slice loaded at once (W: at most kTeamW)
 constexpr int kTeamColours = 64;        // colours whose tables fit the static LDS
-constexpr uint32_t kTeamSpin = 1u << 22;  // polls before a wait gives up
 
 typedef __attribute__((address_space(1))) const uint32_t team_g32;
 typedef __attribute__((address_space(1))) int8_t team_gw8;
@@ -221,7 +226,7 @@ struct TeamArgs {
     int C, G, m, r;     // colours (at most kTeamColours if G > 1); members (1 with bytes), this one; restart
     int8_t* sp;         // the replica's spins (row padded to 256 bytes)
     uint64_t* words;    // two copies of two words per slice, tags zero on entry
-    uint32_t* err;
+    TeamWait wait;      // (G > 1)
     uint32_t base;      // sweeps before the call
     int T, until_conv;
     uint64_t seed;
@@ -242,7 +247,7 @@ __device__ __forceinline__ void team_barrier()
 struct TeamOut {
     long long dE, e6, nf;
     int performed, lastflip;
-    bool dead;  // a wait gave up: nothing is written
+    bool dead;  // a wait gave up: this member's rows are not written
 };
 
 template <bool BYTES, bool TIE, bool TRI, bool E6, int W = kTeamW>
@@ -267,6 +272,8 @@ __device__ __forceinline__ TeamOut team_run(const TeamArgs& A)
         for (int k = tid; k * 16 < n; k += kTeamThreads)
             *(team_l128*)team_lds((uint32_t)k * 16u) = *(const team_v4*)(A.sp + k * 16);
     } else {
+        const int words16 = (n + 15) / 16;  // this member keeps its share of the start
+        const int k0 = (int)((int64_t)words16 * m / G), k1 = G > 1 ? (int)((int64_t)words16 * (m + 1) / G) : 0;
         for (int k = tid; k * 16 < n; k += kTeamThreads) {
             const uint4 v = *reinterpret_cast<const uint4*>(A.sp + k * 16);
             const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -276,6 +283,7 @@ __device__ __forceinline__ TeamOut team_run(const TeamArgs& A)
                 b |= ((w[u] >> 7 & 1u) | (w[u] >> 14 & 2u) | (w[u] >> 21 & 4u) | (w[u] >> 28 & 8u)) << (4 * u);
             if (n - k * 16 < 16) b &= (1u << (n - k * 16)) - 1u;
             *(team_l16*)team_lds((uint32_t)k * 2u) = (uint16_t)b;
+            if (k >= k0 && k < k1) A.wait.save[k] = (uint16_t)b;
         }
     }
     __syncthreads();
@@ -440,10 +448,11 @@ __device__ __forceinline__ TeamOut team_run(const TeamArgs& A)
                     }
                     // bounded: a wait that gives up here or in any other
                     // workgroup raises the error flag and ends them all
-                    for (uint32_t polls = kTeamSpin; ((v[0] ^ tag) | (v[1] ^ tag) | (v[2] ^ tag) | (v[3] ^ tag)) >> 32;) {
-                        if (--polls == 0 || ((polls & 63u) == 0 && __hip_atomic_load(A.err, __ATOMIC_RELAXED,
+                    for (uint32_t polls = A.wait.polls; ((v[0] ^ tag) | (v[1] ^ tag) | (v[2] ^ tag) | (v[3] ^ tag)) >> 32;) {
+                        if (--polls == 0 || ((polls & 63u) == 0 && __hip_atomic_load(A.wait.err, __ATOMIC_RELAXED,
                                                                                     __HIP_MEMORY_SCOPE_AGENT) != 0u)) {
-                            __hip_atomic_store(A.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_store(A.wait.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_store(A.wait.flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                             T.dead = t + 1;
 #pragma unroll
                             for (int u = 0; u < 4; ++u) v[u] = tag;
