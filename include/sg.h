@@ -451,8 +451,14 @@ sg_status sg_solve(sg_handle h, const sg_run_params* p, sg_run_stats* stats, int
  *   "team_wgs"           workgroups per replica where SG_SCHED_AUTO runs the
  *                        phases of an instance it gives to SG_SCHED_PHASE in
  *                        one launch (at most 64 restarts, 1.2 million spins,
- *                        64 colours, packed form): 0 chosen by size, 1..256,
- *                        -1 per-phase launches as under SG_SCHED_PHASE itself
+ *                        64 colours, packed form): 0 chosen by size, 1..256
+ *                        (at most the 64-row slices of the largest colour and
+ *                        what the device holds at once; set before sg_bind, so
+ *                        that the workspace has the room teams need, which is
+ *                        left out where it would take the handle beyond
+ *                        SG_NOALLOC_MAX_BYTES: such an instance runs on one
+ *                        workgroup per replica, or if it is large, as under
+ *                        -1), -1 per-phase launches as under SG_SCHED_PHASE
  *                        (default 0; stats report SG_SCHED_PHASE either way).
  *                        -1 also keeps the queue schedule from running its
  *                        largest items on several workgroups.  The workgroups

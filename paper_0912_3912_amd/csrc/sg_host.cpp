@@ -1515,7 +1515,8 @@ int team_slices(const HostInst& q)
 
 // Team kernel (sg_team.hip): instances whose spins fit LDS as bits, and with
 // exchange words those large enough to split, unless a batch (which the queue
-// schedule takes).
+// schedule takes), or all that have more than one slice of some colour when
+// team_wgs asks for teams.
 constexpr int32_t kTeamMaxR = 64;
 constexpr int32_t kTeamSplit = 80;   // slices of a colour beyond which a replica is split over workgroups
 constexpr int32_t kTeamAlone = 128;  // and up to which one workgroup beats per-phase launches
@@ -1532,8 +1533,9 @@ struct TeamShare {
 bool can_team(const HostInst& q) { return !q.wide && !q.dense && sg::team_fits(q.n, q.C); }
 bool team_words(const sg_ctx* H, const HostInst& q)
 {
-    return can_team(q) && q.R <= kTeamMaxR && team_slices(q) > kTeamSplit &&
-           (q.n > kQueueMaxN || q.lat_ok || H->total_reps < 64);
+    if (!can_team(q) || q.R > kTeamMaxR) return false;
+    if (H->team_wgs > 1) return team_slices(q) > 1;
+    return team_slices(q) > kTeamSplit && (q.n > kQueueMaxN || q.lat_ok || H->total_reps < 64);
 }
 
 // Teams of the queue schedule: items that may run on several workgroups, at
@@ -1900,7 +1902,7 @@ int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
         if (most < 0) most = sg::team_max_blocks(q.n, p->rule == SG_RULE_GREEDY_TIE, q.t > 0, q.max_ew);
         g = q.off_team == UINT64_MAX ? 1 : std::min(g, most / q.R);
     }
-    if (g >= 2 || ns <= kTeamAlone || H->team_wgs > 0) return std::max(g, 1);
+    if (g >= 2 || ns <= kTeamAlone || H->team_wgs == 1) return std::max(g, 1);
     return 0;  // large and not split: the per-phase launches use the whole device
 }
 
@@ -4086,6 +4088,7 @@ sg_status sg_tune(sg_handle H, const char* key, int64_t value)
     } else if (k == "team_wgs") {
         if (value < -1 || value > 256) return fail(SG_EINVAL, "team_wgs must be -1..256");
         H->team_wgs = (int32_t)value;
+        if (!H->bound) layout(H);
     } else if (k == "team_polls") {
         if (value < 0 || value > (1 << 30)) return fail(SG_EINVAL, "team_polls must be in [0, 2^30]");
         H->team_polls = (int32_t)value;
