@@ -178,7 +178,7 @@ __device__ __forceinline__ void queue_phase(const InstDev& I0, const Slice* __re
 }
 
 // e6: -6 E of the last sweep's fields, exact when that sweep flipped nothing.
-__device__ __forceinline__ void queue_finish(const InstTab& Q, int r, long long dE, long long e6, int nflip,
+__device__ __forceinline__ void queue_finish(const InstTab& Q, int r, long long dE, long long e6, long long nflip,
                                              int performed, int lastflip, int T, int until_conv,
                                              RepState* __restrict__ rs, CallStats* __restrict__ cs)
 {
@@ -213,8 +213,8 @@ __device__ __forceinline__ InstDev queue_inst(const InstDev& I)
 
 struct QueueLds {
     TeamLds team;
-    long long pd[kBatWaves], pe[kBatWaves];
-    int pf[kBatWaves], item;
+    long long pd[kBatWaves], pe[kBatWaves], pf[kBatWaves];
+    int item;
 };
 
 template <bool TIE>
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
             if (tid == 0 && !o.dead && __hip_atomic_fetch_add(w + 3, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned long long)G) {
                 const long long a = (long long)__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const long long e = (long long)__hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const int b = (int)__hip_atomic_load(w + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const long long b = (long long)__hip_atomic_load(w + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 queue_finish(Q, it.r, a, e, b, o.performed, o.lastflip, T, until_conv, rs, cs);
             }
         }
@@ -290,12 +290,11 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
         if (lane == 0) {
             F.pd[wave] = wd;
             F.pe[wave] = we;
-            F.pf[wave] = (int)o.nf;
+            F.pf[wave] = o.nf;
         }
         __syncthreads();
         if (tid == 0) {
-            long long a = 0, e = 0;
-            int b = 0;
+            long long a = 0, e = 0, b = 0;
             for (int w = 0; w < kBatWaves; ++w) {
                 a += F.pd[w];
                 e += F.pe[w];
@@ -326,8 +325,8 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                long long dE = 0, e6 = 0;
-                int nflip = 0, performed = 0, lastflip = 0;
+                long long dE = 0, e6 = 0, nflip = 0;  // (nflip: per lane)
+                int performed = 0, lastflip = 0;
                 for (int t = 0; t < T; ++t) {
                     int my = 0;
                     e6 = 0;
@@ -347,8 +346,7 @@ __global__ __launch_bounds__(kBatThreads) void k_queue(const InstTab* __restrict
                     if (until_conv && tot == 0) break;
                 }
                 for (int k = lane; k < I.n; k += 64) gsp[k] = wl[k];
-                long long wd = dE, we = e6;
-                int wf = nflip;
+                long long wd = dE, we = e6, wf = nflip;
 #pragma unroll
                 for (int off = 32; off > 0; off >>= 1) {
                     wd += __shfl_xor(wd, off, 64);
