@@ -18,7 +18,10 @@
 // four LDS round trips), against 107 ms on k_fm, whose lanes each rescan n / 64
 // spins one after another and look their rows up through the sliced layout;
 // with Gaussian int32 couplings 10.2 ms against 130 ms.  With the device full
-// (8192 restarts, two passes) 13.7 ms against 166 ms.
+// (8192 restarts, two passes) 13.7 ms against 166 ms.  Building the rows counts
+// where they are many and the moves few: three passes of one replica of a
+// complete graph of 200 spins (a slice per spin) take 1.8 ms, 2.3 ms on k_fm, and
+// 12.5 ms if a lane copies a row's couplings one after another.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -127,6 +130,28 @@ struct RowsPolicy {
     __device__ __forceinline__ void load(int g, int32_t& x, int32_t& at) const { part(fetch(g), x, at); }
     __device__ __forceinline__ int index(int g, int o, int32_t) const { return g * 64 + o; }
 };
+
+// f(l, k) for every row l below `rows` and k below `width` of a slice, on the
+// lanes of a wavefront: load(l, k) of four of them before put(l, k, value).
+template <class LOAD, class PUT>
+__device__ __forceinline__ void slice_entries(int rows, int width, int lane, const LOAD& load, const PUT& put)
+{
+    const int m = rows * width;
+    for (int x0 = lane; x0 < m; x0 += 256) {
+        decltype(load(0, 0)) v[4];
+        int l[4], k[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int x = min(x0 + 64 * u, m - 1);
+            k[u] = x / rows;
+            l[u] = x - k[u] * rows;
+            v[u] = load(l[u], k[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (x0 + 64 * u < m) put(l[u], k[u], v[u]);
+    }
+}
 
 // What a workgroup runs: restarts [r0, r0 + nr) of one instance.
 struct RowsInst {
@@ -324,6 +349,28 @@ __global__ __launch_bounds__(kRowsThreads) void k_fm_rows(const InstTab* __restr
     auto fill = [&](uint32_t* cw, uint32_t* tw, const uint32_t* ext, int wave, int lane) {
         for (int s = wave; s < D.nslices; s += (int)(blockDim.x >> 6)) {
             const Slice S = D.slices[s];
+            if (S.ew <= dc && (!TRI || S.tw <= tt)) {
+                // every entry where it stands in the slice, on all lanes (a
+                // complete graph has a row per slice)
+                slice_entries(S.rows, S.ew, lane, [&](int l, int k) { return D.nbr[S.ebase + k * kSlice + l]; },
+                              [&](int l, int k, uint32_t w) {
+                                  if (w & 0xffu) cw[(size_t)ext[S.row0 + l] * dc + k] = ext[w >> 8] << 8 | (w & 0xffu);
+                              });
+                if (!TRI) continue;
+                slice_entries(S.rows, S.tw, lane,
+                              [&](int l, int k) {
+                                  const uint32_t at = S.tbase + k * kSlice + l;
+                                  return make_uint2(D.ta[at], D.tb[at]);
+                              },
+                              [&](int l, int k, uint2 w) {
+                                  if (!(w.x & 0xffu)) return;
+                                  uint32_t* t = tw + ((size_t)ext[S.row0 + l] * tt + k) * 2;
+                                  t[0] = ext[w.x >> 8] << 8 | (w.x & 0xffu);
+                                  t[1] = ext[w.y];
+                              });
+                continue;
+            }
+            // rows narrower than the slice, whose unused entries are left out
             if (lane >= S.rows) continue;
             const uint32_t e = ext[S.row0 + lane];
             uint32_t* c = cw + (size_t)e * dc;
@@ -358,27 +405,32 @@ __global__ __launch_bounds__(kRowsThreads) void k_fm_rows_wide(const WideDev D, 
     const RowsInst I{D.ext, spins, stride, rs, D.n, r0, min(W, R - r0)};
     auto fill = [&](uint32_t* cw, uint32_t* tw, const uint32_t* ext, int wave, int lane) {
         for (int s = wave; s < D.nslices; s += W) {
+            // (the widths are those of the widest slice)
             const WSlice S = D.slices[s];
-            if ((uint32_t)lane >= S.rows) continue;
-            const uint32_t e = ext[S.row0 + lane];
-            uint32_t* c = cw + (size_t)e * dc * 2;
-            for (uint32_t k = 0; k < S.ew; ++k) {
-                const uint64_t at = S.ebase + (uint64_t)k * kSlice + lane;
-                const int32_t J = D.J[at];
-                if (!J) continue;
-                *c++ = ext[D.nbr[at]];
-                *c++ = (uint32_t)J;
-            }
+            slice_entries((int)S.rows, (int)S.ew, lane,
+                          [&](int l, int k) {
+                              const uint64_t at = S.ebase + (uint64_t)k * kSlice + l;
+                              return make_uint2(D.nbr[at], (uint32_t)D.J[at]);
+                          },
+                          [&](int l, int k, uint2 w) {
+                              if (!w.y) return;
+                              uint32_t* c = cw + ((size_t)ext[S.row0 + l] * dc + k) * 2;
+                              c[0] = ext[w.x];
+                              c[1] = w.y;
+                          });
             if (!TRI) continue;
-            uint32_t* t = tw + (size_t)e * tt * 3;
-            for (uint32_t k = 0; k < S.tw; ++k) {
-                const uint64_t at = S.tbase + (uint64_t)k * kSlice + lane;
-                const int32_t K = D.K[at];
-                if (!K) continue;
-                *t++ = ext[D.ta[at]];
-                *t++ = ext[D.tb[at]];
-                *t++ = (uint32_t)K;
-            }
+            slice_entries((int)S.rows, (int)S.tw, lane,
+                          [&](int l, int k) {
+                              const uint64_t at = S.tbase + (uint64_t)k * kSlice + l;
+                              return make_uint3(D.ta[at], D.tb[at], (uint32_t)D.K[at]);
+                          },
+                          [&](int l, int k, uint3 w) {
+                              if (!w.z) return;
+                              uint32_t* t = tw + ((size_t)ext[S.row0 + l] * tt + k) * 3;
+                              t[0] = ext[w.x];
+                              t[1] = ext[w.y];
+                              t[2] = w.z;
+                          });
         }
     };
     auto field = [&](int i) { return D.h[i]; };
