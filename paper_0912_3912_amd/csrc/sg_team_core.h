@@ -181,9 +181,17 @@ __device__ __forceinline__ int team_field(const InstDev& I, const TeamSlice& S, 
 #pragma unroll
             for (int k = k0; k < k0 + 4; ++k) f = SP::add(L.w[k], SP::pick(v[k], L.w[k] >> 8), f);
         }
-    for (int k = W; k < S.ew; ++k) {
-        const uint32_t w = ((team_g32*)I.nbr + S.ebase)[l + (uint32_t)(k * kSlice)];
-        f = SP::add(w, SP::pick(SP::at(w >> 8), w >> 8), f);
+    if (W == kTeamW && S.ew > W) {  // longer rows: eight words at a time
+        const __amdgpu_buffer_rsrc_t p = team_buffer(I.nbr, S.ebase, S.ew);
+        for (int k = W; k < S.ew; k += 8) {
+            uint32_t w[8], x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) w[u] = __builtin_amdgcn_raw_buffer_load_b32(p, (int)(l * 4 + (uint32_t)(k + u) * kSlice * 4), 0, 0);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = SP::at(w[u] >> 8);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) f = SP::add(w[u], SP::pick(x[u], w[u] >> 8), f);
+        }
     }
     f1 = f;
     if (TRI) {
@@ -194,10 +202,25 @@ __device__ __forceinline__ int team_field(const InstDev& I, const TeamSlice& S, 
                 for (int k = k0; k < k0 + 2; ++k)
                     f = SP::add(L.a[k], SP::product(SP::pick(ua[k], L.a[k] >> 8), SP::pick(ub[k], L.b[k])), f);
             }
-        for (int k = kTeamT; k < S.tw; ++k) {
-            const uint32_t a = ((team_g32*)I.ta + S.tbase)[l + (uint32_t)(k * kSlice)];
-            const uint32_t b = ((team_g32*)I.tb + S.tbase)[l + (uint32_t)(k * kSlice)];
-            f = SP::add(a, SP::product(SP::pick(SP::at(a >> 8), a >> 8), SP::pick(SP::at(b), b)), f);
+        if (S.tw > kTeamT) {
+            const __amdgpu_buffer_rsrc_t pa = team_buffer(I.ta, S.tbase, S.tw), pb = team_buffer(I.tb, S.tbase, S.tw);
+            for (int k = kTeamT; k < S.tw; k += 4) {
+                uint32_t a[4], b[4], x[4], y[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int at = (int)(l * 4 + (uint32_t)(k + u) * kSlice * 4);
+                    a[u] = __builtin_amdgcn_raw_buffer_load_b32(pa, at, 0, 0);
+                    b[u] = __builtin_amdgcn_raw_buffer_load_b32(pb, at, 0, 0);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    x[u] = SP::at(a[u] >> 8);
+                    y[u] = SP::at(b[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    f = SP::add(a[u], SP::product(SP::pick(x[u], a[u] >> 8), SP::pick(y[u], b[u])), f);
+            }
         }
     }
     return f;
