@@ -17,6 +17,7 @@
 #include <string>
 #include <atomic>
 #include <thread>
+#include <utility>
 #include <vector>
 
 #include "sg.h"
@@ -261,8 +262,9 @@ struct sg_ctx {
     std::vector<uint8_t> e_written;  // this call's kernels wrote the final energies of the instance
     // the current call launched kernels whose workgroups wait for one another:
     // read their error flags at its end (words of off_err: lattice tiles,
-    // teams, the queue schedule's teams)
-    bool err_check = false;
+    // teams, the queue schedule's teams).  err_clean: the last call that used
+    // them read zeros, so that they need no clearing.
+    bool err_check = false, err_clean = false;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     hipEvent_t evh0 = nullptr, evh1 = nullptr;  // around the hot kernel(s) of the last schedule run
     // pinned host memory for the small results a call reads back (sg_bind;
@@ -1907,11 +1909,12 @@ int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
 }
 
 // The call's error flags, cleared by its first launch that needs them (so that a
-// failed wait in any launch of the call is reported).
+// failed wait in any launch of the call is reported) unless they are zero.
 hipError_t clear_err(sg_handle H)
 {
     if (H->err_check) return hipSuccess;
     H->err_check = true;
+    if (std::exchange(H->err_clean, false)) return hipSuccess;
     return sg::launch_fill_u32(H->at<uint32_t>(H->off_err), 3, 0u, H->stream);
 }
 
@@ -2975,6 +2978,7 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
     H->last_fm_waves = wave_reps ? waves : rw;
     sg::QueueItem* dit = H->at<sg::QueueItem>(H->off_qitems);
     uint32_t* err = H->at<uint32_t>(H->off_err);
+    H->err_clean = false;
     SG_HIP(sg::launch_fill_u32(H->at<uint32_t>(H->off_stats), sizeof(sg::CallStats) / 4, 0u, st), "fill kernel");
     SG_HIP(sg::launch_fill_u32(err, 1, 0u, st), "fill kernel");
     if (!H->h_qitems.empty())
@@ -3348,6 +3352,7 @@ sg_status bind_impl(sg_handle H, void* dev_ptr, uint64_t bytes, void* hip_stream
     H->stats_zero = false;
     std::fill(H->started.begin(), H->started.end(), 0);
     H->e_pending = false;
+    H->err_clean = false;
     H->e_deferred.assign(H->insts.size(), 0);
     int dev_id = 0, cus = 0;
     if (hipGetDevice(&dev_id) == hipSuccess &&
@@ -3715,6 +3720,7 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
     if (H->err_check) SG_HIP(out.copy(herr, H->at<uint32_t>(H->off_err), sizeof herr, st), "error flag copy");
     SG_HIP(hipStreamSynchronize(st), "stream sync");
     out.finish();
+    if (H->err_check) H->err_clean = !(herr[0] | herr[1] | herr[2]);
     if (herr[0])
         return fail(SG_EDEVICE, "lattice tile kernel: a neighbour wait timed out (replica state is undefined; start "
                                 "again with sg_init_spins)");

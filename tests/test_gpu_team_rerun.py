@@ -48,6 +48,12 @@ def _check(insts, rule, uc, runs, pending, schedule, polls):
     compare(h, insts, ref)
     assert (s["attempts"], s["flips"]) == expected_stats(insts, before, ref)
     assert s["n_unconverged"] == (sum(int((st.converged == 0).sum()) for st in ref) if uc else 0)
+    # the flags of that call do not outlive it
+    h.tune("team_polls", 1 << 22)
+    for _ in range(2):
+        h.init_spins(3)
+        h.run_sweeps(seed=3, rule=rule, max_sweeps=2, until_converged=False, schedule=schedule)
+        assert h.query("last_team_reruns") == 0
     h.free()
 
 
