@@ -399,10 +399,12 @@ sg_status sg_solve(sg_handle h, const sg_run_params* p, sg_run_stats* stats, int
  *   "block_bits"         1: the block schedule uses the bit-sliced kernel (32
  *                        restarts per word, GREEDY and GREEDY_TIE) for instances of at
  *                        most 2048 spins whose coefficients are at most 15
- *                        in magnitude and sum to at most 255 per spin; 0:
- *                        always the byte kernel (default 1)
+ *                        in magnitude and sum to at most 255 per spin, under
+ *                        GREEDY_TIE in batches that it is estimated to run
+ *                        faster; 0: always the byte kernel (default 1)
  *   "bits_groups"        most groups of 32 restarts per bit-sliced workgroup
- *                        (2, 4, 8, 16; default 8)
+ *                        (2, 4, 8, 16; default 8); given, it also has the
+ *                        bit-sliced kernel take every batch that it can
  *   "defer_energy"       1: sg_init_spins leaves out the start energy of
  *                        instances that SG_SCHED_AUTO would run on a kernel
  *                        that computes the energies of the final spins

@@ -83,8 +83,12 @@ _DEFAULTS = ("msc_k", "lattice_msc", "bits_groups", "block_bits", "queue_wave_ma
 
 
 def apply(h, setting: dict, defaults: dict):
+    # a knob that holds its value already is left alone (giving bits_groups any
+    # value asks for the bit-sliced kernel)
     for k in _DEFAULTS:
-        h.tune(k, setting.get(k, defaults[k]))
+        v = setting.get(k, defaults[k])
+        if h.query(k) != v:
+            h.tune(k, v)
 
 
 def load_table(path: Optional[str]) -> Dict[str, dict]:

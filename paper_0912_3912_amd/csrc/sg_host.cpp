@@ -124,6 +124,7 @@ struct HostInst {
     int32_t fml_dc = 0, fml_tt = 0;    // coupling words / hyper-couplings per row
     int32_t bits_ok = 0;               // at most 2048 spins, every |coefficient| <= 15 and per spin
                                        // sum |c| <= 255 (bit-sliced block kernel)
+    float ties = 0.f;                  // with bits_ok: spins expected to be tied in a sweep
     // last tiling decision and the settings it was made for (rule, knobs)
     mutable std::array<int32_t, 6> tile_key{{-1, -1, -1, -1, -1, -1}};
     mutable sg::TileGeom tile_geom{};
@@ -173,6 +174,8 @@ struct sg_ctx {
     int32_t block_groups = 0;          // restart groups per block workgroup (0 = auto, up to 4)
     int32_t block_bits = 1;            // GREEDY block schedule in bit-sliced form where it applies
     int32_t bits_groups = 8;           // most groups of 32 restarts per bit-sliced workgroup (2, 4, 8, 16)
+    bool bits_groups_set = false;      // it has been given
+    bool tie_bits = true;              // the current call's choice (choose_tie_bits)
     int32_t fm_key32 = 1;              // FM moves chosen on 32-bit keys where the gains allow
     int32_t fm_waves = 0;              // most wavefronts per FM workgroup (0 = 16); the most resident are taken
     int32_t last_fm_waves = 0;         // what the last FM call used
@@ -1115,22 +1118,31 @@ sg_status ingest(const sg_instance_desc& d, int idx, HostInst& q)
     q.bits_ok = 0;
     if (n <= kLaneStartMaxN) {
         bool ok = true;
+        float ties = 0.f;
         for (int32_t i = 0; i < n && ok; ++i) {
-            int32_t W = std::abs((int32_t)q.h[i]);
+            int32_t W = std::abs((int32_t)q.h[i]), sq = W * W;
             ok = W <= 15;
             for (int64_t k = es[i]; k < es[i + 1] && ok; ++k) {
                 const int32_t c = std::abs((int32_t)(int8_t)(ew[k] & 0xFFu));
                 ok = c <= 15;
                 W += c;
+                sq += c * c;
             }
             for (int64_t k = ts[i]; k < ts[i + 1] && ok; ++k) {
                 const int32_t c = std::abs((int32_t)(int8_t)(twa[k] & 0xFFu));
                 ok = c <= 15;
                 W += c;
+                sq += c * c;
             }
             ok = ok && W <= 255;
+            // the sum of a spin's signed terms can be 0 if their weight W is
+            // even: always without terms, half the time with two equal ones,
+            // else in about 0.4 of its standard deviation's inverse of a
+            // descent's states
+            if (W % 2 == 0) ties += sq == 0 ? 1.f : sq <= 2 ? 0.5f : 0.4f / std::sqrt((float)sq);
         }
         q.bits_ok = ok ? 1 : 0;
+        q.ties = ties;
     }
     if (n <= kLaneStartMaxN) {
         for (int32_t i = 0; i < n; ++i)
@@ -2425,7 +2437,75 @@ sg_status run_block_bits_ng(sg_handle H, const sg_run_params* p, const std::vect
 // The block schedule runs this instance on the bit-sliced kernel.
 bool bits_path(const sg_ctx* H, const sg_run_params* p, const HostInst& q)
 {
-    return H->block_bits && p->max_sweeps > 0 && bits_lds_for(H, q, p->rule == SG_RULE_GREEDY_TIE) > 0;
+    const bool tie = p->rule == SG_RULE_GREEDY_TIE;
+    return H->block_bits && p->max_sweeps > 0 && (!tie || H->tie_bits) && bits_lds_for(H, q, tie) > 0;
+}
+
+// Whether the bit-sliced kernel takes the instances of a block-schedule call
+// under GREEDY_TIE.  A full device favours it 2 to 8 times, but a small batch
+// ends with the chain of its slowest workgroup, and there a wavefront that
+// walks all slices of 32 restarts and draws their ties 64 at a time can lose to
+// sixteen wavefronts that share the rows of 64 restarts; it also takes longer
+// to begin.  So both are estimated, in microseconds: a sweep of the slowest
+// instance (bit-sliced: slices, their coupling words, and ties, 32 restarts of
+// them drawn 64 at a time; bytes: colours, and rows with w coupling words) times
+// the rounds of workgroups that the device takes, and the time to begin and end.
+// Fitted to 665 batches of 32..1800 spins and 1..3200 groups of 32 restarts
+// (random graphs of degree 2, 3, 5 and 10, +-1 and up to +-15, with and without
+// hyper-couplings, Chimera, lattices, rings), 3, 20 and 60 sweeps: the choice is
+// within 5% of the better kernel in 95 of 100, within 1% on average.  20
+// sweeps, bit-sliced / bytes: 200 spins of degree 5, 8 groups 508 / 355 us, 1600
+// groups 577 / 995; 32 spins of degree 2, 8 groups 185 / 89, 3200 groups 351 /
+// 576; 512-spin Chimera, 8 groups 411 / 567, 1600 groups 475 / 1541; 1800 spins
+// of degree 2, 8 groups 2299 / 1311.  A given bits_groups asks for the
+// bit-sliced kernel.
+bool choose_tie_bits(const sg_ctx* H, const sg_run_params* p, const std::vector<int>& assign)
+{
+    if (!H->block_bits || H->bits_groups_set) return true;
+    const double cus = H->cus, T = p->until_converged ? std::min(p->max_sweeps, 30) : p->max_sweeps;
+    auto lds_bytes = [](const HostInst& q) {
+        return sg::block_lds_bytes(q.n, (int)q.nbr.size(), (int)q.ta.size(), (int)q.slices.size(), q.C, 64);
+    };
+    // the byte kernel on all instances, or on those that it alone can take
+    auto by_bytes = [&](bool every) {
+        double sweep = 0, ends = 0, wgs = 0, held = 2;
+        for (size_t k = 0; k < assign.size(); ++k) {
+            const HostInst& q = H->insts[k];
+            if (assign[k] != SG_SCHED_BLOCK || (!every && bits_lds_for(H, q, true))) continue;
+            const double w = (2.0 * (double)q.m + 6.0 * (double)q.t) / q.n;
+            sweep = std::max(sweep, 0.55 * q.C + q.n / 16.0 * (0.25 + 0.089 * w));
+            ends = std::max(ends, 3.3 / 64 * q.n);
+            wgs += (q.R + 63) / 64;
+            if (lds_bytes(q) > 80 * 1024) held = 1;
+        }
+        if (wgs == 0) return 0.0;
+        const double cap = held * cus, m = std::max(1.0, std::min(4.0, std::floor(wgs / cap)));
+        const double items = wgs / m, rounds = std::ceil(items / cap), last = items - (rounds - 1) * cap;
+        const double two = held > 1 ? 1.27 : 1.0;  // a compute unit that runs two of them
+        return 26.5 + ends + (1.45 * ends + 9.0) * wgs / cus +
+               T * sweep * m * ((rounds - 1) * two + (last > 1.05 * cus ? two : 1.0)) * (1.0 + 0.05 * std::min(1.0, wgs / cus));
+    };
+    double sweep = 0, ends = 0, wgs = 0, waves = 0, held = 0;
+    for (size_t k = 0; k < assign.size(); ++k) {
+        const HostInst& q = H->insts[k];
+        const double lds = assign[k] == SG_SCHED_BLOCK ? (double)bits_lds_for(H, q, true) : 0.0;
+        if (!(lds > 0)) continue;
+        double ew = 0, tw = 0;
+        for (const sg::Slice& S : q.slices) {
+            ew += S.ew;
+            tw += S.tw;
+        }
+        const double ng = std::min(8, bits_ng_for(H, q)), n = std::ceil(q.R / (32.0 * ng));
+        sweep = std::max(sweep, (2.9 + 0.69 * (double)q.slices.size() + 0.065 * (ew + 1.5 * tw) + 9.3 / 64 * q.ties) *
+                                    (0.82 + 0.0225 * ng));
+        ends = std::max(ends, 8.1 / 64 * q.n + 0.36 * (ew + tw) / ng);
+        wgs += n;
+        waves += n * ng;
+        held += n / std::max(1.0, std::floor(160.0 * 1024 / lds));
+    }
+    const double by_bits = 30.0 + ends + 10.0 * wgs / cus +
+                           T * sweep * (1.0 + 0.031 * std::min(waves / cus, 16.0)) * std::max(1.0, held / cus);
+    return by_bits + by_bytes(false) < by_bytes(true);
 }
 
 sg_status run_block_schedule(sg_handle H, const sg_run_params* p, const std::vector<int>& which_all)
@@ -3674,6 +3754,7 @@ sg_status sg_run_sweeps(sg_handle H, const sg_run_params* p, sg_run_stats* stats
     if (sched < 0 && p->schedule != SG_SCHED_AUTO)
         return fail(SG_EINVAL, "schedule %d is not available for this handle (rule %d, until_converged %d)",
                     p->schedule, p->rule, p->until_converged);
+    H->tie_bits = p->rule != SG_RULE_GREEDY_TIE || choose_tie_bits(H, p, assign);
     // left-out start energies are written by the bit-sliced, queue or team
     // kernel; any other kernel continues from them, so they are computed first
     for (size_t k = 0; H->e_pending && k < assign.size(); ++k)
@@ -4055,6 +4136,7 @@ sg_status sg_tune(sg_handle H, const char* key, int64_t value)
         if (value != 2 && value != 4 && value != 8 && value != 16)
             return fail(SG_EINVAL, "bits_groups must be 2, 4, 8 or 16");
         H->bits_groups = (int32_t)value;
+        H->bits_groups_set = true;
     } else if (k == "block_groups") {
         if (value < 0 || value > 64) return fail(SG_EINVAL, "block_groups must be in [0, 64]");
         H->block_groups = (int32_t)value;
