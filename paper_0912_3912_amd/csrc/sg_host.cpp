@@ -1905,7 +1905,27 @@ sg_status run_phase_schedule(sg_handle H, const sg_run_params* p, const std::vec
 //   60000         272 / 317    181 / 555    104 / 214 (30)
 //   500000                                   136 / 284 (245)
 // With triples, 20000: 539 / 810, 268 / 501, 298 / 540 (7).  Teams of a twelfth
-// of the largest colour's slices are within 10% of the best.
+// of the largest colour's slices are within 10% of the best.  A call of few
+// phases does not earn back what a team costs to begin (the cooperative launch,
+// every member's copy of the spins): see team_pays.
+//
+// team_pays: microseconds of the call, against per-phase launches.  A team
+// begins 25 + 0.04 per 1000 spins + 0.3 per replica later, and saves 1.8 + 0.001
+// per 1000 spins, + 0.0028 per 1000 spins of every further replica, in a phase
+// (eight sweeps of them, or max_sweeps, until converged) and the per-phase
+// launches' check of the stopping rule, 45.  One sweep / five of a 3-regular
+// graph, team and per-phase launches: 60000 spins 79, 61 / 109, 121; 600000 102,
+// 61 / 147, 150; 60000, 31 replicas 88, 74 / 131, 201; 600000, 8 replicas 119,
+// 120 / 206, 438; a graph with triples (10 colours), 60000 spins 96, 89 / 186,
+// 291.  (One workgroup per replica is the faster from the first sweep: 6000
+// spins 51, 59 / 65, 122.)
+bool team_pays(const HostInst& q, const sg_run_params* p)
+{
+    const double phases = (double)q.C * (p->until_converged ? std::min(p->max_sweeps, 8) : p->max_sweeps);
+    const double save = phases * (1.8 + 1e-6 * q.n + 2.8e-6 * q.n * (q.R - 1)) + (p->until_converged && p->max_sweeps > 2 ? 45.0 : 0.0);
+    return save > 25.0 + 4e-5 * q.n + 0.3 * q.R;
+}
+
 int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
 {
     if (H->team_wgs < 0 || p->schedule != SG_SCHED_AUTO || p->max_sweeps <= 0 || q.R > kTeamMaxR || !can_team(q)) return 0;
@@ -1915,6 +1935,7 @@ int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
         int32_t& most = q.team_most[p->rule == SG_RULE_GREEDY_TIE];
         if (most < 0) most = sg::team_max_blocks(q.n, p->rule == SG_RULE_GREEDY_TIE, q.t > 0, q.max_ew);
         g = q.off_team == UINT64_MAX ? 1 : std::min(g, most / q.R);
+        if (g > 1 && H->team_wgs == 0 && !team_pays(q, p)) return 0;
     }
     if (g >= 2 || ns <= kTeamAlone || H->team_wgs == 1) return std::max(g, 1);
     return 0;  // large and not split: the per-phase launches use the whole device
@@ -3228,7 +3249,7 @@ bool team_bound(const sg_ctx* H, const HostInst& q)
 {
     sg_run_params p{};
     p.rule = SG_RULE_GREEDY;
-    p.max_sweeps = 1;
+    p.max_sweeps = 1000;
     p.until_converged = 1;
     p.schedule = SG_SCHED_AUTO;
     return !q.lat_ok && !H->fields_ws && !H->auto_graph && !(q.R >= H->block_min_restarts && can_block(H, q)) &&

@@ -57,7 +57,7 @@ def _check(insts, rule, uc, runs, pending, schedule, polls):
     h.free()
 
 
-CASES = [(GREEDY, True, [1000], True), (GREEDY, True, [1000], False), (GREEDY, True, [2, 2], True),
+CASES = [(GREEDY, True, [1000], True), (GREEDY, True, [1000], False), (GREEDY, True, [3], True),
          (TIE, False, [5], False), (TIE, True, [2, 3, 9], False)]
 
 
