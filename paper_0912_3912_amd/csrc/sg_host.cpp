@@ -2596,64 +2596,95 @@ sg_status run_block_schedule(sg_handle H, const sg_run_params* p, const std::vec
 }
 
 // Teams for the first items of the sorted queue, listed per workgroup in
-// h_qteams; returns the bytes of words they take.  A workgroup runs an item
-// of n spins in about n + 3000 units of time (11 ns) and a team of g in
-// 1.28 n / g + 25000 (bits instead of bytes; an exchange every phase): 100000
-// spins with triples take 1121 us alone, 742, 527 and 426 us in teams of 2, 4
-// and 8.  With the first k items in teams that end with the largest of the
-// others, the call takes that long, or the mean load of the workgroups and
-// three tenths for what an uneven queue leaves idle; k minimises it, if it
-// saves a twelfth.  Kernel times without teams / with: 96 graphs up to 100000
-// spins, 8 restarts 1076 / 985 us (32 items in teams); 82 graphs up to 81550,
-// one restart 762 / 504 us (10); 38 graphs up to 83236, 8 restarts, 20 sweeps
-// under TIE 1891 / 1214 us (24).
+// h_qteams; returns the bytes of words they take.  Microseconds of a sweep of an
+// item of n spins and C colours: a workgroup takes A n + 0.9 C, A = 0.00012 +
+// 0.000052 per coupling and 4.9 times that per hyper-coupling of a spin, 0.00012
+// more under TIE; sixteen wavefront items the same together; a team of g takes
+// (1.3 A + 0.00015) n / g + 2 C (bits instead of bytes; an exchange every
+// phase).  (100000 spins, 9 colours, 50 sweeps under TIE: 97.9 alone, 83.5, 50.8
+// and 37.2 in teams of 2, 4 and 8; 3-regular, 4 colours: 49.1, 44.3, 26.4,
+// 16.6.)  With the first k items in teams that end with the largest of the
+// others, a sweep takes that long, or the mean load of the workgroups and three
+// tenths for what an uneven queue leaves idle; and k teams cost the call 20 +
+// 1.2 k to begin.  k saves the most, in max_sweeps sweeps or the 0.7 ln n or so
+// until convergence (random graphs of degree 3 to 12: 4 to 6 for 200 spins, 6
+// to 12 for 100000), and at least a twelfth.  Kernel times with / without
+// teams: 48 graphs up to 101713 spins, 6 restarts, to convergence 701 / 1014 us,
+// 20 sweeps under TIE 1246 / 2109; 16 graphs up to 77277 spins 378 / 681, 854 /
+// 1653; 48 graphs up to 75186, 6 restarts, one sweep 198 / 127 (not taken), 20
+// sweeps 1432 / 1631.
 uint64_t queue_teams(sg_handle H, const sg_run_params* p, int n_big, int grid, size_t lds, sg::QueueTeams& teams)
 {
     if (H->team_wgs < 0 || !H->qteam_bytes || p->max_sweeps <= 0 || n_big < 1 || grid < 64 || H->queue_grid > 0) return 0;
     auto inst = [&](int k) -> const HostInst& { return H->insts[(size_t)H->h_qitems[(size_t)k].inst]; };
-    auto alone = [&](int k) { return inst(k).n + 3000.0; };
     if (!queue_team_fits(inst(0))) return 0;
-    double rest = 0;  // load of the items not in teams
-    for (const sg::QueueItem& it : H->h_qitems) rest += H->insts[(size_t)it.inst].n;
+    struct Cost {
+        double alone, shared, swap;  // on one workgroup; by a team's members together; of every member
+    };
+    auto cost = [&](const HostInst& q) {
+        const double sweeps = p->until_converged ? std::min<double>(p->max_sweeps, 0.7 * std::log((double)q.n)) : p->max_sweeps;
+        const double A = 1.2e-4 + 5.2e-5 * (2.0 * (double)q.m + 14.7 * (double)q.t) / q.n +
+                         (p->rule == SG_RULE_GREEDY_TIE ? 1.2e-4 : 0.0);
+        return Cost{sweeps * (A * q.n + 0.9 * q.C), sweeps * (1.3 * A + 1.5e-4) * q.n, sweeps * 2.0 * q.C};
+    };
+    std::vector<Cost> c;  // of the items that may be in teams
+    std::vector<double> longest(kQueueTeams + 1, 0.0);  // of item k and those after it, alone
+    double rest = 0, last = 0;                          // load of the items not in teams
+    for (int k = 0, of = -1; k < (int)H->h_qitems.size(); ++k) {
+        if (H->h_qitems[(size_t)k].inst != of || k < kQueueTeams || k == n_big) {
+            of = H->h_qitems[(size_t)k].inst;
+            const Cost x = cost(inst(k));
+            if (k < kQueueTeams) c.push_back(x);
+            last = x.alone / (k < n_big ? 1 : 16);
+            double& l = longest[(size_t)std::min(k, kQueueTeams)];
+            l = std::max(l, x.alone);
+        }
+        rest += last;
+    }
+    for (int k = kQueueTeams; k > 0; --k) longest[(size_t)k - 1] = std::max(longest[(size_t)k - 1], longest[(size_t)k]);
     const int most = std::min(grid * 9 / 10, kQueueTeamWgs);
-    const double base = std::max(alone(0), rest / grid);
-    double best = base * 11 / 12;
+    const double base = std::max(longest[0], rest / grid);
+    double best = 0, least = 0;  // saved; the shortest that a team may take
     int best_k = 0;
     uint64_t bytes = 0, best_bytes = 0;
-    auto size = [&](int i, double end) { return std::max(2, (int)std::ceil(1.28 * inst(i).n / (end - 25000.0))); };
+    std::vector<int> g, best_g;
     for (int k = 1; k <= kQueueTeams && k < n_big; ++k) {
         if (!queue_team_fits(inst(k - 1))) break;
         bytes += queue_team_bytes(inst(k - 1));
         if (bytes > H->qteam_bytes) break;
-        rest -= inst(k - 1).n;
-        const double end = std::max(alone(k), 40000.0);
+        const Cost& x = c[(size_t)k - 1];
+        rest -= x.alone;
+        least = std::max(least, x.swap * (1.0 + 2.5 / inst(k - 1).C));  // (5 us a sweep more)
+        const double end = std::max(longest[(size_t)k], least);
+        if (base - end < 20.0 + 1.2 * k + best) continue;
         int wgs = 0;
         double load = rest;
+        g.clear();
         for (int i = 0; i < k; ++i) {
-            const int g = size(i, end);
-            wgs += g;
-            load += 1.28 * inst(i).n + 25000.0 * g;
+            g.push_back(std::max(2, (int)std::ceil(c[(size_t)i].shared / (end - c[(size_t)i].swap))));
+            wgs += g.back();
+            load += c[(size_t)i].shared + c[(size_t)i].swap * g.back();
         }
         if (wgs > most) break;
-        const double t = std::max(end, 1.3 * load / grid);
-        if (t < best) {
-            best = t;
+        const double t = std::max(end, 1.3 * load / grid), saved = base - t - 20.0 - 1.2 * k;
+        if (t < base * 11 / 12 && saved > best) {
+            best = saved;
             best_k = k;
             best_bytes = bytes;
+            best_g = g;
         }
+        if (t > end) break;  // more teams only add to the load
     }
     if (!best_k || grid > sg::queue_max_blocks(lds)) return 0;
     H->h_qteams.clear();
-    const double end = std::max(alone(best_k), 40000.0);
     uint32_t at = 0;
     for (int i = 0; i < best_k; ++i) {
-        const int g = size(i, end);
         const sg::QueueItem it = H->h_qitems[(size_t)i];
-        for (int m = 0; m < g; ++m) {
+        for (int m = 0; m < best_g[(size_t)i]; ++m) {
             H->h_qteams.push_back(it);
-            H->h_qteams.push_back(sg::QueueItem{m | g << 16, (int32_t)at});
+            H->h_qteams.push_back(sg::QueueItem{m | best_g[(size_t)i] << 16, (int32_t)at});
         }
-        teams.nwg += g;
+        teams.nwg += best_g[(size_t)i];
         at += (uint32_t)(queue_team_bytes(inst(i)) / 32);
     }
     teams.n = best_k;
