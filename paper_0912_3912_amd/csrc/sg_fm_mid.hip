@@ -50,7 +50,7 @@ __host__ __device__ inline size_t mid_pad(int n) { return ((size_t)n + kLeaf - 1
 template <bool BYTES, int RL, bool TRI>
 struct MidPolicy {
     static constexpr int kRL = RL;
-    static constexpr bool kTri = TRI;
+    static constexpr bool kTri = TRI, kPlaced = false;
     static constexpr int32_t kNone = BYTES ? 0 : INT32_MIN, kBias = BYTES ? 128 : 0;
     mid_g32* rows;
     uint8_t* half;

@@ -49,7 +49,7 @@ __host__ __device__ inline size_t rows_wave_bytes(int n) { return 7 * rows_n64(n
 template <bool WIDE, bool TRI>
 struct RowsPolicy {
     static constexpr int kRL = 1;
-    static constexpr bool kTri = TRI;
+    static constexpr bool kTri = TRI, kPlaced = true;
     static constexpr int32_t kNone = INT32_MIN, kBias = 0;
     const uint32_t* cw;  // couplings
     const uint32_t* tw;  // hyper-couplings
