@@ -7,8 +7,8 @@
 //
 // Everything here is in external order, so that the largest key names its
 // spin directly.  Per instance a row table (FmbRows): per spin a word with
-// its field, then dc couplings and tt hyper-couplings, unused entries naming
-// the spin itself with coefficient zero:
+// its field, then dc couplings and tt hyper-couplings, unused ones with
+// coefficient zero (couplings name the spin itself):
 // in the packed form words partner << 8 | J & 255 and pairs (a << 8 | K &
 // 255, b), in the wide form (any int32 coefficient) pairs (partner, J) and
 // triples (a, b, K).  A move's terms are taken 64 at a time (a lane each).  Per

@@ -1109,37 +1109,38 @@ sg_status ingest(const sg_instance_desc& d, int idx, HostInst& q)
     q.eterm.clear();
     q.n_eh = q.n_ee = q.n_et = 0;
     q.max_w = 0;
-    for (int32_t i = 0; i < n; ++i) {
-        int64_t W = std::abs((int32_t)q.h[i]);
-        for (int64_t k = es[i]; k < es[i + 1]; ++k) W += std::abs((int32_t)(int8_t)(ew[k] & 0xFFu));
-        for (int64_t k = ts[i]; k < ts[i + 1]; ++k) W += std::abs((int32_t)(int8_t)(twa[k] & 0xFFu));
-        q.max_w = std::max(q.max_w, W);
-    }
     q.bits_ok = 0;
-    if (n <= kLaneStartMaxN) {
+    // the sum of a spin's signed terms can be 0 if their weight W is even: always
+    // without terms, half the time with two equal ones, else in about 0.4 of its
+    // standard deviation's inverse of a descent's states
+    static const std::vector<float> tied = [] {
+        std::vector<float> v(255 * 15 + 1);  // by the sum of squares of terms of at most 15 that sum to at most 255
+        for (size_t k = 0; k < v.size(); ++k) v[k] = k == 0 ? 1.f : k <= 2 ? 0.5f : 0.4f / std::sqrt((float)k);
+        return v;
+    }();
+    if (n > kLaneStartMaxN) {
+        for (int32_t i = 0; i < n; ++i) {
+            int64_t W = std::abs((int32_t)q.h[i]);
+            for (int64_t k = es[i]; k < es[i + 1]; ++k) W += std::abs((int32_t)(int8_t)(ew[k] & 0xFFu));
+            for (int64_t k = ts[i]; k < ts[i + 1]; ++k) W += std::abs((int32_t)(int8_t)(twa[k] & 0xFFu));
+            q.max_w = std::max(q.max_w, W);
+        }
+    } else {
         bool ok = true;
         float ties = 0.f;
-        for (int32_t i = 0; i < n && ok; ++i) {
-            int32_t W = std::abs((int32_t)q.h[i]), sq = W * W;
-            ok = W <= 15;
-            for (int64_t k = es[i]; k < es[i + 1] && ok; ++k) {
-                const int32_t c = std::abs((int32_t)(int8_t)(ew[k] & 0xFFu));
-                ok = c <= 15;
+        for (int32_t i = 0; i < n; ++i) {
+            int32_t W = std::abs((int32_t)q.h[i]), sq = W * W, most = W;
+            auto term = [&](uint32_t w) {
+                const int32_t c = std::abs((int32_t)(int8_t)(w & 0xFFu));
                 W += c;
                 sq += c * c;
-            }
-            for (int64_t k = ts[i]; k < ts[i + 1] && ok; ++k) {
-                const int32_t c = std::abs((int32_t)(int8_t)(twa[k] & 0xFFu));
-                ok = c <= 15;
-                W += c;
-                sq += c * c;
-            }
-            ok = ok && W <= 255;
-            // the sum of a spin's signed terms can be 0 if their weight W is
-            // even: always without terms, half the time with two equal ones,
-            // else in about 0.4 of its standard deviation's inverse of a
-            // descent's states
-            if (W % 2 == 0) ties += sq == 0 ? 1.f : sq <= 2 ? 0.5f : 0.4f / std::sqrt((float)sq);
+                most = std::max(most, c);
+            };
+            for (int64_t k = es[i]; k < es[i + 1]; ++k) term(ew[k]);
+            for (int64_t k = ts[i]; k < ts[i + 1]; ++k) term(twa[k]);
+            q.max_w = std::max<int64_t>(q.max_w, W);
+            ok = ok && most <= 15 && W <= 255;
+            if (ok && W % 2 == 0) ties += tied[(size_t)sq];
         }
         q.bits_ok = ok ? 1 : 0;
         q.ties = ties;
@@ -1365,31 +1366,18 @@ int32_t fmb_stride(const HostInst& q) { return q.wide ? 1 + 2 * q.fmb_dc + 3 * q
 
 // The large-instance pass kernel's rows (FmbRows): per spin in external order
 // its field, its nonzero couplings and hyper-couplings with partners in
-// external order, padded to q.fmb_dc and q.fmb_tt by entries that name the
-// spin itself with coefficient zero.
+// external order, padded to q.fmb_dc by couplings that name the spin itself
+// with coefficient zero and to q.fmb_tt by zeros.
 void build_fmb_rows(const HostInst& q, std::vector<uint32_t>& out)
 {
     const int32_t dc = q.fmb_dc, stride = fmb_stride(q);
-    out.resize((size_t)q.n * stride);
-    for (uint32_t e = 0; e < (uint32_t)q.n; ++e) {
-        uint32_t* row = out.data() + (size_t)e * stride;
-        const uint32_t self = q.wide ? e : e << 8;
-        uint32_t* end = row + 1 + (q.wide ? 2 : 1) * dc;
-        for (uint32_t* w = row + 1; w < end; w += q.wide ? 2 : 1) {
-            w[0] = self;
-            if (q.wide) w[1] = 0u;
-        }
-        for (uint32_t* w = end; w < row + stride; w += q.wide ? 3 : 2) {
-            w[0] = self;
-            w[1] = e;
-            if (q.wide) w[2] = 0u;
-        }
-    }
+    out.assign((size_t)q.n * stride, 0u);
     if (!q.wide) {
         for (const sg::Slice& S : q.slices)
             for (int32_t l = 0; l < S.rows; ++l) {
                 const int32_t i = (int32_t)S.row0 + l;
-                uint32_t* row = out.data() + (size_t)q.ext_of[(size_t)i] * stride;
+                const uint32_t e = q.ext_of[(size_t)i];
+                uint32_t* row = out.data() + (size_t)e * stride;
                 row[0] = (uint32_t)(uint8_t)q.h[(size_t)i];
                 int32_t c = 0, t = 0;
                 for (int32_t k = 0; k < S.ew; ++k) {
@@ -1404,13 +1392,14 @@ void build_fmb_rows(const HostInst& q, std::vector<uint32_t>& out)
                     row[2 + dc + 2 * t] = q.ext_of[b];
                     ++t;
                 }
+                for (; c < dc; ++c) row[1 + c] = e << 8;
             }
         return;
     }
     for (const sg::WSlice& S : q.w_slices)
         for (uint32_t l = 0; l < S.rows; ++l) {
-            const uint32_t i = S.row0 + l;
-            uint32_t* row = out.data() + (size_t)q.ext_of[i] * stride;
+            const uint32_t i = S.row0 + l, e = q.ext_of[i];
+            uint32_t* row = out.data() + (size_t)e * stride;
             row[0] = (uint32_t)q.w_h[i];
             int32_t c = 0, t = 0;
             for (uint32_t k = 0; k < S.ew; ++k) {
@@ -1429,6 +1418,7 @@ void build_fmb_rows(const HostInst& q, std::vector<uint32_t>& out)
                 t3[2] = (uint32_t)q.w_K[at];
                 ++t;
             }
+            for (; c < dc; ++c) row[1 + 2 * c] = e;
         }
 }
 

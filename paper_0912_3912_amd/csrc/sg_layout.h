@@ -156,7 +156,7 @@ struct InstTab {
 
 // Per-spin term rows in external order for the pass kernel of instances
 // beyond 4096 spins (sg_fm_mid.hip, sg_fm_big.hip): spin e's row is the stride
-// words from rows + e * stride, unused entries naming e with coefficient zero.  Packed form (wide = 0): a word
+// words from rows + e * stride, unused couplings naming e with coefficient zero.  Packed form (wide = 0): a word
 // with the field in its low byte (int8), dc coupling words (partner << 8 |
 // J & 255), tt hyper-coupling pairs (a << 8 | K & 255, b).  Wide form: the
 // field (int32), dc pairs (partner, J), tt triples (a, b, K).
