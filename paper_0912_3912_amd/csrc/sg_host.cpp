@@ -3605,12 +3605,26 @@ sg_status bind_impl(sg_handle H, void* dev_ptr, uint64_t bytes, void* hip_stream
             std::vector<sg::QueueItem> items;
             std::vector<uint32_t> rows;
             const int64_t at_once = std::min<int64_t>(H->fm_slots, H->fmb_reps);
+            // The kernels run one after the other.  Where one instance needs
+            // the device-memory kernel and all replicas run at once, that
+            // kernel takes the others beside it if that ends sooner than
+            // giving them a launch of their own (45000 spins, one instance in
+            // the wide form, one not: 455 ms in one launch, 525 in two).
+            int32_t n_lds = 0, n_mem = 0;
+            for (const HostInst& q : H->insts) {
+                if (q.off_fmb_rows == UINT64_MAX) continue;
+                int32_t& m = fm_big_class(q, at_once, H->cus) < 2 ? n_lds : n_mem;
+                m = std::max(m, q.n);
+            }
+            const bool one = n_lds && n_mem && H->fmb_reps <= std::min<int64_t>(at_once, 4 * H->cus) &&
+                             4.1 * std::max(n_lds, n_mem) < 4.1 * n_mem + 0.7 * n_lds;
+            auto kind = [&](const HostInst& q) { return one ? 2 : fm_big_class(q, at_once, H->cus); };
             for (int c = 0; c < 3; ++c) {
                 H->fmb_class_reps[c] = 0;
                 H->fmb_class_nmax[c] = H->fmb_class_tri[c] = 0;
                 for (size_t k = 0; k < H->insts.size(); ++k) {
                     const HostInst& q = H->insts[k];
-                    if (q.off_fmb_rows == UINT64_MAX || fm_big_class(q, at_once, H->cus) != c) continue;
+                    if (q.off_fmb_rows == UINT64_MAX || kind(q) != c) continue;
                     H->fmb_class_reps[c] += q.R;
                     H->fmb_class_nmax[c] = std::max(H->fmb_class_nmax[c], q.n);
                     H->fmb_class_tri[c] |= q.t > 0 ? 1 : 0;

@@ -1,0 +1,37 @@
+"""Pass-based search on handles whose instances need different kernels: few
+replicas share the launch that the largest or densest needs, where a launch of
+their own would only come on top of it; equal to the oracle."""
+import pytest
+
+import instances as gen
+import oracle
+from parity import compare, log
+
+pytestmark = pytest.mark.gpu
+
+FM = 2
+
+
+def _run(insts, knobs, passes, seed=5):
+    import paper_0912_3912_amd as sg
+    h = sg.load_instance(insts)
+    for k, v in knobs.items():
+        h.tune(k, v)
+    h.bind()
+    h.init_spins(seed)
+    h.run_sweeps(seed=seed, rule=FM, max_sweeps=passes, until_converged=False)
+    launches = h.query("hot_launches")
+    compare(h, insts, [oracle.fm(i, seed=seed, max_passes=passes, until_converged=False, threads=8)[0] for i in insts])
+    h.free()
+    return launches
+
+
+@pytest.mark.parametrize("sizes,launches", [((39300, 6000), 1), ((39300, 39200), 1), ((6000, 5000), 2)])
+def test_beyond_4096(gpu, sizes, launches):
+    """The first instance in the wide form (beyond 39168 spins only the
+    device-memory kernel takes it), the second not."""
+    wide = gen.erdos_renyi_triples(sizes[0], seed=1, mean_degree=3, triples_per_spin=0.1, instance_id=1)
+    insts = [wide.replace(J=wide.J * 1000),
+             gen.erdos_renyi_triples(sizes[1], seed=2, mean_degree=3, triples_per_spin=0.1, instance_id=2)]
+    log(f"pass kernels beyond 4096 spins: {sizes}")
+    assert _run(insts, {"fm_slots": 4}, 1) == launches
