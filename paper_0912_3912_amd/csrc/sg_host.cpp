@@ -2924,23 +2924,32 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
         fm_row_widths(q, dc, tt);
         return sg::fm_rows_lds_bytes(q.n, dc, tt, q.wide != 0, 1) <= kFmRowsLds;
     };
-    // The two packed kernels run one after the other.  A row-table move takes
-    // about an eighth of the other kernel's time, and few replicas cost the
-    // chain of their largest instance: with instances left to the other
-    // kernel, a row-table launch beside it pays if its largest instance is
-    // the larger, or if its replicas fill the device (30 instances of
-    // 200..1070 spins, the densest too large: 48 ms in two launches, 38 ms in
-    // one)
+    // The two packed kernels run one after the other, and few replicas cost the
+    // chain of the slowest instance: its spins times a move, about 0.4 us with
+    // row tables (0.8 in rows beyond 64 couplings or with hyper-couplings) and
+    // 0.008 per word of a row, 1.2 us, 1.15 per 1000 spins and 0.012 per word on
+    // the other kernel.  With instances left to the latter, a row-table launch
+    // beside it pays if the two chains end sooner than one launch of all, or if
+    // its replicas fill the device (12 instances of 100..760 spins beside a
+    // complete graph of 400: 10.3 ms in two launches, 9.0 in one; 30 of
+    // 200..1070 spins, the densest too large: 48 and 38 ms)
     {
-        int32_t nr = 0, no = 0;
+        double with = 0.0, without = 0.0, rest = 0.0;  // chains: row tables, the same without, those left
         int64_t reps = 0;
         for (const HostInst& q : H->insts)
             if (!q.wide && q.n <= kFmMaxN && !on_lanes(q)) {
-                const bool r = on_rows(q);
-                (r ? nr : no) = std::max(r ? nr : no, q.n);
-                reps += r ? q.R : 0;
+                int32_t dc, tt;
+                fm_row_widths(q, dc, tt);
+                const double other = q.n * (1.2 + 1.15e-3 * q.n + 0.012 * (dc + 2 * tt));
+                if (!on_rows(q)) {
+                    rest = std::max(rest, other);
+                    continue;
+                }
+                with = std::max(with, q.n * ((dc > 64 || tt ? 0.8 : 0.4) + 0.008 * (dc + 2 * tt)));
+                without = std::max(without, other);
+                reps += q.R;
             }
-        rows = no == 0 || (int64_t)nr * 8 > (int64_t)no * 9 || reps > 16 * H->cus;
+        rows = rest == 0.0 || with + rest < std::max(without, rest) || reps > 16 * H->cus;
     }
     const int most_waves = H->fm_waves ? std::min(H->fm_waves, 16) : 16;
     int64_t big_reps = 0;

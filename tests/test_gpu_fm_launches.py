@@ -35,3 +35,14 @@ def test_beyond_4096(gpu, sizes, launches):
              gen.erdos_renyi_triples(sizes[1], seed=2, mean_degree=3, triples_per_spin=0.1, instance_id=2)]
     log(f"pass kernels beyond 4096 spins: {sizes}")
     assert _run(insts, {"fm_slots": 4}, 1) == launches
+
+
+@pytest.mark.parametrize("dense,sparse,launches", [(400, 300, 1), (400, 3000, 2), (0, 3000, 1)])
+def test_up_to_4096(gpu, dense, sparse, launches):
+    """A complete graph too large for row tables beside sparse graphs: these get
+    a row-table launch of their own only if they are much the longer."""
+    insts = [gen.lattice((sparse // 50, 50), seed=k, instance_id=k, j_values=(-90, 80), restarts=2) for k in range(2)]
+    if dense:
+        insts.append(gen.complete_graph(dense, seed=1).replace(instance_id=9, restarts=2))
+    log(f"pass kernels up to 4096 spins: complete graph of {dense} beside {sparse}")
+    assert _run(insts, {"fm_lanes": 0}, 2) == launches
