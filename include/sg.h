@@ -515,6 +515,8 @@ sg_status sg_tune(sg_handle h, const char* key, int64_t value);
  * wavefront), "last_fm_big" (its replicas on the kernel for instances beyond
  * 4096 spins), "energy_pending" (1 while start energies
  * left out by sg_init_spins are not yet computed), "last_queue_grid",
+ * "may_team" (1 when SG_SCHED_AUTO may split a replica of the handle over
+ * workgroups that wait for one another, see "team_wgs"; bound handles),
  * "last_queue_teams" (queue items the last call ran on several workgroups),
  * "last_team" (workgroups per replica of the last such launch of the last
  * call, 0 for none), "last_team_reruns" (replicas that call ran again because

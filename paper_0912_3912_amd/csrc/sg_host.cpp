@@ -3286,6 +3286,21 @@ bool team_bound(const sg_ctx* H, const HostInst& q)
            team_groups(H, q, &p) > 0;
 }
 
+// Some colour-sweep run of SG_SCHED_AUTO would split a replica over several
+// workgroups (the queue schedule's teams included).
+bool may_team(const sg_ctx* H)
+{
+    sg_run_params p{};
+    p.max_sweeps = INT32_MAX;
+    p.schedule = SG_SCHED_AUTO;
+    for (const HostInst& q : H->insts)
+        for (int rule : {SG_RULE_GREEDY, SG_RULE_GREEDY_TIE}) {
+            p.rule = rule;
+            if (team_groups(H, q, &p) > 1) return true;
+        }
+    return H->team_wgs >= 0 && H->qteam_bytes > 0;
+}
+
 bool defer_unit_energy(const sg_ctx* H)
 {
     if (!H->defer_energy || H->h_esegs.empty()) return false;
@@ -4283,6 +4298,7 @@ sg_status sg_query(sg_handle H, const char* key, int64_t* value)
     else if (k == "queue_grid") *value = H->queue_grid;
     else if (k == "team_wgs") *value = H->team_wgs;
     else if (k == "team_polls") *value = H->team_polls;
+    else if (k == "may_team") *value = may_team(H) ? 1 : 0;
     else if (k == "last_team") *value = H->last_team;
     else if (k == "last_team_reruns") *value = H->last_team_reruns;
     else if (k == "queue_min_items") *value = H->queue_min_items;

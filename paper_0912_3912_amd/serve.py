@@ -203,8 +203,8 @@ class Server:
         self.scratch = None
         self.shared_launches = 0
         self.shared_batch_sizes: List[int] = []
-        # Large lattices and large irregular graphs use co-resident launches;
-        # two such grids must not be resident at once (each could
+        # Large lattices and replicas split over workgroups use co-resident
+        # launches; two such grids must not be resident at once (each could
         # hold CUs the other needs), so they take turns.
         self.coop_lock = threading.Lock()
         self.loop_error: Optional[BaseException] = None
@@ -454,9 +454,12 @@ class Server:
             info = h.info(0)
             # a lattice beyond one workgroup runs on the co-resident tile launch
             # (fixed budgets, and GREEDY until converged on the bit-plane
-            # kernel), a larger irregular graph on a co-resident launch of
-            # several workgroups per replica
-            coop = info["n"] > (h.query("lattice_wg_max_n") if info["lattice"] else 4096)
+            # kernel), and the handle says whether a colour-sweep run may split
+            # a replica over several workgroups
+            if info["lattice"]:
+                coop = info["n"] > h.query("lattice_wg_max_n")
+            else:
+                coop = req.rule != self.sg.FM and h.query("may_team") != 0
             if coop:
                 with self.coop_lock:
                     stats = h.run_sweeps(seed=req.seed, rule=req.rule, max_sweeps=req.max_sweeps,
