@@ -513,7 +513,8 @@ sg_status sg_tune(sg_handle h, const char* key, int64_t value);
  * workgroup, 0 when every replica ran one per lane), "last_fm_lanes" (its
  * replicas run one per lane), "last_fm_lane_nr" (its restarts per lane-kernel
  * wavefront), "last_fm_big" (its replicas on the kernel for instances beyond
- * 4096 spins), "energy_pending" (1 while start energies
+ * 4096 spins), "last_dense_tables" (instances that the last call on a dense
+ * handle searched by a table of all energies), "energy_pending" (1 while start energies
  * left out by sg_init_spins are not yet computed), "last_queue_grid",
  * "may_team" (1 when SG_SCHED_AUTO may split a replica of the handle over
  * workgroups that wait for one another, see "team_wgs"; bound handles),

@@ -42,13 +42,6 @@ __device__ __forceinline__ long long dense_term(uint64_t state, uint64_t m, long
     return (__popcll(state & m) & 1) ? -c : c;
 }
 
-__device__ __forceinline__ long long dense_energy_of(const DenseTab& D, uint64_t state)
-{
-    long long E = 0;
-    for (int t = 0; t < D.nterms; ++t) E -= dense_term(state, D.tmask[t], D.tcoef[t]);
-    return E;
-}
-
 // f_i = sum over terms holding i of coef * (product of the other members)
 __device__ __forceinline__ long long dense_field(const DenseTab& D, uint64_t state, int i)
 {

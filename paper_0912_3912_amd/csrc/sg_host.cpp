@@ -228,6 +228,7 @@ struct sg_ctx {
     // energy tables of the pass-based search: how many the workspace holds at
     // once, the largest instance that uses one, where they stand
     int32_t dense_tables = 0, dense_table_n = 0;
+    int32_t last_dense_tables = 0;  // instances that the last call ran by one
     uint64_t off_dense_table = 0;
     // one replica's spins in external order on their way out (instances beyond
     // the pinned buffer): the largest that fits, 0 for none
@@ -1554,35 +1555,44 @@ uint64_t queue_team_bytes(const HostInst& q) { return sg::queue_team_bytes(q.n, 
 
 // Energy tables (sg_dense.hip) for the pass-based search of a dense handle:
 // instances of at most kDenseTableMaxN spins share room for up to 32 MiB of
-// tables and run in rounds of as many instances as that holds.  A step takes
-// a round about 1.5 us and its table and launches about 20 us, on three passes
-// or so; without a table a step takes about 0.45 us per term of the picked
-// spin, for up to ~3000 wavefronts of 64 replicas at once (12 per compute
-// unit).  20 spins, 3135 terms: 15000 replicas 31 ms by terms, 0.2 ms by the
-// table; 64 replicas 19.7 against 0.17 ms; 21 = 3 x 7 (3 spins, 7 terms) stays
-// by terms.
-void dense_tables(sg_ctx* H, uint64_t off)
+// tables and run in rounds of as many instances as that holds.  Microseconds: a
+// step takes a round about 1.5, and its tables and launches about 20 and 2.2 per
+// MB; without a table a step takes about 1.5 and 0.45 per term of the picked
+// spin, for up to 12 wavefronts of 64 replicas per compute unit at once.  20
+// spins, 3135 terms: 15000 replicas 31 ms by terms, 0.2 ms by the table; 64
+// replicas 19.7 against 0.17 ms; 22 spins, 44 terms, 64 replicas, one pass 136
+// us by terms, 149 by the table, to convergence 442 and 234; 21 = 3 x 7 (3
+// spins, 7 terms) stays by terms.  k: the instances of a round.
+bool dense_pays(const sg_ctx* H, int64_t k, int passes)
 {
-    H->dense_tables = H->dense_table_n = 0;
     int64_t items = 0, insts = 0;
     double per_spin = 0.0;
     for (const HostInst& q : H->insts) {
         if (!q.dense || q.n > sg::kDenseTableMaxN) continue;
         ++insts;
         items += (q.R + 63) / 64;
-        H->dense_table_n = std::max(H->dense_table_n, q.n);
         per_spin = std::max(per_spin, (double)q.d_start[(size_t)q.n] / q.n);
+    }
+    const double steps = (double)passes * H->dense_table_n;
+    const double by_table = (double)((insts + k - 1) / k) * (20.0 + 1.5 * steps) + 2.2e-6 * (double)insts * (double)((int64_t)8 << H->dense_table_n);
+    return by_table < (1.5 + 0.45 * per_spin) * steps * std::max(1.0, (double)items / (12.0 * H->cus));
+}
+
+void dense_tables(sg_ctx* H, uint64_t off)
+{
+    H->dense_tables = H->dense_table_n = 0;
+    int64_t insts = 0;
+    for (const HostInst& q : H->insts) {
+        if (!q.dense || q.n > sg::kDenseTableMaxN) continue;
+        ++insts;
+        H->dense_table_n = std::max(H->dense_table_n, q.n);
     }
     if (!insts) return;
     const int64_t each = (int64_t)8 << H->dense_table_n;
     int64_t k = std::min<int64_t>(std::min<int64_t>(insts, 65535), ((int64_t)32 << 20) / each);
     // the tables take no handle beyond sg_bind_noalloc's workspace
     if (off <= SG_NOALLOC_MAX_BYTES) k = std::min<int64_t>(k, (int64_t)(SG_NOALLOC_MAX_BYTES - off) / each);
-    if (k < 1) return;
-    const double steps = 3.0 * H->dense_table_n;
-    const double by_table = (double)((insts + k - 1) / k) * (20.0 + 1.5 * steps);
-    const double by_terms = 0.45 * per_spin * steps * std::max(1.0, (double)items / (12.0 * 256.0));
-    if (by_table >= by_terms) return;
+    if (k < 1 || !dense_pays(H, k, 3)) return;
     H->dense_tables = (int32_t)k;
 }
 
@@ -2820,7 +2830,9 @@ sg_status run_dense(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
     SG_HIP(hipEventRecord(H->ev0, st), "event record");
     SG_HIP(hipEventRecord(H->evh0, st), "event record");
     H->hot_launches = 0;
-    if (p->max_sweeps > 0 && p->rule == SG_RULE_FM && H->dense_tables) {
+    H->last_dense_tables = 0;
+    if (p->max_sweeps > 0 && p->rule == SG_RULE_FM && H->dense_tables &&
+        dense_pays(H, H->dense_tables, std::min(p->max_sweeps, 3))) {
         // instances in order: those with a table in rounds of as many as the
         // workspace holds, runs of larger ones without
         const int count = (int)H->insts.size();
@@ -2833,6 +2845,7 @@ sg_status run_dense(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
                    (!tab || b - a < H->dense_tables))
                 ie += ((size_t)H->insts[(size_t)b++].R + 63) / 64;
             const sg::BlockItem* items = H->at<sg::BlockItem>(H->off_ditems) + it;
+            if (tab) H->last_dense_tables += b - a;
             if (tab)
                 SG_HIP(sg::launch_dense_fm_table(H->at<sg::DenseTab>(H->off_dtab), a, b - a, items, (int)(ie - it),
                                                  H->at<int64_t>(H->off_dense_table), H->dense_table_n, H->reps(),
@@ -4310,6 +4323,7 @@ sg_status sg_query(sg_handle H, const char* key, int64_t* value)
     else if (k == "msc_k") *value = H->msc_k;
     else if (k == "last_msc") *value = H->last_msc;
     else if (k == "last_bits") *value = H->last_bits;
+    else if (k == "last_dense_tables") *value = H->last_dense_tables;
     else if (k == "last_queue_grid") *value = H->last_queue_grid;
     else if (k == "last_queue_teams") *value = H->last_queue_teams;
     else if (k == "hot_ns") *value = (int64_t)(H->hot_us * 1000.0);
