@@ -2604,15 +2604,17 @@ sg_status run_block_schedule(sg_handle H, const sg_run_params* p, const std::vec
 // phase).  (100000 spins, 9 colours, 50 sweeps under TIE: 97.9 alone, 83.5, 50.8
 // and 37.2 in teams of 2, 4 and 8; 3-regular, 4 colours: 49.1, 44.3, 26.4,
 // 16.6.)  With the first k items in teams that end with the largest of the
-// others, a sweep takes that long, or the mean load of the workgroups and three
-// tenths for what an uneven queue leaves idle; and k teams cost the call 20 +
-// 1.2 k to begin.  k saves the most, in max_sweeps sweeps or the 0.7 ln n or so
-// until convergence (random graphs of degree 3 to 12: 4 to 6 for 200 spins, 6
-// to 12 for 100000), and at least a twelfth.  Kernel times with / without
-// teams: 48 graphs up to 101713 spins, 6 restarts, to convergence 701 / 1014 us,
-// 20 sweeps under TIE 1246 / 2109; 16 graphs up to 77277 spins 378 / 681, 854 /
-// 1653; 48 graphs up to 75186, 6 restarts, one sweep 198 / 127 (not taken), 20
-// sweeps 1432 / 1631.
+// others, a call takes that long, or the mean load of the workgroups and what
+// the teams' traffic and an uneven queue cost: six tenths with a fixed number of
+// sweeps, 0.15 until convergence, where the last items vary more; and k teams
+// cost the call 20 + 1.2 k to begin.  k saves the most, in max_sweeps sweeps or
+// the 0.7 ln n or so until convergence (random graphs of degree 3 to 12: 4 to 6
+// for 200 spins, 6 to 12 for 100000), and at least a twelfth.  Kernel times with
+// / without teams: 96 graphs with triples up to 100000 spins, 8 restarts, to
+// convergence 831..1037 / 965..1232 us over eight seeds (one 1024 / 999); 48
+// graphs up to 101713 spins, 6 restarts 701 / 1014, 20 sweeps under TIE 1246 /
+// 2109; 16 graphs up to 77277 spins 378 / 681, 854 / 1653; 48 graphs up to 75186,
+// 6 restarts, one sweep 198 / 127 (not taken), 20 sweeps 1432 / 1631.
 uint64_t queue_teams(sg_handle H, const sg_run_params* p, int n_big, int grid, size_t lds, sg::QueueTeams& teams)
 {
     if (H->team_wgs < 0 || !H->qteam_bytes || p->max_sweeps <= 0 || n_big < 1 || grid < 64 || H->queue_grid > 0) return 0;
@@ -2642,6 +2644,7 @@ uint64_t queue_teams(sg_handle H, const sg_run_params* p, int n_big, int grid, s
         rest += last;
     }
     for (int k = kQueueTeams; k > 0; --k) longest[(size_t)k - 1] = std::max(longest[(size_t)k - 1], longest[(size_t)k]);
+    const double idle = p->until_converged ? 1.15 : 1.6;
     const int most = std::min(grid * 9 / 10, kQueueTeamWgs);
     const double base = std::max(longest[0], rest / grid);
     double best = 0, least = 0;  // saved; the shortest that a team may take
@@ -2666,7 +2669,7 @@ uint64_t queue_teams(sg_handle H, const sg_run_params* p, int n_big, int grid, s
             load += c[(size_t)i].shared + c[(size_t)i].swap * g.back();
         }
         if (wgs > most) break;
-        const double t = std::max(end, 1.3 * load / grid), saved = base - t - 20.0 - 1.2 * k;
+        const double t = std::max(end, idle * load / grid), saved = base - t - 20.0 - 1.2 * k;
         if (t < base * 11 / 12 && saved > best) {
             best = saved;
             best_k = k;

@@ -4,10 +4,10 @@
 // rows of the sliced layout on lanes, couplings streamed from memory a slice
 // ahead, spins in LDS as bytes); small items run one per wavefront in a
 // private LDS window, 16 at a time.  Items that would outlast the rest run on
-// teams of workgroups first (QueueTeams).  Bound by the largest items: 96 instances
-// of 100 to 100000 spins, 8 restarts each: 1.07 ms a call (1.21 without
-// teams), against 2.43 ms
-// with loads under branches and an LDS wait per coupling.
+// teams of workgroups first (QueueTeams).  Bound by the largest items: 96 graphs
+// with triples of 100 to 100000 spins, 8 restarts each, 0.83 to 1.04 ms over
+// eight seeds (0.97 to 1.23 without teams; 2.43 with loads under branches and an
+// LDS wait per coupling).
 // Each replica runs to its own stopping point, and the replica state and the
 // call totals follow the per-phase kernels exactly: with until_converged a
 // replica stops after its first sweep without a flip (that sweep counts).
