@@ -1909,21 +1909,29 @@ sg_status run_phase_schedule(sg_handle H, const sg_run_params* p, const std::vec
 // phases does not earn back what a team costs to begin (the cooperative launch,
 // every member's copy of the spins): see team_pays.
 //
-// team_pays: microseconds of the call, against per-phase launches.  A team
-// begins 25 + 0.04 per 1000 spins + 0.3 per replica later, and saves 1.8 + 0.001
-// per 1000 spins, + 0.0028 per 1000 spins of every further replica, in a phase
-// (eight sweeps of them, or max_sweeps, until converged) and the per-phase
-// launches' check of the stopping rule, 45.  One sweep / five of a 3-regular
-// graph, team and per-phase launches: 60000 spins 79, 61 / 109, 121; 600000 102,
-// 61 / 147, 150; 60000, 31 replicas 88, 74 / 131, 201; 600000, 8 replicas 119,
-// 120 / 206, 438; a graph with triples (10 colours), 60000 spins 96, 89 / 186,
-// 291.  (One workgroup per replica is the faster from the first sweep: 6000
+// team_pays: microseconds of the call, against per-phase launches.  Over the
+// phases (max_sweeps sweeps of them, eight under GREEDY until converged) of rows
+// = n / C rows, R replicas: a launch 3.6 + 1.3e-5 rows R (4e-6 where rows are as
+// short as a chain's and GREEDY reads nothing else), a team's phase 1.7 + (3.5 +
+// 3.5 R) 1e-6 rows, under TIE 2.3 + (6.3 + 4.4 R) 1e-6 rows; a check of the
+// stopping rule 15, after two sweeps and six; a team begins 26 + 6e-5 n + 0.3 R
+// later (the cooperative launch, every member's copy of the spins).  One sweep
+// / five of a 3-regular graph, team and per-phase launches: 60000 spins 79, 61 /
+// 109, 121; 600000 102, 61 / 147, 150; 60000, 31 replicas 88, 74 / 131, 201;
+// 600000, 8 replicas 119, 120 / 206, 438; a graph with triples (10 colours),
+// 60000 spins 96, 89 / 186, 291; until converged under TIE four sweeps / twenty
+// of a 500 x 500 lattice 109, 116 / 238, 364, of a 1000 x 1000 one 168, 134 /
+// 422, 460; six sweeps / twelve of a chain of 20000 spins 92, 77 / 113, 116, four
+// replicas of 200000 116, 93 / 156, 145.  (One workgroup per replica is the faster from the first sweep: 6000
 // spins 51, 59 / 65, 122.)
 bool team_pays(const HostInst& q, const sg_run_params* p)
 {
-    const double phases = (double)q.C * (p->until_converged ? std::min(p->max_sweeps, 8) : p->max_sweeps);
-    const double save = phases * (1.8 + 1e-6 * q.n + 2.8e-6 * q.n * (q.R - 1)) + (p->until_converged && p->max_sweeps > 2 ? 45.0 : 0.0);
-    return save > 25.0 + 4e-5 * q.n + 0.3 * q.R;
+    const bool tie = p->rule == SG_RULE_GREEDY_TIE, uc = p->until_converged != 0;
+    const double sweeps = uc && !tie ? std::min(p->max_sweeps, 8) : p->max_sweeps, rows = (double)q.n / q.C;
+    const double launch = 3.6 + (tie || q.t > 0 || 5 * q.m > 6 * q.n ? 1.3e-5 : 4e-6) * rows * q.R;
+    const double phase = tie ? 2.3 + (6.3 + 4.4 * q.R) * 1e-6 * rows : 1.7 + (3.5 + 3.5 * q.R) * 1e-6 * rows;
+    const double checks = uc ? 15.0 * (sweeps > 2) + 15.0 * (sweeps > 6) : 0.0;
+    return sweeps * q.C * (launch - phase) + checks > 26.0 + 6e-5 * q.n + 0.3 * q.R;
 }
 
 int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)

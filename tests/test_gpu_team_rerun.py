@@ -57,8 +57,8 @@ def _check(insts, rule, uc, runs, pending, schedule, polls):
     h.free()
 
 
-CASES = [(GREEDY, True, [1000], True), (GREEDY, True, [1000], False), (GREEDY, True, [3], True),
-         (TIE, False, [5], False), (TIE, True, [2, 3, 9], False)]
+CASES = [(GREEDY, True, [1000], True), (GREEDY, True, [1000], False), (GREEDY, True, [4], True),
+         (TIE, False, [12], False), (TIE, True, [2, 3, 9], False)]
 
 
 @pytest.mark.parametrize("polls", [1, 0])

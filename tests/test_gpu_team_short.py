@@ -30,6 +30,23 @@ def test_short_calls(gpu, rule, uc, runs):
     h.free()
 
 
+@pytest.mark.parametrize("rule,runs", [(GREEDY, [(6, False), (30, True)]), (TIE, [(3, False), (12, True)])])
+def test_two_colours(gpu, rule, runs):
+    """A chain: two phases a sweep, and rows that cost a launch little."""
+    import paper_0912_3912_amd as sg
+    inst = gen.chain(40000, seed=1, periodic=True).replace(restarts=3)
+    st = None
+    h = sg.load_instance([inst]).bind()
+    h.init_spins(5)
+    for r, team in runs:
+        log(f"short calls on a chain: rule={rule} sweeps={r}")
+        st, _ = oracle.run(inst, seed=5, rule=rule, max_sweeps=r, until_converged=False, state=st, threads=8)
+        h.run_sweeps(seed=5, rule=rule, max_sweeps=r, until_converged=False)
+        assert (h.query("last_team") > 1) == team
+        compare(h, [inst], [st])
+    h.free()
+
+
 def test_given_team(gpu):
     """A given number of workgroups is used in calls of any length."""
     import paper_0912_3912_amd as sg
