@@ -157,6 +157,15 @@ struct HostInst {
     uint64_t off_dstart = 0, off_dmask = 0, off_dcoef = 0, off_tmask = 0, off_tcoef = 0, off_dorder = 0;
 };
 
+// What an instance adds to the estimates of choose_tie_bits: of a sweep and of
+// beginning and ending (microseconds), workgroups, wavefronts and compute units
+// held, on the bit-sliced kernel and on the byte kernel.
+struct TieCost {
+    bool bits = false, alone = false;  // the bit-sliced kernel can take it; a compute unit holds one byte workgroup
+    float bits_sweep = 0, bits_ends = 0, bits_wgs = 0, bits_waves = 0, bits_held = 0;
+    float byte_sweep = 0, byte_ends = 0, byte_wgs = 0;
+};
+
 }  // namespace
 
 struct sg_ctx {
@@ -176,6 +185,7 @@ struct sg_ctx {
     int32_t bits_groups = 8;           // most groups of 32 restarts per bit-sliced workgroup (2, 4, 8, 16)
     bool bits_groups_set = false;      // it has been given
     bool tie_bits = true;              // the current call's choice (choose_tie_bits)
+    std::vector<TieCost> tie_costs;    // its instances' part, built by the first call that asks
     int32_t fm_key32 = 1;              // FM moves chosen on 32-bit keys where the gains allow
     int32_t fm_waves = 0;              // most wavefronts per FM workgroup (0 = 16); the most resident are taken
     int32_t last_fm_waves = 0;         // what the last FM call used
@@ -1922,8 +1932,8 @@ sg_status run_phase_schedule(sg_handle H, const sg_run_params* p, const std::vec
 // 60000 spins 96, 89 / 186, 291; until converged under TIE four sweeps / twenty
 // of a 500 x 500 lattice 109, 116 / 238, 364, of a 1000 x 1000 one 168, 134 /
 // 422, 460; six sweeps / twelve of a chain of 20000 spins 92, 77 / 113, 116, four
-// replicas of 200000 116, 93 / 156, 145.  (One workgroup per replica is the faster from the first sweep: 6000
-// spins 51, 59 / 65, 122.)
+// replicas of 200000 116, 93 / 156, 145.  (One workgroup per replica is the
+// faster from the first sweep: 6000 spins 51, 59 / 65, 122.)
 bool team_pays(const HostInst& q, const sg_run_params* p)
 {
     const bool tie = p->rule == SG_RULE_GREEDY_TIE, uc = p->until_converged != 0;
@@ -2488,53 +2498,69 @@ bool bits_path(const sg_ctx* H, const sg_run_params* p, const HostInst& q)
 // 576; 512-spin Chimera, 8 groups 411 / 567, 1600 groups 475 / 1541; 1800 spins
 // of degree 2, 8 groups 2299 / 1311.  A given bits_groups asks for the
 // bit-sliced kernel.
-bool choose_tie_bits(const sg_ctx* H, const sg_run_params* p, const std::vector<int>& assign)
+TieCost tie_cost(const sg_ctx* H, const HostInst& q)
+{
+    TieCost c;
+    const double w = (2.0 * (double)q.m + 6.0 * (double)q.t) / q.n;
+    c.byte_sweep = (float)(0.55 * q.C + q.n / 16.0 * (0.25 + 0.089 * w));
+    c.byte_ends = (float)(3.3 / 64 * q.n);
+    c.byte_wgs = (float)((q.R + 63) / 64);
+    c.alone = sg::block_lds_bytes(q.n, (int)q.nbr.size(), (int)q.ta.size(), (int)q.slices.size(), q.C, 64) > 80 * 1024;
+    const double lds = (double)bits_lds_for(H, q, true);
+    c.bits = lds > 0;
+    if (!c.bits) return c;
+    double ew = 0, tw = 0;
+    for (const sg::Slice& S : q.slices) {
+        ew += S.ew;
+        tw += S.tw;
+    }
+    const double ng = std::min(8, bits_ng_for(H, q)), n = std::ceil(q.R / (32.0 * ng));
+    c.bits_sweep = (float)((2.9 + 0.69 * (double)q.slices.size() + 0.065 * (ew + 1.5 * tw) + 9.3 / 64 * q.ties) *
+                           (0.82 + 0.0225 * ng));
+    c.bits_ends = (float)(8.1 / 64 * q.n + 0.36 * (ew + tw) / ng);
+    c.bits_wgs = (float)n;
+    c.bits_waves = (float)(n * ng);
+    c.bits_held = (float)(n / std::max(1.0, std::floor(160.0 * 1024 / lds)));
+    return c;
+}
+
+bool choose_tie_bits(sg_ctx* H, const sg_run_params* p, const std::vector<int>& assign)
 {
     if (!H->block_bits || H->bits_groups_set) return true;
+    if (H->tie_costs.empty())  // sizes and structure only, at the default bits_groups
+        for (const HostInst& q : H->insts) H->tie_costs.push_back(tie_cost(H, q));
     const double cus = H->cus, T = p->until_converged ? std::min(p->max_sweeps, 30) : p->max_sweeps;
-    auto lds_bytes = [](const HostInst& q) {
-        return sg::block_lds_bytes(q.n, (int)q.nbr.size(), (int)q.ta.size(), (int)q.slices.size(), q.C, 64);
-    };
-    // the byte kernel on all instances, or on those that it alone can take
-    auto by_bytes = [&](bool every) {
-        double sweep = 0, ends = 0, wgs = 0, held = 2;
-        for (size_t k = 0; k < assign.size(); ++k) {
-            const HostInst& q = H->insts[k];
-            if (assign[k] != SG_SCHED_BLOCK || (!every && bits_lds_for(H, q, true))) continue;
-            const double w = (2.0 * (double)q.m + 6.0 * (double)q.t) / q.n;
-            sweep = std::max(sweep, 0.55 * q.C + q.n / 16.0 * (0.25 + 0.089 * w));
-            ends = std::max(ends, 3.3 / 64 * q.n);
-            wgs += (q.R + 63) / 64;
-            if (lds_bytes(q) > 80 * 1024) held = 1;
-        }
-        if (wgs == 0) return 0.0;
-        const double cap = held * cus, m = std::max(1.0, std::min(4.0, std::floor(wgs / cap)));
-        const double items = wgs / m, rounds = std::ceil(items / cap), last = items - (rounds - 1) * cap;
-        const double two = held > 1 ? 1.27 : 1.0;  // a compute unit that runs two of them
-        return 26.5 + ends + (1.45 * ends + 9.0) * wgs / cus +
-               T * sweep * m * ((rounds - 1) * two + (last > 1.05 * cus ? two : 1.0)) * (1.0 + 0.05 * std::min(1.0, wgs / cus));
-    };
+    // the byte kernel on all instances [1], or on those that it alone can take [0]
+    double bsweep[2] = {}, bends[2] = {}, bwgs[2] = {}, bheld[2] = {2, 2};
     double sweep = 0, ends = 0, wgs = 0, waves = 0, held = 0;
     for (size_t k = 0; k < assign.size(); ++k) {
-        const HostInst& q = H->insts[k];
-        const double lds = assign[k] == SG_SCHED_BLOCK ? (double)bits_lds_for(H, q, true) : 0.0;
-        if (!(lds > 0)) continue;
-        double ew = 0, tw = 0;
-        for (const sg::Slice& S : q.slices) {
-            ew += S.ew;
-            tw += S.tw;
+        if (assign[k] != SG_SCHED_BLOCK) continue;
+        const TieCost& c = H->tie_costs[k];
+        for (int e = c.bits ? 1 : 0; e < 2; ++e) {
+            bsweep[e] = std::max(bsweep[e], (double)c.byte_sweep);
+            bends[e] = std::max(bends[e], (double)c.byte_ends);
+            bwgs[e] += c.byte_wgs;
+            if (c.alone) bheld[e] = 1;
         }
-        const double ng = std::min(8, bits_ng_for(H, q)), n = std::ceil(q.R / (32.0 * ng));
-        sweep = std::max(sweep, (2.9 + 0.69 * (double)q.slices.size() + 0.065 * (ew + 1.5 * tw) + 9.3 / 64 * q.ties) *
-                                    (0.82 + 0.0225 * ng));
-        ends = std::max(ends, 8.1 / 64 * q.n + 0.36 * (ew + tw) / ng);
-        wgs += n;
-        waves += n * ng;
-        held += n / std::max(1.0, std::floor(160.0 * 1024 / lds));
+        if (!c.bits) continue;
+        sweep = std::max(sweep, (double)c.bits_sweep);
+        ends = std::max(ends, (double)c.bits_ends);
+        wgs += c.bits_wgs;
+        waves += c.bits_waves;
+        held += c.bits_held;
     }
+    auto by_bytes = [&](int e) {
+        if (bwgs[e] == 0) return 0.0;
+        const double cap = bheld[e] * cus, m = std::max(1.0, std::min(4.0, std::floor(bwgs[e] / cap)));
+        const double items = bwgs[e] / m, rounds = std::ceil(items / cap), last = items - (rounds - 1) * cap;
+        const double two = bheld[e] > 1 ? 1.27 : 1.0;  // a compute unit that runs two of them
+        return 26.5 + bends[e] + (1.45 * bends[e] + 9.0) * bwgs[e] / cus +
+               T * bsweep[e] * m * ((rounds - 1) * two + (last > 1.05 * cus ? two : 1.0)) *
+                   (1.0 + 0.05 * std::min(1.0, bwgs[e] / cus));
+    };
     const double by_bits = 30.0 + ends + 10.0 * wgs / cus +
                            T * sweep * (1.0 + 0.031 * std::min(waves / cus, 16.0)) * std::max(1.0, held / cus);
-    return by_bits + by_bytes(false) < by_bytes(true);
+    return by_bits + by_bytes(0) < by_bytes(1);
 }
 
 sg_status run_block_schedule(sg_handle H, const sg_run_params* p, const std::vector<int>& which_all)
