@@ -10,14 +10,15 @@
 // K & 255 and b; in the wide form a, b, K), unused entries with coefficient
 // zero, couplings among them naming the spin itself.  A wavefront
 // keeps its replica's half-gains v_e = -s_e f_e (int32), spins and move list
-// there, and the 64 leaf maxima (leaves of 64 spins) in registers; fmcore::run_pass moves the spins.
+// there, and the 64 leaf maxima (leaves of 64 spins) in registers;
+// fmcore::run_pass moves the spins.
 //
 // The kernel is bound by the latency of its serial chain of moves (see
 // fmcore::run_pass): a 50 x 50 +-J lattice with 62 restarts to convergence
-// takes 10.2 ms here, 0.37 us or 970 cycles a move (about 115 instructions and
-// four LDS round trips), against 107 ms on k_fm, whose lanes each rescan n / 64
+// takes 10.0 ms here, 0.40 us or 965 cycles a move (119 instructions and four
+// LDS round trips), against 107 ms on k_fm, whose lanes each rescan n / 64
 // spins one after another and look their rows up through the sliced layout;
-// with Gaussian int32 couplings 10.2 ms against 130 ms.  With the device full
+// with Gaussian int32 couplings 9.9 ms against 130 ms.  With the device full
 // (8192 restarts, two passes) 13.7 ms against 166 ms.  Building the rows counts
 // where they are many and the moves few: three passes of one replica of a
 // complete graph of 200 spins (a slice per spin) take 1.8 ms, 2.3 ms on k_fm, and

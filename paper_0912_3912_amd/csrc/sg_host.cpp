@@ -1906,15 +1906,15 @@ sg_status run_phase_schedule(sg_handle H, const sg_run_params* p, const std::vec
 // SG_SCHED_AUTO would otherwise give to per-phase launches; 0: not used.  A
 // workgroup's sixteen wavefronts take a phase's slices in turn, a microsecond
 // or so each, an exchange costs about two, and one workgroup needs no
-// cooperative launch.  Kernel times in microseconds, GREEDY to convergence /
-// 16 sweeps under TIE, 3-regular graphs (slices of the largest colour = n / 200
-// or so): per-phase launches, one workgroup, a team (members):
-//   6000 spins    139 / 297     49 / 106
-//   20000         144 / 308     79 / 227     91 / 200 (10)
-//   26000         146 / 312     91 / 271     91 / 197 (13)
-//   60000         272 / 317    181 / 555    104 / 214 (30)
-//   500000                                   136 / 284 (245)
-// With triples, 20000: 539 / 810, 268 / 501, 298 / 540 (7).  Teams of a twelfth
+// cooperative launch.  Calls of sg_run_sweeps in microseconds, GREEDY to
+// convergence / 16 sweeps under TIE, 3-regular graphs (slices of the largest
+// colour = n / 200 or so): per-phase launches, one workgroup, a team (members):
+//   6000 spins    181 / 305     65 / 123    104 / 215 (3)
+//   20000         187 / 319     99 / 239    111 / 218 (10)
+//   26000         184 / 323    112 / 291    110 / 214 (13)
+//   60000         186 / 330    188 / 561    117 / 226 (30)
+//   500000        334 / 394   1940 / 5969   155 / 310 (245)
+// With triples, 20000: 603 / 847, 269 / 487, 262 / 447 (7).  Teams of a twelfth
 // of the largest colour's slices are within 10% of the best.  A call of few
 // phases does not earn back what a team costs to begin (the cooperative launch,
 // every member's copy of the spins): see team_pays.

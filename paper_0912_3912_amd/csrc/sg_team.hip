@@ -7,8 +7,8 @@
 // of phases: LDS reads, the exchange's round trip through memory between
 // compute units, the barrier (and the traffic of the exchange: every member
 // reads every word of the phase).  500000 spins of a 3-regular graph to
-// convergence (7 sweeps of 4 colours): 160 us a call, against 330 us with
-// per-phase launches.
+// convergence (7 sweeps of 4 colours): the kernel 97 us, 3.5 us a phase; the
+// call (sg_run_sweeps) 155 us, against 334 us with per-phase launches.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -4,7 +4,7 @@
 //
 // Every workgroup holds the replica's whole spin configuration in LDS: one
 // byte per spin (a workgroup alone, up to 150000 spins), or one bit (set when
-// s = -1), so that up to 1.1 million spins fit; every partner read is an LDS
+// s = -1), so that up to 1.2 million spins fit; every partner read is an LDS
 // read.  Lane = row of a slice, a wavefront takes a phase's slices in turn.
 //
 // Bound by what a wavefront waits for, with 16 of them on a compute unit: so a

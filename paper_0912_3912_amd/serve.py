@@ -203,9 +203,11 @@ class Server:
         self.scratch = None
         self.shared_launches = 0
         self.shared_batch_sizes: List[int] = []
-        # Large lattices and replicas split over workgroups use co-resident
-        # launches; two such grids must not be resident at once (each could
-        # hold CUs the other needs), so they take turns.
+        # Large lattices and replicas split over workgroups use launches whose
+        # workgroups wait for one another.  Two such grids must not be resident
+        # at once (each could hold CUs the other needs): the runtime runs a
+        # process's cooperative launches one after another, and requests that
+        # make them take turns here, one whole run each.
         self.coop_lock = threading.Lock()
         self.loop_error: Optional[BaseException] = None
         self.loop = threading.Thread(target=self._group_loop, name="sg-shared-batch", daemon=True)
