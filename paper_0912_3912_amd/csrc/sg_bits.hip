@@ -520,7 +520,13 @@ __global__ __launch_bounds__(bits_threads<NG>()) void k_block_bits(const InstTab
                         bits_sum<N>(m, U);
                     };
                     int done;
-                    if (sew <= 3) {
+                    if (sew == 0) {  // the field alone (300 free spins, 600 restarts, 200 sweeps: 705 -> 447 us)
+                        uint32_t m[4];
+                        bits_mask(rw, xi ^ bits_sign(rw), m);
+#pragma unroll
+                        for (int p = 0; p < 8; ++p) U[p] = p < 4 ? m[p] : 0u;
+                        done = 0;
+                    } else if (sew <= 3) {
                         head(std::integral_constant<int, 4>{});
                         done = 3;
                     } else if (sew == 4) {
