@@ -2553,7 +2553,9 @@ bool choose_tie_bits(sg_ctx* H, const sg_run_params* p, const std::vector<int>& 
         if (bwgs[e] == 0) return 0.0;
         const double cap = bheld[e] * cus, m = std::max(1.0, std::min(4.0, std::floor(bwgs[e] / cap)));
         const double items = bwgs[e] / m, rounds = std::ceil(items / cap), last = items - (rounds - 1) * cap;
-        const double two = bheld[e] > 1 ? 1.27 : 1.0;  // a compute unit that runs two of them
+        // a compute unit that runs two of them, which share its issue the more the
+        // longer their rows keep them busy (32 spins 1.06..1.39, 400 spins 1.34..1.64)
+        const double two = bheld[e] > 1 ? 1.2 + 0.22 * std::min(1.0, bends[e] / 13.0) : 1.0;
         return 26.5 + bends[e] + (1.45 * bends[e] + 9.0) * bwgs[e] / cus +
                T * bsweep[e] * m * ((rounds - 1) * two + (last > 1.05 * cus ? two : 1.0)) *
                    (1.0 + 0.05 * std::min(1.0, bwgs[e] / cus));

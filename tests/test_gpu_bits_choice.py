@@ -57,6 +57,24 @@ def test_choice(gpu, name, uc):
         h.free()
 
 
+def test_sparse_full_device(gpu):
+    """Many ties on a device full of workgroups, where both kernels come close."""
+    import paper_0912_3912_amd as sg
+    insts = [gen.erdos_renyi_triples(400, seed=k, mean_degree=2, triples_per_spin=0.0, restarts=256, instance_id=k)
+             for k in range(256)]
+    log("block kernel under TIE: 256 sparse graphs, 50 sweeps")
+    h = sg.load_instance(insts).bind()
+    h.init_spins(3)
+    h.run_sweeps(seed=3, rule=TIE, max_sweeps=50, until_converged=False)
+    assert h.query("last_bits") == 1
+    E = h.energy()
+    assert (E == h.energy(recompute=True)).all()
+    for k in (0, 255):
+        st = oracle.run(insts[k], seed=3, rule=TIE, max_sweeps=50, until_converged=False, threads=8)[0]
+        assert (E[k * 256:(k + 1) * 256] == st.energy).all() and (h.spins_out_batch(k) == st.spins).all()
+    h.free()
+
+
 def test_autotuner_leaves_the_choice(gpu):
     """Applying a setting that changes nothing does not ask for a kernel."""
     import paper_0912_3912_amd as sg
