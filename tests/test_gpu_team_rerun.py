@@ -62,15 +62,12 @@ CASES = [(GREEDY, True, [1000], True), (GREEDY, True, [1000], False), (GREEDY, T
 
 
 @pytest.mark.parametrize("polls", [1, 0])
-@pytest.mark.parametrize("rule,uc,runs,pending", CASES)
-@pytest.mark.parametrize("name", ["regular", "lattice"])
+@pytest.mark.parametrize("name,rule,uc,runs,pending", [("regular", *c) for c in CASES] + [("lattice", *CASES[-1])])
 def test_team(gpu, name, rule, uc, runs, pending, polls):
     """A replica split by itself beside one that a workgroup takes; a lattice
     that only the stopping rule under TIE gives to the team kernel."""
     import paper_0912_3912_amd as sg
     if name == "lattice":
-        if (rule, uc) != (TIE, True):
-            pytest.skip("runs on the lattice kernels")
         insts = [gen.lattice((40, 40, 42), seed=6, h_range=(-2, 2), j_values=(-3, -1, 2), restarts=2, hint=True)]
     else:
         insts = [gen.random_regular3(70002, seed=6, instance_id=1, restarts=2),
