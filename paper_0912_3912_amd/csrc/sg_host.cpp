@@ -2953,6 +2953,107 @@ int fm_rows_waves(int most, int cus, F&& lds, G&& items)
     return best;
 }
 
+// The instances of at most kFmMaxN spins that the pass kernel with row tables in
+// LDS (sg_fm_rows.hip) takes, of those not on the lane kernel: it needs a
+// workgroup of one wavefront with its rows, and 32-bit keys allowed.  A move of
+// a wavefront is estimated, in microseconds, on either kernel.  With row tables:
+// 0.42; 0.62 for every 64 entries of rows beyond 64 (all rows are as wide as the
+// widest), 1.5 times that with hyper-couplings, which add 0.5 to narrow rows too;
+// filling the tables 0.0035 a word and call.
+// On the kernels of sg_fm.hip: 1.05 and 0.0005 n (1.35 and 0.0007 in the wide
+// form, much more beyond 512 spins, whose scan takes turns), 0.0072 (0.009) per
+// coupling of the mean row, 0.3 with hyper-couplings.  Wavefronts of a compute
+// unit share its issue (3% each); what it cannot hold at once runs in rounds:
+// wide tables leave room for few.  Fitted to 84 instances of 66 to 400 spins
+// (stars, hubs, random graphs of mean degree 2 to 199), 4 to 6000 replicas; old
+// kernels / row tables: star of 131 spins, 4 replicas, 4 passes 624 / 989 us, of
+// 60 spins 299 / 159; random of 100 spins, degree 79, 694 / 568; 6000 replicas,
+// two passes: of 300 spins, degree 90, 1911 / 3094, of 100 spins, degree 99, 1046
+// / 539, 20 hubs of degree 150 among 200 spins 12948 / 2074 (its staged copy
+// leaves room for three wavefronts).
+//
+// A handle's packed instances run in one launch of either kernel, one after the
+// other, and few replicas cost the chain of the slowest instance; so the launches
+// are compared as they are left by all instances on the kernel of their own, by
+// all that can be on row tables, and by none (12 instances of 100..760 spins
+// beside a complete graph of 400: 10.3 ms in two launches, 9.0 in one; 30 of
+// 200..1070 spins, the densest too large: 48 and 38 ms).  An instance in the wide
+// form has a launch of its own.
+template <class F>
+std::vector<char> fm_rows_choice(const sg_ctx* H, const sg_run_params* p, F&& on_lanes)
+{
+    std::vector<char> on(H->insts.size(), 0);
+    struct Est {
+        size_t k;
+        double rows, other;  // a pass; rows < 0: they do not fit
+    };
+    std::vector<Est> est;
+    int64_t reps = 0;
+    for (const HostInst& q : H->insts)
+        if (!q.dense && !q.wide && q.n <= kFmMaxN && !on_lanes(q)) reps += q.R;
+    const size_t lds_cu = 160 * 1024;
+    const double passes = std::max(1, std::min(p->max_sweeps, 5));
+    // a move where load wavefronts per compute unit run at most `held` at once
+    auto shared = [](double move, double load, double held) {
+        const double x = load / held, rounds = x <= 1.0 ? 1.0 : 0.5 * (x + std::ceil(x));
+        return move * rounds * (1.0 + 0.03 * std::min(load, held));
+    };
+    for (size_t k = 0; k < H->insts.size(); ++k) {
+        const HostInst& q = H->insts[k];
+        if (q.dense || q.n > kFmMaxN || on_lanes(q)) continue;
+        const double load = (double)(q.wide ? q.R : reps) / H->cus;
+        int32_t dc, tt;
+        fm_row_widths(q, dc, tt);
+        Est e{k, -1.0, 0.0};
+        // locked spins take the values below -2^31 + 4096
+        if (H->fm_key32 && q.max_w < INT32_MAX - kFmMaxN && sg::fm_rows_lds_bytes(q.n, dc, tt, q.wide, 1) <= kFmRowsLds) {
+            int64_t held = 1;
+            for (int w = 1; w <= 16; ++w) {
+                const size_t b = sg::fm_rows_lds_bytes(q.n, dc, tt, q.wide, w);
+                if (b > kFmRowsLds) break;
+                held = std::max(held, w * std::min<int64_t>((int64_t)(lds_cu / (b + 256)), 32 / w));
+            }
+            const double chunks = (dc + 63) / 64;
+            e.rows = q.n * (shared(dc > 64 ? 0.62 * chunks * (tt ? 1.5 : 1.0) : tt ? 0.92 : 0.42, load, (double)held) +
+                            3.5e-3 * (dc + 2 * tt) / passes);
+        }
+        const double w = 2.0 * (double)q.m / q.n;
+        const size_t stage = q.wide ? 0 : q.slices.size() * sizeof(sg::Slice) + q.nbr.size() * 4 + q.ta.size() * 8;
+        int64_t held = 1;
+        for (int v = 1; v <= 16; ++v) {
+            const size_t b = sg::fm_lds_bytes(q.n, v) + (sg::fm_lds_bytes(q.n, 1) + stage > kLdsBudget ? 0 : stage);
+            if (b <= kLdsBudget) held = std::max(held, v * std::min<int64_t>((int64_t)(lds_cu / b), 32 / v));
+        }
+        const double scan = q.wide ? std::max(1.35 + 7e-4 * q.n, 0.8 + 1.6e-3 * q.n)
+                                   : std::max(1.05 + 5e-4 * q.n, 0.6 + 1.35e-3 * q.n);
+        // (beyond the 4 MB of an L2 the sliced words come from further away)
+        const double far = q.nbr.size() * 4 > (size_t)4 << 20 && load > 8.0 ? 1.4 : 1.0;
+        e.other = q.n * shared(far * (scan + (q.wide ? 9e-3 : 7.2e-3) * w + (q.t > 0 ? 0.3 : 0.0)), load, (double)held);
+        if (q.wide) {
+            on[k] = e.rows >= 0.0 && e.rows < 1.08 * e.other;
+        } else {
+            est.push_back(e);
+        }
+    }
+    // what the packed launches take with row tables for all whose estimate is
+    // within `more` of the other kernel's
+    auto launches = [&](double more) {
+        double with = 0.0, without = 0.0;
+        for (const Est& e : est) {
+            if (e.rows >= 0.0 && e.rows < more * e.other) with = std::max(with, e.rows);
+            else without = std::max(without, e.other);
+        }
+        return with + without;
+    };
+    double more = 1.08;
+    if (reps <= 16 * H->cus) {
+        const double own = launches(1.08), all = launches(1e9), none = launches(0.0);
+        more = own <= std::min(all, none) ? 1.08 : all <= none ? 1e9 : 0.0;
+    }
+    for (const Est& e : est) on[e.k] = e.rows >= 0.0 && e.rows < more * e.other;
+    return on;
+}
+
 // The pass-based search (SG_RULE_FM): every replica of every instance is one
 // wavefront item, largest instances first.
 sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
@@ -2963,46 +3064,11 @@ sg_status run_fm(sg_handle H, const sg_run_params* p, sg_run_stats* stats)
     bool tri = false, key32 = true, rtri = false;
     int64_t lane_reps = 0, wave_reps = 0, row_reps = 0;
     auto on_lanes = [&](const HostInst& q) { return H->fm_lanes && q.fml_off != UINT64_MAX; };
-    // one replica per wavefront with the rows in LDS (sg_fm_rows.hip) where a
-    // workgroup of one wavefront holds them; the kernels of sg_fm.hip read
-    // what is larger from the sliced layout (dense graphs), and order moves
-    // on 64-bit keys when fm_key32 = 0 asks for them
-    bool rows = true;
-    auto on_rows = [&](const HostInst& q) {
-        if (!q.wide && !rows) return false;
-        if (on_lanes(q) || q.dense || q.n > kFmMaxN || !H->fm_key32) return false;
-        if (q.max_w >= INT32_MAX - kFmMaxN) return false;  // locked spins take the values below -2^31 + 4096
-        int32_t dc, tt;
-        fm_row_widths(q, dc, tt);
-        return sg::fm_rows_lds_bytes(q.n, dc, tt, q.wide != 0, 1) <= kFmRowsLds;
-    };
-    // The two packed kernels run one after the other, and few replicas cost the
-    // chain of the slowest instance: its spins times a move, about 0.4 us with
-    // row tables (0.8 in rows beyond 64 couplings or with hyper-couplings) and
-    // 0.008 per word of a row, 1.2 us, 1.15 per 1000 spins and 0.012 per word on
-    // the other kernel.  With instances left to the latter, a row-table launch
-    // beside it pays if the two chains end sooner than one launch of all, or if
-    // its replicas fill the device (12 instances of 100..760 spins beside a
-    // complete graph of 400: 10.3 ms in two launches, 9.0 in one; 30 of
-    // 200..1070 spins, the densest too large: 48 and 38 ms)
-    {
-        double with = 0.0, without = 0.0, rest = 0.0;  // chains: row tables, the same without, those left
-        int64_t reps = 0;
-        for (const HostInst& q : H->insts)
-            if (!q.wide && q.n <= kFmMaxN && !on_lanes(q)) {
-                int32_t dc, tt;
-                fm_row_widths(q, dc, tt);
-                const double other = q.n * (1.2 + 1.15e-3 * q.n + 0.012 * (dc + 2 * tt));
-                if (!on_rows(q)) {
-                    rest = std::max(rest, other);
-                    continue;
-                }
-                with = std::max(with, q.n * ((dc > 64 || tt ? 0.8 : 0.4) + 0.008 * (dc + 2 * tt)));
-                without = std::max(without, other);
-                reps += q.R;
-            }
-        rows = rest == 0.0 || with + rest < std::max(without, rest) || reps > 16 * H->cus;
-    }
+    // one replica per wavefront with the rows in LDS (sg_fm_rows.hip), or on the
+    // kernels of sg_fm.hip, which read them from the sliced layout (and order
+    // moves on 64-bit keys when fm_key32 = 0 asks for them)
+    const std::vector<char> rows = fm_rows_choice(H, p, on_lanes);
+    auto on_rows = [&](const HostInst& q) { return rows[(size_t)(&q - H->insts.data())] != 0; };
     const int most_waves = H->fm_waves ? std::min(H->fm_waves, 16) : 16;
     int64_t big_reps = 0;
     for (const HostInst& q : H->insts) {

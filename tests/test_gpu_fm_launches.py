@@ -46,3 +46,29 @@ def test_up_to_4096(gpu, dense, sparse, launches):
         insts.append(gen.complete_graph(dense, seed=1).replace(instance_id=9, restarts=2))
     log(f"pass kernels up to 4096 spins: complete graph of {dense} beside {sparse}")
     assert _run(insts, {"fm_lanes": 0}, 2) == launches
+
+
+@pytest.mark.parametrize("hub,passes,restarts,waves", [(150, 3, 4, False), (50, 3, 4, True), (110, 3, 4, True),
+                                                       (110, 1, 4, False)])
+def test_wide_rows(gpu, hub, passes, restarts, waves):
+    """One spin coupled to many others makes every row of a table as wide; the
+    table is left out where that costs more than the sliced rows (waves: the
+    launch has a row table's few wavefronts, one for few replicas)."""
+    import numpy as np
+    import paper_0912_3912_amd as sg
+    r = np.random.default_rng(3)
+    n = 200
+    j = np.arange(1, hub + 1, dtype=np.int32)
+    ring = np.arange(1, n - 1, dtype=np.int32)
+    e = np.concatenate([np.stack([np.zeros_like(j), j], 1), np.stack([ring, ring + 1], 1)])
+    if hub == 110:  # dense beside it: the sliced rows are long too
+        a, b = np.triu_indices(100, 2)
+        e = np.concatenate([e, np.stack([a + 1, b + 1], 1)]).astype(np.int32)
+    inst = gen.Instance(n, e[:, 0].copy(), e[:, 1].copy(), r.integers(-3, 4, len(e)), None).replace(restarts=restarts)
+    log(f"row tables: hub={hub} passes={passes}")
+    h = sg.load_instance([inst]).tune("fm_lanes", 0).bind()
+    h.init_spins(5)
+    h.run_sweeps(seed=5, rule=FM, max_sweeps=passes, until_converged=False)
+    assert (h.query("last_fm_waves") == 1) == waves
+    compare(h, [inst], [oracle.fm(inst, seed=5, max_passes=passes, until_converged=False, threads=8)[0]])
+    h.free()
