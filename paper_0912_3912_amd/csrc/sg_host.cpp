@@ -1921,10 +1921,11 @@ sg_status run_phase_schedule(sg_handle H, const sg_run_params* p, const std::vec
 //
 // team_pays: microseconds of the call, against per-phase launches.  Over the
 // phases (max_sweeps sweeps of them, eight under GREEDY until converged) of rows
-// = n / C rows, R replicas: a launch 3.6 + 1.3e-5 rows R (4e-6 where rows are as
-// short as a chain's and GREEDY reads nothing else), a team's phase 1.7 + (3.5 +
-// 3.5 R) 1e-6 rows, under TIE 2.3 + (6.3 + 4.4 R) 1e-6 rows; a check of the
-// stopping rule 15, after two sweeps and six; a team begins 26 + 6e-5 n + 0.3 R
+// = n / C rows, R replicas: a launch 3.6 + 1e-5 rows R (random graphs 1.3e-5,
+// lattices 6e-6; 4e-6 where rows are as short as a chain's; 1.3e-5 under TIE), a
+// team's phase 1.7 + (3.5 + 3.5 R) 1e-6 rows, under TIE 2.3 + (6.3 + 4.4 R) 1e-6
+// rows; a check of the stopping rule 15, after two sweeps and six; a team begins
+// 30 + 6e-5 n + 0.3 R
 // later (the cooperative launch, every member's copy of the spins).  One sweep
 // / five of a 3-regular graph, team and per-phase launches: 60000 spins 79, 61 /
 // 109, 121; 600000 102, 61 / 147, 150; 60000, 31 replicas 88, 74 / 131, 201;
@@ -1938,10 +1939,10 @@ bool team_pays(const HostInst& q, const sg_run_params* p)
 {
     const bool tie = p->rule == SG_RULE_GREEDY_TIE, uc = p->until_converged != 0;
     const double sweeps = uc && !tie ? std::min(p->max_sweeps, 8) : p->max_sweeps, rows = (double)q.n / q.C;
-    const double launch = 3.6 + (tie || q.t > 0 || 5 * q.m > 6 * q.n ? 1.3e-5 : 4e-6) * rows * q.R;
+    const double launch = 3.6 + (tie ? 1.3e-5 : q.t > 0 || 5 * q.m > 6 * q.n ? 1e-5 : 4e-6) * rows * q.R;
     const double phase = tie ? 2.3 + (6.3 + 4.4 * q.R) * 1e-6 * rows : 1.7 + (3.5 + 3.5 * q.R) * 1e-6 * rows;
     const double checks = uc ? 15.0 * (sweeps > 2) + 15.0 * (sweeps > 6) : 0.0;
-    return sweeps * q.C * (launch - phase) + checks > 26.0 + 6e-5 * q.n + 0.3 * q.R;
+    return sweeps * q.C * (launch - phase) + checks > 30.0 + 6e-5 * q.n + 0.3 * q.R;
 }
 
 int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
@@ -3434,12 +3435,15 @@ bool defer_unit_energy(const sg_ctx* H)
     return true;
 }
 
-// The run writes the final energies of a deferred instance itself.
+// The run writes the final energies of a deferred instance itself.  (One or two
+// sweeps of the team kernel converge from next to no start, and energies computed
+// after the run cost one more wait: 289 spins, one sweep 94 us, 83 with them
+// first.)
 bool run_writes_energy(const sg_ctx* H, const sg_run_params* p, int kind, int sched, const HostInst& q)
 {
     if (kind == 1) return sched == SG_SCHED_BLOCK && bits_path(H, p, q);
     if (sched == SG_SCHED_LATTICE) return lattice_msc_bound(H, q) && !p->until_converged && p->max_sweeps > 0;
-    if (sched == SG_SCHED_PHASE) return p->until_converged && team_groups(H, q, p) > 0;
+    if (sched == SG_SCHED_PHASE) return p->until_converged && p->max_sweeps > 2 && team_groups(H, q, p) > 0;
     return sched == SG_SCHED_QUEUE && p->until_converged && p->max_sweeps > 0;
 }
 

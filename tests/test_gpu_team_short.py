@@ -58,3 +58,21 @@ def test_given_team(gpu):
     h.run_sweeps(seed=3, rule=TIE, max_sweeps=1, until_converged=False)
     assert h.query("last_team") == 5
     h.free()
+
+
+@pytest.mark.parametrize("rule", [GREEDY, TIE])
+def test_few_sweeps(gpu, rule):
+    """One or two sweeps until converged on one workgroup per replica: from random
+    starts and from where nothing moves."""
+    import paper_0912_3912_amd as sg
+    inst = gen.chain(289, seed=1, periodic=True).replace(restarts=5)
+    log(f"few sweeps until converged: rule={rule}")
+    h = sg.load_instance([inst]).bind()
+    h.init_spins(5)
+    st = None
+    for r in (1, 2, 40, 1, 2):
+        st, _ = oracle.run(inst, seed=5, rule=rule, max_sweeps=r, until_converged=True, state=st, threads=8)
+        h.run_sweeps(seed=5, rule=rule, max_sweeps=r, until_converged=True)
+        assert h.query("last_team") == 1 and h.query("energy_pending") == 0
+        compare(h, [inst], [st])
+    h.free()
