@@ -162,6 +162,7 @@ struct HostInst {
 // held, on the bit-sliced kernel and on the byte kernel.
 struct TieCost {
     bool bits = false, alone = false;  // the bit-sliced kernel can take it; a compute unit holds one byte workgroup
+    int ng = 0;                        // groups of a bit-sliced workgroup: one launch for each
     float bits_sweep = 0, bits_ends = 0, bits_wgs = 0, bits_waves = 0, bits_held = 0;
     float byte_sweep = 0, byte_ends = 0, byte_wgs = 0;
 };
@@ -2489,7 +2490,8 @@ bool bits_path(const sg_ctx* H, const sg_run_params* p, const HostInst& q)
 // to begin.  So both are estimated, in microseconds: a sweep of the slowest
 // instance (bit-sliced: slices, their coupling words, and ties, 32 restarts of
 // them drawn 64 at a time; bytes: colours, and rows with w coupling words) times
-// the rounds of workgroups that the device takes, and the time to begin and end.
+// the rounds of workgroups that the device takes, and the time to begin and end,
+// for each launch (instances of other restart counts have other workgroups).
 // Fitted to 665 batches of 32..1800 spins and 1..3200 groups of 32 restarts
 // (random graphs of degree 2, 3, 5 and 10, +-1 and up to +-15, with and without
 // hyper-couplings, Chimera, lattices, rings), 3, 20 and 60 sweeps: the choice is
@@ -2506,6 +2508,7 @@ TieCost tie_cost(const sg_ctx* H, const HostInst& q)
     c.byte_sweep = (float)(0.55 * q.C + q.n / 16.0 * (0.25 + 0.089 * w));
     c.byte_ends = (float)(3.3 / 64 * q.n);
     c.byte_wgs = (float)((q.R + 63) / 64);
+    c.ng = bits_ng_for(H, q);
     c.alone = sg::block_lds_bytes(q.n, (int)q.nbr.size(), (int)q.ta.size(), (int)q.slices.size(), q.C, 64) > 80 * 1024;
     const double lds = (double)bits_lds_for(H, q, true);
     c.bits = lds > 0;
@@ -2531,39 +2534,47 @@ bool choose_tie_bits(sg_ctx* H, const sg_run_params* p, const std::vector<int>& 
     if (H->tie_costs.empty())  // sizes and structure only, at the default bits_groups
         for (const HostInst& q : H->insts) H->tie_costs.push_back(tie_cost(H, q));
     const double cus = H->cus, T = p->until_converged ? std::min(p->max_sweeps, 30) : p->max_sweeps;
-    // the byte kernel on all instances [1], or on those that it alone can take [0]
-    double bsweep[2] = {}, bends[2] = {}, bwgs[2] = {}, bheld[2] = {2, 2};
-    double sweep = 0, ends = 0, wgs = 0, waves = 0, held = 0;
+    struct Launch {
+        double sweep = 0, ends = 0, wgs = 0, waves = 0, held = 0;
+    };
+    // the byte kernel on all instances [1], or on those that it alone can take
+    // [0], and the bit-sliced kernel with 2, 4, 8 groups per workgroup
+    Launch bytes[2], bits[3];
     for (size_t k = 0; k < assign.size(); ++k) {
         if (assign[k] != SG_SCHED_BLOCK) continue;
         const TieCost& c = H->tie_costs[k];
         for (int e = c.bits ? 1 : 0; e < 2; ++e) {
-            bsweep[e] = std::max(bsweep[e], (double)c.byte_sweep);
-            bends[e] = std::max(bends[e], (double)c.byte_ends);
-            bwgs[e] += c.byte_wgs;
-            if (c.alone) bheld[e] = 1;
+            Launch& l = bytes[e];
+            l.sweep = std::max(l.sweep, (double)c.byte_sweep);
+            l.ends = std::max(l.ends, (double)c.byte_ends);
+            l.wgs += c.byte_wgs;
+            if (c.alone) l.held = 1;  // workgroups that a compute unit holds, 0: two
         }
         if (!c.bits) continue;
-        sweep = std::max(sweep, (double)c.bits_sweep);
-        ends = std::max(ends, (double)c.bits_ends);
-        wgs += c.bits_wgs;
-        waves += c.bits_waves;
-        held += c.bits_held;
+        Launch& l = bits[c.ng <= 2 ? 0 : c.ng <= 4 ? 1 : 2];
+        l.sweep = std::max(l.sweep, (double)c.bits_sweep);
+        l.ends = std::max(l.ends, (double)c.bits_ends);
+        l.wgs += c.bits_wgs;
+        l.waves += c.bits_waves;
+        l.held += c.bits_held;
     }
-    auto by_bytes = [&](int e) {
-        if (bwgs[e] == 0) return 0.0;
-        const double cap = bheld[e] * cus, m = std::max(1.0, std::min(4.0, std::floor(bwgs[e] / cap)));
-        const double items = bwgs[e] / m, rounds = std::ceil(items / cap), last = items - (rounds - 1) * cap;
+    auto by_bytes = [&](const Launch& l) {
+        if (l.wgs == 0) return 0.0;
+        const double cap = (l.held > 0 ? 1 : 2) * cus, m = std::max(1.0, std::min(4.0, std::floor(l.wgs / cap)));
+        const double items = l.wgs / m, rounds = std::ceil(items / cap), last = items - (rounds - 1) * cap;
         // a compute unit that runs two of them, which share its issue the more the
         // longer their rows keep them busy (32 spins 1.06..1.39, 400 spins 1.34..1.64)
-        const double two = bheld[e] > 1 ? 1.2 + 0.22 * std::min(1.0, bends[e] / 13.0) : 1.0;
-        return 26.5 + bends[e] + (1.45 * bends[e] + 9.0) * bwgs[e] / cus +
-               T * bsweep[e] * m * ((rounds - 1) * two + (last > 1.05 * cus ? two : 1.0)) *
-                   (1.0 + 0.05 * std::min(1.0, bwgs[e] / cus));
+        const double two = l.held > 0 ? 1.0 : 1.2 + 0.22 * std::min(1.0, l.ends / 13.0);
+        return 26.5 + l.ends + (1.45 * l.ends + 9.0) * l.wgs / cus +
+               T * l.sweep * m * ((rounds - 1) * two + (last > 1.05 * cus ? two : 1.0)) *
+                   (1.0 + 0.05 * std::min(1.0, l.wgs / cus));
     };
-    const double by_bits = 30.0 + ends + 10.0 * wgs / cus +
-                           T * sweep * (1.0 + 0.031 * std::min(waves / cus, 16.0)) * std::max(1.0, held / cus);
-    return by_bits + by_bytes(0) < by_bytes(1);
+    double by_bits = 0.0;
+    for (const Launch& l : bits)
+        if (l.wgs > 0)
+            by_bits += 30.0 + l.ends + 10.0 * l.wgs / cus +
+                       T * l.sweep * (1.0 + 0.031 * std::min(l.waves / cus, 16.0)) * std::max(1.0, l.held / cus);
+    return by_bits + by_bytes(bytes[0]) < by_bytes(bytes[1]);
 }
 
 sg_status run_block_schedule(sg_handle H, const sg_run_params* p, const std::vector<int>& which_all)

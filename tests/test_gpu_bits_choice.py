@@ -25,6 +25,10 @@ CASES = {  # instances, knobs, whether the bit-sliced kernel runs under TIE
     "given": (lambda: _er(200, 2, 64), {"bits_groups": 8}, 1),
     "many": (lambda: _er(72, 500, 256), {}, 1),
     "chimera": (lambda: [gen.chimera(8, 8, seed=k, instance_id=k, restarts=64) for k in range(4)], {}, 1),
+    # one launch for every number of groups per workgroup: two in turn lose
+    "chimera, lattices": (lambda: [gen.chimera(11, 11, seed=1, instance_id=1, restarts=117)] +
+                          [gen.lattice((20, 20), seed=2, instance_id=2, restarts=58)], {}, 0),
+    "chimera of 968": (lambda: [gen.chimera(11, 11, seed=1, instance_id=1, restarts=117)], {}, 1),
     "mixed": (lambda: _er(64, 2, 64) + [gen.random_regular3(300, seed=5, j_range=(-40, 40), instance_id=9, restarts=64)],
               {}, 0),
 }
