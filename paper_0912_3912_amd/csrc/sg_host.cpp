@@ -124,7 +124,7 @@ struct HostInst {
     int32_t fml_dc = 0, fml_tt = 0;    // coupling words / hyper-couplings per row
     int32_t bits_ok = 0;               // at most 2048 spins, every |coefficient| <= 15 and per spin
                                        // sum |c| <= 255 (bit-sliced block kernel)
-    float ties = 0.f;                  // with bits_ok: spins expected to be tied in a sweep
+    float ties = 0.f, even = 0.f;      // with bits_ok: spins expected to be tied in a sweep, and that can be
     // last tiling decision and the settings it was made for (rule, knobs)
     mutable std::array<int32_t, 6> tile_key{{-1, -1, -1, -1, -1, -1}};
     mutable sg::TileGeom tile_geom{};
@@ -1139,7 +1139,7 @@ sg_status ingest(const sg_instance_desc& d, int idx, HostInst& q)
         }
     } else {
         bool ok = true;
-        float ties = 0.f;
+        float ties = 0.f, even = 0.f;
         for (int32_t i = 0; i < n; ++i) {
             int32_t W = std::abs((int32_t)q.h[i]), sq = W * W, most = W;
             auto term = [&](uint32_t w) {
@@ -1152,10 +1152,14 @@ sg_status ingest(const sg_instance_desc& d, int idx, HostInst& q)
             for (int64_t k = ts[i]; k < ts[i + 1]; ++k) term(twa[k]);
             q.max_w = std::max<int64_t>(q.max_w, W);
             ok = ok && most <= 15 && W <= 255;
-            if (ok && W % 2 == 0) ties += tied[(size_t)sq];
+            if (ok && W % 2 == 0) {
+                ties += tied[(size_t)sq];
+                even += 1.f;
+            }
         }
         q.bits_ok = ok ? 1 : 0;
         q.ties = ties;
+        q.even = even;
     }
     if (n <= kLaneStartMaxN) {
         for (int32_t i = 0; i < n; ++i)
@@ -1926,7 +1930,7 @@ sg_status run_phase_schedule(sg_handle H, const sg_run_params* p, const std::vec
 // lattices 6e-6; 4e-6 where rows are as short as a chain's; 1.3e-5 under TIE), a
 // team's phase 1.7 + (3.5 + 3.5 R) 1e-6 rows, under TIE 2.3 + (6.3 + 4.4 R) 1e-6
 // rows; a check of the stopping rule 15, after two sweeps and six; a team begins
-// 30 + 6e-5 n + 0.3 R
+// 35 + 6e-5 n + 0.3 R
 // later (the cooperative launch, every member's copy of the spins).  One sweep
 // / five of a 3-regular graph, team and per-phase launches: 60000 spins 79, 61 /
 // 109, 121; 600000 102, 61 / 147, 150; 60000, 31 replicas 88, 74 / 131, 201;
@@ -1938,12 +1942,13 @@ sg_status run_phase_schedule(sg_handle H, const sg_run_params* p, const std::vec
 // faster from the first sweep: 6000 spins 51, 59 / 65, 122.)
 bool team_pays(const HostInst& q, const sg_run_params* p)
 {
+    if (q.C == 1) return false;  // no couplings, nothing to exchange (300000 spins, 40 sweeps under TIE: 340 us, 284)
     const bool tie = p->rule == SG_RULE_GREEDY_TIE, uc = p->until_converged != 0;
     const double sweeps = uc && !tie ? std::min(p->max_sweeps, 8) : p->max_sweeps, rows = (double)q.n / q.C;
     const double launch = 3.6 + (tie ? 1.3e-5 : q.t > 0 || 5 * q.m > 6 * q.n ? 1e-5 : 4e-6) * rows * q.R;
     const double phase = tie ? 2.3 + (6.3 + 4.4 * q.R) * 1e-6 * rows : 1.7 + (3.5 + 3.5 * q.R) * 1e-6 * rows;
     const double checks = uc ? 15.0 * (sweeps > 2) + 15.0 * (sweeps > 6) : 0.0;
-    return sweeps * q.C * (launch - phase) + checks > 30.0 + 6e-5 * q.n + 0.3 * q.R;
+    return sweeps * q.C * (launch - phase) + checks > 35.0 + 6e-5 * q.n + 0.3 * q.R;
 }
 
 int team_groups(const sg_ctx* H, const HostInst& q, const sg_run_params* p)
@@ -2488,14 +2493,16 @@ bool bits_path(const sg_ctx* H, const sg_run_params* p, const HostInst& q)
 // walks all slices of 32 restarts and draws their ties 64 at a time can lose to
 // sixteen wavefronts that share the rows of 64 restarts; it also takes longer
 // to begin.  So both are estimated, in microseconds: a sweep of the slowest
-// instance (bit-sliced: slices, their coupling words, and ties, 32 restarts of
-// them drawn 64 at a time; bytes: colours, and rows with w coupling words) times
-// the rounds of workgroups that the device takes, and the time to begin and end,
-// for each launch (instances of other restart counts have other workgroups).
-// Fitted to 665 batches of 32..1800 spins and 1..3200 groups of 32 restarts
-// (random graphs of degree 2, 3, 5 and 10, +-1 and up to +-15, with and without
-// hyper-couplings, Chimera, lattices, rings), 3, 20 and 60 sweeps: the choice is
-// within 5% of the better kernel in 95 of 100, within 1% on average.  20
+// instance (tie_cost; bit-sliced: the slices' words, and for a slice the rounds
+// in which its rows' ties are queued and drawn, as many as its most tied row has
+// restarts tied; bytes: colours, slices, rows and their words, and rows that can
+// be tied) times the rounds of workgroups that the device takes, and the time to
+// begin and end, for each launch (instances of other restart counts have other
+// workgroups).  Fitted to 1684 batches of 32..1800 spins and 1..3200 groups of 32
+// restarts (random graphs of degree 2, 3, 5 and 10, +-1 and up to +-15, with and
+// without hyper-couplings, Chimera, lattices with and without fields, rings), 10,
+// 20 and 400 sweeps: the choice is within 5% of the better kernel in 95 of 100,
+// within 1% on average, and leans to bytes where both are close.  20
 // sweeps, bit-sliced / bytes: 200 spins of degree 5, 8 groups 508 / 355 us, 1600
 // groups 577 / 995; 32 spins of degree 2, 8 groups 185 / 89, 3200 groups 351 /
 // 576; 512-spin Chimera, 8 groups 411 / 567, 1600 groups 475 / 1541; 1800 spins
@@ -2504,8 +2511,16 @@ bool bits_path(const sg_ctx* H, const sg_run_params* p, const HostInst& q)
 TieCost tie_cost(const sg_ctx* H, const HostInst& q)
 {
     TieCost c;
-    const double w = (2.0 * (double)q.m + 6.0 * (double)q.t) / q.n;
-    c.byte_sweep = (float)(0.55 * q.C + q.n / 16.0 * (0.25 + 0.089 * w));
+    double ew = 0, tw = 0, rew = 0, rtw = 0;  // coupling and hyper-coupling words of the slices, and of their rows
+    for (const sg::Slice& S : q.slices) {
+        ew += S.ew;
+        tw += S.tw;
+        rew += (double)S.ew * S.rows;
+        rtw += (double)S.tw * S.rows;
+    }
+    const double sl = (double)q.slices.size(), ts = q.ties / std::max(1.0, sl);
+    c.byte_sweep = (float)(0.41 * q.C + 0.23 * sl +
+                           (0.08 * q.n + 0.036 * rew + 0.109 * rtw + 0.31 * q.ties + 0.3 * q.even) / 16.0);
     c.byte_ends = (float)(3.3 / 64 * q.n);
     c.byte_wgs = (float)((q.R + 63) / 64);
     c.ng = bits_ng_for(H, q);
@@ -2513,14 +2528,9 @@ TieCost tie_cost(const sg_ctx* H, const HostInst& q)
     const double lds = (double)bits_lds_for(H, q, true);
     c.bits = lds > 0;
     if (!c.bits) return c;
-    double ew = 0, tw = 0;
-    for (const sg::Slice& S : q.slices) {
-        ew += S.ew;
-        tw += S.tw;
-    }
     const double ng = std::min(8, bits_ng_for(H, q)), n = std::ceil(q.R / (32.0 * ng));
-    c.bits_sweep = (float)((2.9 + 0.69 * (double)q.slices.size() + 0.065 * (ew + 1.5 * tw) + 9.3 / 64 * q.ties) *
-                           (0.82 + 0.0225 * ng));
+    c.bits_sweep = (float)((1.46 + 0.069 * ew + 0.113 * tw + sl * (0.3 * std::min(ts, 1.0) + 0.55 * std::sqrt(ts))) *
+                           (0.95 + 0.026 * ng));
     c.bits_ends = (float)(8.1 / 64 * q.n + 0.36 * (ew + tw) / ng);
     c.bits_wgs = (float)n;
     c.bits_waves = (float)(n * ng);
@@ -2564,7 +2574,7 @@ bool choose_tie_bits(sg_ctx* H, const sg_run_params* p, const std::vector<int>& 
         const double items = l.wgs / m, rounds = std::ceil(items / cap), last = items - (rounds - 1) * cap;
         // a compute unit that runs two of them, which share its issue the more the
         // longer their rows keep them busy (32 spins 1.06..1.39, 400 spins 1.34..1.64)
-        const double two = l.held > 0 ? 1.0 : 1.2 + 0.22 * std::min(1.0, l.ends / 13.0);
+        const double two = l.held > 0 ? 1.0 : 1.1 + 0.3 * std::min(1.0, l.ends / 13.0);
         return 26.5 + l.ends + (1.45 * l.ends + 9.0) * l.wgs / cus +
                T * l.sweep * m * ((rounds - 1) * two + (last > 1.05 * cus ? two : 1.0)) *
                    (1.0 + 0.05 * std::min(1.0, l.wgs / cus));
@@ -2574,7 +2584,7 @@ bool choose_tie_bits(sg_ctx* H, const sg_run_params* p, const std::vector<int>& 
         if (l.wgs > 0)
             by_bits += 30.0 + l.ends + 10.0 * l.wgs / cus +
                        T * l.sweep * (1.0 + 0.031 * std::min(l.waves / cus, 16.0)) * std::max(1.0, l.held / cus);
-    return by_bits + by_bytes(bytes[0]) < by_bytes(bytes[1]);
+    return 1.06 * by_bits + by_bytes(bytes[0]) < by_bytes(bytes[1]);
 }
 
 sg_status run_block_schedule(sg_handle H, const sg_run_params* p, const std::vector<int>& which_all)

@@ -28,6 +28,7 @@ CASES = {  # instances, knobs, whether the bit-sliced kernel runs under TIE
     # one launch for every number of groups per workgroup: two in turn lose
     "chimera, lattices": (lambda: [gen.chimera(11, 11, seed=1, instance_id=1, restarts=117)] +
                           [gen.lattice((20, 20), seed=2, instance_id=2, restarts=58)], {}, 0),
+    "lattice with fields": (lambda: [gen.lattice((22, 24), seed=3, h_range=(-2, 2), instance_id=1, restarts=113)], {}, 0),
     "chimera of 968": (lambda: [gen.chimera(11, 11, seed=1, instance_id=1, restarts=117)], {}, 1),
     "mixed": (lambda: _er(64, 2, 64) + [gen.random_regular3(300, seed=5, j_range=(-40, 40), instance_id=9, restarts=64)],
               {}, 0),
@@ -41,7 +42,7 @@ def test_choice(gpu, name, uc):
     make, knobs, bits = CASES[name]
     insts = make()
     schedules = (sg.SCHED_AUTO, sg.SCHED_BLOCK) if name != "many" else (sg.SCHED_AUTO,)
-    ref = [oracle.run(i, seed=3, rule=TIE, max_sweeps=5, until_converged=uc, threads=8)[0] for i in insts[:40]]
+    ref = [oracle.run(i, seed=3, rule=TIE, max_sweeps=20, until_converged=uc, threads=8)[0] for i in insts[:40]]
     for schedule in schedules:
         log(f"block kernel under TIE: {name} schedule={schedule} uc={uc}")
         h = sg.load_instance(insts)
@@ -49,7 +50,7 @@ def test_choice(gpu, name, uc):
             h.tune(k, v)
         h.bind()
         h.init_spins(3)
-        h.run_sweeps(seed=3, rule=TIE, max_sweeps=5, until_converged=uc, schedule=schedule)
+        h.run_sweeps(seed=3, rule=TIE, max_sweeps=20, until_converged=uc, schedule=schedule)
         assert h.query("last_bits") == bits
         if name == "many":
             E = h.energy()

@@ -76,3 +76,19 @@ def test_few_sweeps(gpu, rule):
         assert h.query("last_team") == 1 and h.query("energy_pending") == 0
         compare(h, [inst], [st])
     h.free()
+
+
+@pytest.mark.parametrize("rule,uc", [(GREEDY, True), (TIE, False)])
+def test_no_couplings(gpu, rule, uc):
+    import numpy as np
+    import paper_0912_3912_amd as sg
+    e = np.zeros(0, np.int32)
+    inst = gen.Instance(70001, e, e, e, np.random.default_rng(1).integers(-1, 2, 70001))
+    log(f"no couplings: rule={rule} uc={uc}")
+    st, _ = oracle.run(inst, seed=5, rule=rule, max_sweeps=25, until_converged=uc, threads=8)
+    h = sg.load_instance([inst]).bind()
+    h.init_spins(5)
+    h.run_sweeps(seed=5, rule=rule, max_sweeps=25, until_converged=uc)
+    assert h.query("last_team") == 0
+    compare(h, [inst], [st])
+    h.free()
